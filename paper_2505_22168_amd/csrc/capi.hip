@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "contract_lanes.h"
 #include "model.h"
 #include "neighbors.h"
 #include "pair_math.h"
@@ -650,7 +651,10 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
                            phases);
       } else {
         mark(2);
-        st = launch_tile(false, var, 16, db, ds, bf16, psi, atomic_e, psibar, nullptr, nullptr, gstride, nullptr, s);
+        float* dg = (float*)(W + L.dg);
+        st = launch_tile(false, var, 16, db, ds, bf16, psi, atomic_e, var ? psibar : dg, nullptr, nullptr, gstride,
+                         nullptr, s);
+        if (st == GMNN_OK && !var) st = launch_contract_back(N, 1, psi, dg, psibar, s);
         for (int k = 3; k < 8; ++k) mark(k);
       }
       if (st != GMNN_OK) return st;

@@ -9,13 +9,14 @@
 //                     every weight fragment fetched from L2 feeds 2 to 4 MFMA
 //                     row blocks, 1/2 to 1/4 of the L2 traffic per atom of
 //                     the 16-row tile
-//   readout_backward  product-rule backward of the invariants, 8 atoms per
-//                     block -> dE/dPsi [N][100]
+//   contract_back     product-rule backward of the invariants, one atom per
+//                     lane -> dE/dPsi [N][100] (contract_lanes.hip)
 //
 // The arithmetic is the tile's, operation for operation (same contraction
-// code, same MFMA shapes and k order, same epilogues), so both give the same
-// result up to FP32 summation order.
+// code, same MFMA shapes and k order, same epilogues; the same backward
+// kernel follows both), so both give the same result bit for bit.
 #include "common.h"
+#include "contract_lanes.h"
 #include "contraction.h"
 #include "mfma.h"
 #include "model.h"
@@ -156,7 +157,7 @@ __device__ inline void split_pre(bf16x8 (&bh)[kPfSplit][TPW], bf16x8 (&bl)[kPfSp
 
 // plain BF16 rows product, acc += A B, with b holding the first kPfPlain
 // k-steps (plain_pre)
-template <int MB, int TPW>
+template <int MB, int TPW, bool ATOM_ROWS = false>
 __device__ inline void mma_rows_bf16(const __bf16* __restrict__ A, int lda, const bf16x8* __restrict__ Bp, int KB,
                                      int nb0, int nbs, int NB, floatx4 (&acc)[MB][TPW],
                                      bf16x8 (&b)[kPfPlain][TPW]) {
@@ -179,7 +180,9 @@ __device__ inline void mma_rows_bf16(const __bf16* __restrict__ A, int lda, cons
       const int nb = nb0 + i * nbs;
       if (nb < NB)
 #pragma unroll
-        for (int r = 0; r < MB; ++r) acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[i], a[r], acc[r][i], 0, 0, 0);
+        for (int r = 0; r < MB; ++r)
+          acc[r][i] = ATOM_ROWS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], bb[i], acc[r][i], 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[i], a[r], acc[r][i], 0, 0, 0);
     }
   };
   for (int kb = 0; kb < KB; kb += PF) {
@@ -243,7 +246,7 @@ __device__ inline void mma_rows_split(const __bf16* __restrict__ A, int alo, int
   }
 }
 
-template <int MB, int TPW>
+template <int MB, int TPW, bool ATOM_ROWS = false>
 __device__ inline void mma_rows_f32(const float* __restrict__ A, int lda, const float4* __restrict__ Bp, int KC,
                                     int nb0, int nbs, int NB, floatx4 (&acc)[MB][TPW]) {
   constexpr int PF = 2;
@@ -267,10 +270,10 @@ __device__ inline void mma_rows_f32(const float* __restrict__ A, int lda, const 
       if (nb < NB)
 #pragma unroll
         for (int r = 0; r < MB; ++r) {
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(bb[i].x, a[r].x, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(bb[i].y, a[r].y, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(bb[i].z, a[r].z, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(bb[i].w, a[r].w, acc[r][i], 0, 0, 0);
+          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].x : bb[i].x, ATOM_ROWS ? bb[i].x : a[r].x, acc[r][i], 0, 0, 0);
+          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].y : bb[i].y, ATOM_ROWS ? bb[i].y : a[r].y, acc[r][i], 0, 0, 0);
+          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].z : bb[i].z, ATOM_ROWS ? bb[i].z : a[r].z, acc[r][i], 0, 0, 0);
+          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].w : bb[i].w, ATOM_ROWS ? bb[i].w : a[r].w, acc[r][i], 0, 0, 0);
         }
     }
   };
@@ -556,14 +559,16 @@ __global__ void __launch_bounds__(kRoThreads)
   }
   lds_barrier();
 
-  // dE/dG = delta1 W1^T -> HBM [N][kFP] (FP32)
+  // dE/dG = delta1 W1^T -> HBM (FP32, dg_index).  The activations are the
+  // A operand here, so a lane holds one feature of four consecutive atoms:
+  // one 16-byte store in the feature-major runs
   {
     floatx4 acc[MB][TPW_G];
     zero_rows(acc);
     if constexpr (BF16) {
-      mma_rows_bf16<MB, TPW_G>((const __bf16*)sA, St::H, m.w1t_bf16, HP / 32, w, NW, NBG, acc, pg);
+      mma_rows_bf16<MB, TPW_G, true>((const __bf16*)sA, St::H, m.w1t_bf16, HP / 32, w, NW, NBG, acc, pg);
     } else {
-      mma_rows_f32<MB, TPW_G>((const float*)sA, St::H, (const float4*)m.w1t_f32, HP / 16, w, NW, NBG, acc);
+      mma_rows_f32<MB, TPW_G, true>((const float*)sA, St::H, (const float4*)m.w1t_f32, HP / 16, w, NW, NBG, acc);
     }
 #pragma unroll
     for (int i = 0; i < TPW_G; ++i) {
@@ -571,103 +576,19 @@ __global__ void __launch_bounds__(kRoThreads)
       if (nb >= NBG) continue;
 #pragma unroll
       for (int r = 0; r < MB; ++r) {
-        const int row = r * 16 + ar;
-        if (row < n_rows) *(floatx4*)(dG + (int64_t)(row0 + row) * kFP + nb * 16 + uq) = acc[r][i];
+        const int row = r * 16 + uq;
+        if (row >= n_rows) continue;
+        float* o = dG + dg_index(sys.n_atoms, row0 + row, nb * 16 + ar);
+        if (sys.n_atoms - (row0 + row) / kDgRun * kDgRun >= kDgRun) {
+          *(floatx4*)o = acc[r][i];  // a whole run: its rows are 16-byte aligned
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (row + j < n_rows) o[j] = acc[r][i][j];
+        }
       }
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// 3. invariant backward: dE/dG and the moments -> dE/dPsi (packed).  Blocks of
-// 4 atoms and 256 threads: the first forward pass runs each task's two
-// independent halves on two threads; about 29 KB of LDS, so five blocks per
-// CU, and each block's load and barrier waits overlap the others' arithmetic
-// (the time per block is latency: few tasks per atom between barriers).
-constexpr int kBkAtoms = 4;
-constexpr int kBkThreads = 256;
-
-struct BackLds {
-  static constexpr int LDGB = kFP + 1;
-  static constexpr size_t tables = 0;
-  static constexpr size_t psi = ro_al(sizeof(Tables));
-  static constexpr size_t inter = psi + ro_al(4 * (size_t)kBkAtoms * PS);
-  static constexpr size_t gb = inter + ro_al(4 * (size_t)kBkAtoms * IS);
-  static constexpr size_t pb = gb + ro_al(4 * (size_t)kBkAtoms * LDGB);
-  static constexpr size_t bytes = pb + ro_al(4 * (size_t)kBkAtoms * PS);
-};
-
-__global__ void __launch_bounds__(kBkThreads) readout_backward(DevSystem sys, const float* __restrict__ psi,
-                                                               const float* __restrict__ dG,
-                                                               float* __restrict__ psibar) {
-  using L = BackLds;
-  constexpr int TB = kBkAtoms, NT = kBkThreads;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  Tables& tb = *(Tables*)(lds + L::tables);
-  float* sPsi = (float*)(lds + L::psi);
-  float* sI = (float*)(lds + L::inter);
-  float* sGb = (float*)(lds + L::gb);
-  float* sPb = (float*)(lds + L::pb);
-  const int tid = threadIdx.x;
-  const int row0 = xcd_block(blockIdx.x, gridDim.x) * TB;
-  const int n_rows = min(TB, sys.n_atoms - row0);
-  // all loads of the tile (dE/dG rows, packed moments) issued up front
-  constexpr int NG = (TB * kFP / 4 + NT - 1) / NT;  // float4 per thread
-  constexpr int NP = kS * kPacked;
-  constexpr int NM = (TB * NP + NT - 1) / NT;
-  float4 gv[NG];
-  float mv[NM];
-  const float4* gsrc = (const float4*)(dG + (int64_t)row0 * kFP);
-#pragma unroll
-  for (int u = 0; u < NG; ++u) {
-    const int t = tid + u * NT;
-    gv[u] = (t < TB * kFP / 4 && t * 4 / kFP < n_rows) ? gsrc[t] : float4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-#pragma unroll
-  for (int u = 0; u < NM; ++u) {
-    const int t = tid + u * NT;
-    mv[u] = t < n_rows * NP ? psi[(int64_t)row0 * NP + t] : 0.0f;
-  }
-  load_tables(&tb);
-#pragma unroll
-  for (int u = 0; u < NG; ++u) {
-    const int t = (tid + u * NT) * 4;
-    if (t >= TB * kFP) continue;
-    const int a = t / kFP, f = t % kFP;
-    float* d = sGb + a * L::LDGB + f;
-    d[0] = gv[u].x;
-    d[1] = gv[u].y;
-    d[2] = gv[u].z;
-    d[3] = gv[u].w;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < NM; ++u) {
-    const int t = tid + u * NT;
-    if (t < TB * NP) {
-      const int a = t / NP, e = t % NP;
-      const int s = e / kPacked, c = e % kPacked;
-      const int n = tb.packed_mult[c];
-      for (int q = 0; q < n; ++q) sPsi[a * PS + s * kFull + tb.packed_full[c][q]] = mv[u];
-    }
-  }
-  __syncthreads();
-  constexpr int KSF = 2 * ((TB * 20 + 63) / 64 * 64) <= NT ? 2 : 1;
-  // the entry pass stays unsplit: its sums then run in the tile readout's
-  // order, so both readouts give bit-identical results
-  constexpr int KS = 1;
-  contract_forward_a<TB, NT, false, false, IS, KSF>(sPsi, sI, nullptr, 0, tb);
-  __syncthreads();
-  // phase A: each task's two output groups on two threads (no result changes)
-  constexpr int KSA = 2 * ((TB * 30 + 63) / 64 * 64) <= NT ? 2 : 1;
-  contract_backward_a<TB, NT, KSA>(sPsi, sGb, L::LDGB, sI, tb);
-  __syncthreads();
-  contract_backward_b<TB, NT, KS>(sPsi, sGb, L::LDGB, sI, sPb, tb);
-  __syncthreads();
-  auto to_psibar = [&](int a, int e, float v) {
-    if (a < n_rows) psibar[(int64_t)(row0 + a) * (kS * kPacked) + e] = v;
-  };
-  fold_packed<TB, NT>(sPb, tb, to_psibar);
 }
 
 // ---------------------------------------------------------------------------
@@ -684,12 +605,10 @@ static gmnn_status launch_stream_t(const DevModel& m, const DevSystem& sys, cons
   if (NL::bytes(m.M) > kLdsMax) return GMNN_ERR_UNSUPPORTED;
   gmnn_status st = ensure_lds_limit((const void*)readout_features<BF16>, FeatLds<BF16>::bytes);
   if (st == GMNN_OK) st = ensure_lds_limit((const void*)readout_network<HP, BF16>, NL::bytes(m.M));
-  if (st == GMNN_OK) st = ensure_lds_limit((const void*)readout_backward, BackLds::bytes);
   if (st != GMNN_OK) return st;
   const int N = sys.n_atoms;
   const int g16 = (N + kRoAtoms - 1) / kRoAtoms;
   const int gn = (N + NL::TM - 1) / NL::TM;
-  const int gb = (N + kBkAtoms - 1) / kBkAtoms;
   mark(0);
   if (phases & 1)
     hipLaunchKernelGGL(readout_features<BF16>, dim3(g16), dim3(kFtThreads), FeatLds<BF16>::bytes, s, sys, psi, G);
@@ -700,9 +619,10 @@ static gmnn_status launch_stream_t(const DevModel& m, const DevSystem& sys, cons
                        (const void*)G, atomic_e, dG);
   mark(3);
   mark(4);
-  if (phases & 4)
-    hipLaunchKernelGGL(readout_backward, dim3(gb), dim3(kBkThreads), BackLds::bytes, s, sys, psi, (const float*)dG,
-                       psibar);
+  if (phases & 4) {
+    st = launch_contract_back(N, 1, psi, dG, psibar, s);
+    if (st != GMNN_OK) return st;
+  }
   mark(5);
   return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
 }
@@ -716,7 +636,6 @@ size_t stream_lds_bytes(int hp, bool bf16, int n_heads) {
   if (n == 0) return ~size_t(0);
   size_t f = bf16 ? FeatLds<true>::bytes : FeatLds<false>::bytes;
   if (f > n) n = f;
-  if (BackLds::bytes > n) n = BackLds::bytes;
   return n;
 }
 

@@ -21,6 +21,7 @@
 // block, the same network products); the unfused readout serves large
 // systems between the high-occupancy pair kernels.
 #include "common.h"
+#include "contract_lanes.h"
 #include "contraction.h"
 #include "mfma.h"
 #include "model.h"
@@ -65,7 +66,8 @@ struct TileLds {
   static constexpr size_t bytes = ea + (FUSED ? al(4 * (size_t)TM * kMaxHeads) : 0);
 };
 
-// psibar_out: [nh][N][100] (unfused); gpair: [nh][gstride][3] (fused);
+// psibar_out (unfused): dE/dG of the head mean (dg_index), or with PERHEAD
+// dE/dPsi [nh][N][100]; gpair: [nh][gstride][3] (fused);
 // nh = n_heads with PERHEAD (one backward per head), else 1 (head mean).
 // tile_rec (fused, may be null): [tile][kMaxHeads + 9] FP64 sums over the
 // tile's atoms of the energies (heads 0 .. M-1) and of the virial entries,
@@ -228,6 +230,14 @@ __global__ void __launch_bounds__(kTileThreads)
       __syncthreads();
     }
     network_backward<TM, HP, BF16, kTileWaves, kDepth>(m, sD2, sH, sGb, dsw1, ring);
+    if (!FUSED && !PERHEAD) {
+      // head-mean readout: dE/dG goes out; contract_back takes it from there
+      for (int t = tid; t < kFP * TA; t += kTileThreads) {
+        const int a = t % TA, f = t / TA;
+        if (a < n_rows) psibar_out[dg_index(sys.n_atoms, row0 + a, f)] = sGb[a * LDGB + f];
+      }
+      return;
+    }
     // ---- invariants backward ---------------------------------------------------
     // phase A: each task's two output groups on two threads when the tile has
     // the threads (8-atom tiles; no result changes)
@@ -335,7 +345,8 @@ bool tile_fused_supported(int n_species, int hp, bool bf16, bool perhead) {
 
 // fused: moments + readout + pair backward in one launch (gpair, virial,
 // tile records out) on tiles of tile_atoms (8 or 16) atoms; otherwise the
-// readout alone (psi in, psibar out) on 16-atom tiles
+// readout alone on 16-atom tiles (psi in; psibar out: dE/dG of the head mean,
+// or dE/dPsi per head)
 gmnn_status launch_tile(bool fused, bool perhead, int tile_atoms, const DevModel& m, const DevSystem& sys, bool bf16,
                         const float* psi, float* atomic_e, float* psibar, float* gpair, float* virial,
                         int64_t gstride, double* tile_rec, hipStream_t stream) {
