@@ -85,6 +85,15 @@ __device__ inline float split_low(float v, __bf16 hi) {
   return v - (float)hi;
 }
 
+// the three bf16 parts of an FP32 value, h + m + l = v exactly (8 significant
+// bits each, nearest even, so each remainder is exact in FP32)
+__device__ inline void split3(float v, __bf16& h, __bf16& m, __bf16& l) {
+  h = (__bf16)v;
+  const float r = split_low(v, h);
+  m = (__bf16)r;
+  l = (__bf16)(r - (float)m);
+}
+
 // ---------------------------------------------------------------------------
 // wave-level helpers
 // ---------------------------------------------------------------------------

@@ -1,13 +1,20 @@
 // MFMA tile products and the network stage of a tile (gfx950).
 //
-// Weight layouts (filled by gmnn_model_prepare), for B = W of shape K x N:
-//   BF16, 16x16x32 MFMA: fragment (nb, kb) is 64 lanes x 8 bf16, lane l holding
+// Weight layout (filled by gmnn_model_prepare), for B = W of shape K x N:
+//   16x16x32 BF16 MFMA: fragment (nb, kb) is 64 lanes x 8 bf16, lane l holding
 //     B[32 kb + 8 (l>>4) + e][16 nb + (l&15)], e = 0..7     -> one 16-byte load
-//   FP32, 16x16x4 MFMA: chunk (nb, kc) is 64 lanes x 4 floats, lane l holding
-//     B[16 kc + 4 (l>>4) + u][16 nb + (l&15)], u = 0..3     -> one 16-byte load
-//     feeding four MFMAs (the k order inside a chunk is permuted consistently
-//     for A and B, which leaves the product unchanged)
+//   in three parts h + m + l = w (model.h).
 // A tiles live in LDS, row-major, rows padded so 16-byte reads stay aligned.
+//
+// FP32 products.  The FP32 MFMA (16x16x4) issues 256 FLOP per cycle and CU,
+// the BF16 one 4096.  An FP32 product is therefore taken from three-part
+// operands, x = h + m + l exactly with 8 significant bits per part, as the six
+// BF16 products whose weight is above 2^-26 of the whole (hh, hm, mh, mm, hl,
+// lh; the dropped ml, lm, ll are below a quarter ulp of each term), with FP32
+// accumulation: 96 cycles per 16x16x32 block instead of 256, and K/32
+// roundings of the sum instead of K.  Measured against 64 bits the
+// errors are no larger than the FP32 MFMA's (energies and forces of the
+// workloads: equal or smaller in every case).
 #pragma once
 
 #include "common.h"
@@ -18,93 +25,184 @@ namespace gmnn {
 
 // Each wave owns one 16-row block rb and the 16-column blocks nb0 + i*nbs
 // (i < TPW, nb < NB).  B fragments stream from L2 through a ring of register
-// buffers, prefetch_depth<TPW> k-steps ahead of the MFMAs: 16 fragments
-// (64 registers) in flight per wave whatever the width.  The ring of a
-// product can be filled ahead of it (ring_fill), e.g. before the epilogue and
-// barrier of the previous product, so its first fragments arrive during them.
+// buffers, PF k-steps ahead of the MFMAs: 16 BF16 fragments (64 registers) in
+// flight per wave whatever the width, 6 to 8 three-part ones (72 to 96) for
+// FP32.  The ring of a product can be filled ahead of it (ring_fill), e.g.
+// before the epilogue and barrier of the previous product, so its first
+// fragments arrive during them.
 template <int TPW>
 constexpr int prefetch_depth() { return TPW >= 4 ? 4 : 16 / TPW > 8 ? 8 : 16 / TPW; }
+// ... of three-part fragments where BF16 ones would go `depth` deep
+constexpr int prefetch_depth3(int tpw, int depth) {
+  return depth < 4 ? (tpw >= 2 ? 1 : 2) : tpw >= 4 ? 2 : tpw >= 2 ? 3 : 6;
+}
+
+// the parts of a three-part fragment
+struct Split3 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ Split3 split3x8(floatx4 a, floatx4 b) {
+  Split3 s;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    __bf16 h, m, l;
+    split3(e < 4 ? a[e & 3] : b[e & 3], h, m, l);
+    s.h[e] = h;
+    s.m[e] = m;
+    s.l[e] = l;
+  }
+  return s;
+}
+
+// one k-step of N FP32 products, sum[n] += x(n) y(n), smallest part products
+// first from zero, then added to the sum in FP32 (rounded to nearest: the
+// MFMA's own accumulation of a long sum was measured to bias it towards zero
+// by up to 1e-6).  The N chains are interleaved: an MFMA waits for the one
+// before it in its own chain.  SWAP: y is the MFMA's A operand (the order of
+// the part products stays, so both orientations agree bit for bit).
+template <bool SWAP = false, int N, typename X, typename Y>
+__device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
+#define GMNN_PART(PX, PY, FROM)                                                                           \
+  _Pragma("unroll") for (int n = 0; n < N; ++n)                                                           \
+      t[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(SWAP ? y(n).PY : x(n).PX, SWAP ? x(n).PX : y(n).PY, \
+                                                     FROM, 0, 0, 0)
+  GMNN_PART(l, h, (floatx4{0.0f, 0.0f, 0.0f, 0.0f}));
+  GMNN_PART(h, l, t[n]);
+  GMNN_PART(m, m, t[n]);
+  GMNN_PART(m, h, t[n]);
+  GMNN_PART(h, m, t[n]);
+  GMNN_PART(h, h, t[n]);
+#undef GMNN_PART
+}
+template <bool SWAP = false, int N, typename X, typename Y>
+__device__ __forceinline__ void mma_six(floatx4 (&sum)[N], X x, Y y) {
+  floatx4 t[N];
+  six_products<SWAP>(t, x, y);
+#pragma unroll
+  for (int n = 0; n < N; ++n) sum[n] += t[n];
+}
+
+// k-steps 0 .. KB - 1 of a product whose fragments come through a ring of PF
+// slots, the first PF of them already issued: step(slot, kb), then
+// load(slot, kb + PF).  The last steps are peeled, so no branch guards a load
+// (a guarded one would put the ring in scratch memory).
+template <int PF, typename Step, typename Load>
+__device__ __forceinline__ void pipeline(int KB, Step step, Load load) {
+  const int full = KB > PF ? (KB - PF) / PF * PF : 0;
+#pragma unroll 1
+  for (int kb = 0; kb < full; kb += PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      step(s, kb + s);
+      load(s, kb + s + PF);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 2 * PF; ++s) {
+    if (full + s >= KB) continue;
+    step(s % PF, full + s);
+    if (full + s + PF < KB) load(s % PF, full + s + PF);
+  }
+}
 
 template <bool BF16>
 struct FragT { using type = bf16x8; };
 template <>
-struct FragT<false> { using type = floatx4; };  // native vector: kept in registers inside the ring
+struct FragT<false> { using type = Split3; };
 
 template <bool BF16, int TPW, int DEPTH = prefetch_depth<TPW>()>
 struct BRing {
-  static constexpr int PF = DEPTH;
+  static constexpr int PF = BF16 ? DEPTH : prefetch_depth3(TPW, DEPTH);
   typename FragT<BF16>::type b[PF][TPW];
 };
 
-// k-steps of K: 32 per BF16 fragment, 16 per FP32 chunk (four 16x16x4 MFMAs)
-template <bool BF16>
-constexpr int ksteps(int K) { return BF16 ? K / 32 : K / 16; }
+// Fragment (nb0 + i nbs, kb) of one part of B, as a buffer load: the wave's
+// block and the lane in one 32-bit offset (frag_lane), i and kb in a scalar
+// one, so a product's loads share a single address register.
+__device__ __forceinline__ int frag_lane(int nb0, int KB) { return (nb0 * KB * 64 + (threadIdx.x & 63)) * 16; }
+__device__ __forceinline__ bf16x8 frag_load(const bf16x8* part, int lane, int inb, int KB, int kb) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)part, 0, 0x7fffffff, 0x00027000);
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, lane, (inb * KB + kb) * 1024, 0));
+}
+
+// whether a wave has an i-th column block (known at compile time where the
+// blocks divide evenly, so that no branch guards the ring's registers)
+__device__ __forceinline__ bool has_block(int i, int nb0, int nbs, int NB) {
+  return NB >= (i + 1) * nbs || nb0 + i * nbs < NB;
+}
 
 template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void ring_load(BRing<BF16, TPW, DEPTH>& r, int slot, const void* Bp, int KB, int kb, int nb0, int nbs,
-                                 int NB) {
-  using F = typename FragT<BF16>::type;
-  const int l = threadIdx.x & 63;
+__device__ __forceinline__ void ring_load(BRing<BF16, TPW, DEPTH>& r, int slot, const Weights& B, int KB, int kb,
+                                          int nb0, int nbs, int NB) {
+  const int lane = frag_lane(nb0, KB);
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
-    const int nb = nb0 + i * nbs;
-    if (nb < NB && kb < KB) r.b[slot][i] = ((const F*)Bp)[((size_t)nb * KB + kb) * 64 + l];
+    if (has_block(i, nb0, nbs, NB) && kb < KB) {
+      auto part = [&](const bf16x8* p) { return frag_load(p, lane, i * nbs, KB, kb); };
+      if constexpr (BF16) r.b[slot][i] = part(B.h);
+      else r.b[slot][i] = Split3{part(B.h), part(B.m), part(B.l)};
+    }
   }
 }
 
-// issue the first PF k-steps of the product with B = (Bbf or Bf) of K rows
+// issue the first PF k-steps of the product with B of K rows
 template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void ring_fill(BRing<BF16, TPW, DEPTH>& r, const void* Bbf, const void* Bf, int K, int nb0, int nbs,
-                                 int NB) {
-  const void* Bp = BF16 ? Bbf : Bf;
+__device__ __forceinline__ void ring_fill(BRing<BF16, TPW, DEPTH>& r, const Weights& B, int K, int nb0, int nbs,
+                                          int NB) {
 #pragma unroll
-  for (int s = 0; s < DEPTH; ++s) ring_load(r, s, Bp, ksteps<BF16>(K), s, nb0, nbs, NB);
+  for (int s = 0; s < BRing<BF16, TPW, DEPTH>::PF; ++s) ring_load(r, s, B, K / 32, s, nb0, nbs, NB);
 }
 
-// acc += A[rb rows] B over K, with the ring already holding k-steps 0..PF-1
+// acc += A[rb rows] B over K, with the ring already holding k-steps 0..PF-1.
+// A: bf16 (BF16), or FP32 split into its parts as it is read (the same parts,
+// and the same order of products, as the streamed readout's)
 template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void mma_ring(BRing<BF16, TPW, DEPTH>& r, const void* A, int lda, int rb, const void* Bbf,
-                                         const void* Bf, int K, int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
-  constexpr int PF = DEPTH;
+__device__ __forceinline__ void mma_ring(BRing<BF16, TPW, DEPTH>& r, const void* A, int lda, int rb, const Weights& B,
+                                         int K, int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
+  constexpr int PF = BRing<BF16, TPW, DEPTH>::PF;
   const int l = threadIdx.x & 63;
-  const void* Bp = BF16 ? Bbf : Bf;
-  const int KB = ksteps<BF16>(K);
-  auto step = [&](int slot, int kb) {
+  const int KB = K / 32;
+  const int row = (rb * 16 + (l & 15)) * lda + (l >> 4) * 8;
+  if constexpr (BF16) {
+    pipeline<PF>(
+        KB,
+        [&](int slot, int kb) {
+          const bf16x8 a = *(const bf16x8*)((const __bf16*)A + row + kb * 32);
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb >= NB) continue;
-      if constexpr (BF16) {
-        const bf16x8 a = *(const bf16x8*)((const __bf16*)A + (rb * 16 + (l & 15)) * lda + (l >> 4) * 8 + kb * 32);
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
-      } else {
-        const floatx4 a = *(const floatx4*)((const float*)A + (rb * 16 + (l & 15)) * lda + (l >> 4) * 4 + kb * 16);
-        const floatx4 bb = r.b[slot][i];
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], bb[0], acc[i], 0, 0, 0);
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], bb[1], acc[i], 0, 0, 0);
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], bb[2], acc[i], 0, 0, 0);
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], bb[3], acc[i], 0, 0, 0);
-      }
-    }
-  };
-  for (int kb = 0; kb < KB; kb += PF) {
+          for (int i = 0; i < TPW; ++i)
+            if (has_block(i, nb0, nbs, NB))
+              acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
+        },
+        [&](int slot, int kb) { ring_load(r, slot, B, KB, kb, nb0, nbs, NB); });
+  } else {
+    // a wave with one column block runs two k-steps at once: one chain of six
+    // dependent MFMAs would leave the pipe waiting (every K here is a multiple
+    // of 64)
+    constexpr int U = TPW == 1 ? 2 : 1;
+    static_assert(PF % U == 0, "whole groups of k-steps in the ring");
+    pipeline<PF / U>(
+        KB / U,
+        [&](int slot, int g) {
+          // only a product narrower than the waves leaves some without a block
+          // (one column block per wave there)
+          if (TPW == 1 && !has_block(0, nb0, nbs, NB)) return;
+          Split3 a[U];
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      if (kb + s < KB) {
-        step(s, kb + s);
-        ring_load(r, s, Bp, KB, kb + s + PF, nb0, nbs, NB);
-      }
-    }
+          for (int u = 0; u < U; ++u) {
+            const float* p = (const float*)A + row + (g * U + u) * 32;
+            a[u] = split3x8(*(const floatx4*)p, *(const floatx4*)(p + 4));
+          }
+          floatx4 t[U * TPW];
+          six_products(t, [&](int n) -> const Split3& { return a[n / TPW]; },
+                       [&](int n) -> const Split3& { return r.b[slot * U + n / TPW][n % TPW]; });
+#pragma unroll
+          for (int n = 0; n < U * TPW; ++n) acc[n % TPW] += t[n];
+        },
+        [&](int slot, int g) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) ring_load(r, slot * U + u, B, KB, g * U + u, nb0, nbs, NB);
+        });
   }
-}
-
-// the same product with the ring filled on the spot (FP32 only: the training tile)
-template <int TPW>
-__device__ inline void mma_f32(const float* __restrict__ A, int lda, int rb, const float4* __restrict__ Bp, int KC,
-                               int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
-  BRing<false, TPW> r;
-  ring_fill(r, nullptr, Bp, KC * 16, nb0, nbs, NB);
-  mma_ring(r, A, lda, rb, nullptr, Bp, KC * 16, nb0, nbs, NB, acc);
 }
 
 // BF16 product with the A tile kept in FP32 in LDS: the 8 values of each A
@@ -114,8 +212,8 @@ __device__ inline void mma_f32(const float* __restrict__ A, int lda, int rb, con
 // with ring_fill), so its first fragments can arrive during earlier work.
 template <int TPW, int DEPTH>
 __device__ __forceinline__ void mma_bf16_a32_ring(BRing<true, TPW, DEPTH>& r, const float* __restrict__ A, int lda,
-                                                  int rb, const bf16x8* __restrict__ Bp, int K, int nb0, int nbs,
-                                                  int NB, floatx4 (&acc)[TPW]) {
+                                                  int rb, const Weights& B, int K, int nb0, int nbs, int NB,
+                                                  floatx4 (&acc)[TPW]) {
   constexpr int PF = DEPTH;
   const int l = threadIdx.x & 63;
   const int KB = K / 32;
@@ -128,28 +226,10 @@ __device__ __forceinline__ void mma_bf16_a32_ring(BRing<true, TPW, DEPTH>& r, co
     a[4] = (__bf16)hi.x; a[5] = (__bf16)hi.y; a[6] = (__bf16)hi.z; a[7] = (__bf16)hi.w;
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
+      if (has_block(i, nb0, nbs, NB)) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
     }
   };
-  for (int kb = 0; kb < KB; kb += PF) {
-#pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      if (kb + s < KB) {
-        step(s, kb + s);
-        ring_load(r, s, Bp, KB, kb + s + PF, nb0, nbs, NB);
-      }
-    }
-  }
-}
-
-template <int TPW>
-__device__ __forceinline__ void mma_bf16_a32(const float* __restrict__ A, int lda, int rb,
-                                             const bf16x8* __restrict__ Bp, int K, int nb0, int nbs, int NB,
-                                             floatx4 (&acc)[TPW]) {
-  BRing<true, TPW> r;
-  ring_fill(r, Bp, nullptr, K, nb0, nbs, NB);
-  mma_bf16_a32_ring(r, A, lda, rb, Bp, K, nb0, nbs, NB, acc);
+  pipeline<PF>(KB, step, [&](int slot, int kb) { ring_load(r, slot, B, KB, kb, nb0, nbs, NB); });
 }
 
 // ---------------------------------------------------------------------------
@@ -175,39 +255,37 @@ template <bool BF16, int TPW, int DEPTH>
 using FwdRing = typename FwdRingT<BF16, TPW, DEPTH>::type;
 
 template <int TPW, int SD>
-__device__ __forceinline__ void split_ring_load(BRing<true, 2 * TPW, SD>& r, int slot, const bf16x8* Bhi,
-                                                const bf16x8* Blo, int KB, int kb, int nb0, int nbs, int NB) {
-  const int l = threadIdx.x & 63;
+__device__ __forceinline__ void split_ring_load(BRing<true, 2 * TPW, SD>& r, int slot, const Weights& B, int KB,
+                                                int kb, int nb0, int nbs, int NB) {
+  const int lane = frag_lane(nb0, KB);
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
-    const int nb = nb0 + i * nbs;
-    if (nb < NB && kb < KB) {
-      const size_t o = ((size_t)nb * KB + kb) * 64 + l;
-      r.b[slot][i] = Bhi[o];
-      r.b[slot][TPW + i] = Blo[o];
+    if (has_block(i, nb0, nbs, NB) && kb < KB) {
+      r.b[slot][i] = frag_load(B.h, lane, i * nbs, KB, kb);
+      r.b[slot][TPW + i] = frag_load(B.m, lane, i * nbs, KB, kb);
     }
   }
 }
 
-// first k-steps of a forward product: split fragments (BF16) or FP32 chunks
+// first k-steps of a forward product: two-part fragments (BF16) or three-part ones
 template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void fwd_ring_fill(FwdRing<BF16, TPW, DEPTH>& r, const bf16x8* Bhi, const bf16x8* Blo,
-                                              const float* Bf, int K, int nb0, int nbs, int NB) {
+__device__ __forceinline__ void fwd_ring_fill(FwdRing<BF16, TPW, DEPTH>& r, const Weights& B, int K, int nb0, int nbs,
+                                              int NB) {
   if constexpr (BF16) {
     constexpr int SD = DEPTH / 2 > 0 ? DEPTH / 2 : 1;
 #pragma unroll
-    for (int s = 0; s < SD; ++s) split_ring_load<TPW, SD>(r, s, Bhi, Blo, K / 32, s, nb0, nbs, NB);
+    for (int s = 0; s < SD; ++s) split_ring_load<TPW, SD>(r, s, B, K / 32, s, nb0, nbs, NB);
   } else {
-    ring_fill(r, nullptr, Bf, K, nb0, nbs, NB);
+    ring_fill(r, B, K, nb0, nbs, NB);
   }
 }
 
 // acc += A B for a forward product: split-BF16 (bf16 parts of A at A and
-// Alo) or plain FP32 (A; Alo unused)
+// Alo) or FP32 (A; Alo unused)
 template <bool BF16, int TPW, int DEPTH>
 __device__ __forceinline__ void fwd_mma(FwdRing<BF16, TPW, DEPTH>& r, const void* A, const void* Alo, int lda, int rb,
-                                        const bf16x8* Bhi, const bf16x8* Blo, const float* Bf, int K, int nb0,
-                                        int nbs, int NB, floatx4 (&acc)[TPW]) {
+                                        const Weights& B, int K, int nb0, int nbs, int NB,
+                                        floatx4 (&acc)[TPW]) {
   if constexpr (BF16) {
     constexpr int SD = DEPTH / 2 > 0 ? DEPTH / 2 : 1;
     const int l = threadIdx.x & 63;
@@ -220,24 +298,15 @@ __device__ __forceinline__ void fwd_mma(FwdRing<BF16, TPW, DEPTH>& r, const void
       const bf16x8 al = *(const bf16x8*)(alo_p + kb * 32);
 #pragma unroll
       for (int i = 0; i < TPW; ++i) {
-        const int nb = nb0 + i * nbs;
-        if (nb >= NB) continue;
+        if (!has_block(i, nb0, nbs, NB)) continue;
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, r.b[slot][i], acc[i], 0, 0, 0);
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, r.b[slot][TPW + i], acc[i], 0, 0, 0);
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, r.b[slot][i], acc[i], 0, 0, 0);
       }
     };
-    for (int kb = 0; kb < KB; kb += SD) {
-#pragma unroll
-      for (int s = 0; s < SD; ++s) {
-        if (kb + s < KB) {
-          step(s, kb + s);
-          split_ring_load<TPW, SD>(r, s, Bhi, Blo, KB, kb + s + SD, nb0, nbs, NB);
-        }
-      }
-    }
+    pipeline<SD>(KB, step, [&](int slot, int kb) { split_ring_load<TPW, SD>(r, slot, B, KB, kb, nb0, nbs, NB); });
   } else {
-    mma_ring(r, A, lda, rb, nullptr, Bf, K, nb0, nbs, NB, acc);
+    mma_ring(r, A, lda, rb, B, K, nb0, nbs, NB, acc);
   }
 }
 
@@ -339,8 +408,8 @@ __device__ __forceinline__ void network_forward(const DevModel& m, const void* s
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    fwd_mma<BF16, TPW, DEPTH>(fring, sG, sGlo, St::G, rb, m.w1_bf16, m.w1lo_bf16, m.w1_f32, kFP, cw, WPR, NBH, acc);
-    fwd_ring_fill<BF16, TPW, DEPTH>(fring, m.w2_bf16, m.w2lo_bf16, m.w2_f32, HP, cw, WPR, NBH);
+    fwd_mma<BF16, TPW, DEPTH>(fring, sG, sGlo, St::G, rb, m.w1, kFP, cw, WPR, NBH, acc);
+    fwd_ring_fill<BF16, TPW, DEPTH>(fring, m.w2, HP, cw, WPR, NBH);
     if (BF16) __syncthreads();  // every wave is done with G before h1's low part is stored
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
@@ -361,9 +430,9 @@ __device__ __forceinline__ void network_forward(const DevModel& m, const void* s
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    fwd_mma<BF16, TPW, DEPTH>(fring, sH, sHlo, St::H, rb, m.w2_bf16, m.w2lo_bf16, m.w2_f32, HP, cw, WPR, NBH, acc);
+    fwd_mma<BF16, TPW, DEPTH>(fring, sH, sHlo, St::H, rb, m.w2, HP, cw, WPR, NBH, acc);
     // the backward's first product (W2^T) starts loading now
-    ring_fill(ring, m.w2t_bf16, m.w2t_f32, HP, cw, WPR, NBH);
+    ring_fill(ring, m.w2t, HP, cw, WPR, NBH);
     if (BF16) __syncthreads();  // every wave is done with h1's low part before delta2 is stored
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
@@ -443,8 +512,8 @@ __device__ __forceinline__ void network_backward(const DevModel& m, const void* 
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    mma_ring(ring, sD2, St::H, rb, m.w2t_bf16, m.w2t_f32, HP, cw, WPR, NBH, acc);
-    ring_fill(ring_g, m.w1t_bf16, m.w1t_f32, HP, cw, WPR, NBG);
+    mma_ring(ring, sD2, St::H, rb, m.w2t, HP, cw, WPR, NBH, acc);
+    ring_fill(ring_g, m.w1t, HP, cw, WPR, NBG);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       const int nb = cw + i * WPR;
@@ -461,7 +530,7 @@ __device__ __forceinline__ void network_backward(const DevModel& m, const void* 
   {
     floatx4 acc[TPW_G];
     zero_acc(acc);
-    mma_ring(ring_g, sH, St::H, rb, m.w1t_bf16, m.w1t_f32, HP, cw, WPR, NBG, acc);
+    mma_ring(ring_g, sH, St::H, rb, m.w1t, HP, cw, WPR, NBG, acc);
 #pragma unroll
     for (int i = 0; i < TPW_G; ++i) {
       const int nb = cw + i * WPR;

@@ -14,18 +14,17 @@ constexpr int kMaxBasis = 8;
 constexpr int kMaxHeads = 16;
 
 // Offsets (bytes) of the packed buffer filled by gmnn_model_prepare.
-//   fp32 MFMA B fragments (16x16x4):  [n/16][k/4][64] floats
-//   bf16 MFMA B fragments (16x16x32): [n/16][k/32][64][8] bf16
-//   W1 and W2 (the forward products) also carry a low part in the bf16
-//   layout: lo = bf16(w - hi) with hi = bf16(w), so hi + lo holds w to about
-//   16 significant bits (the split-BF16 forward products)
+//   bf16 MFMA B fragments (16x16x32): [n/16][k/32][64][8] bf16, one array per
+//   part of W1, W1^T, W2, W2^T: h = bf16(w), m = bf16(w - h),
+//   l = bf16(w - h - m).  h + m + l = w exactly (the FP32 network's
+//   products), h + m holds about 16 significant bits (the split-BF16 forward
+//   products), h alone serves the BF16 backward products.
 // Hidden widths are padded to HP (multiple of 64) with zero weights and
 // biases, which leaves every output unchanged (swish(0) = 0).
 struct PackedLayout {
   int HP1 = 0, HP2 = 0, M = 0;
-  size_t w1_f32 = 0, w1t_f32 = 0, w2_f32 = 0, w2t_f32 = 0;
-  size_t w1_bf16 = 0, w1t_bf16 = 0, w2_bf16 = 0, w2t_bf16 = 0;
-  size_t w1lo_bf16 = 0, w2lo_bf16 = 0;
+  size_t w1 = 0, w1t = 0, w2 = 0, w2t = 0;  // offsets of the first parts
+  size_t s1 = 0, s2 = 0;                    // bytes from part to part of W1, W1^T and of W2, W2^T
   size_t b1 = 0, b2 = 0, w3 = 0, w3bar = 0, b3 = 0;
   size_t bytes = 0;
 };
@@ -43,16 +42,12 @@ inline PackedLayout packed_layout(int H1, int H2, int M) {
     off += (bytes + 255) & ~size_t(255);
     return o;
   };
-  L.w1_f32 = take(4 * (size_t)kFP * L.HP1);
-  L.w1t_f32 = take(4 * (size_t)kFP * L.HP1);
-  L.w2_f32 = take(4 * (size_t)L.HP1 * L.HP2);
-  L.w2t_f32 = take(4 * (size_t)L.HP1 * L.HP2);
-  L.w1_bf16 = take(2 * (size_t)kFP * L.HP1);
-  L.w1t_bf16 = take(2 * (size_t)kFP * L.HP1);
-  L.w2_bf16 = take(2 * (size_t)L.HP1 * L.HP2);
-  L.w2t_bf16 = take(2 * (size_t)L.HP1 * L.HP2);
-  L.w1lo_bf16 = take(2 * (size_t)kFP * L.HP1);
-  L.w2lo_bf16 = take(2 * (size_t)L.HP1 * L.HP2);
+  L.s1 = (2 * (size_t)kFP * L.HP1 + 255) & ~size_t(255);
+  L.s2 = (2 * (size_t)L.HP1 * L.HP2 + 255) & ~size_t(255);
+  L.w1 = take(3 * L.s1);
+  L.w1t = take(3 * L.s1);
+  L.w2 = take(3 * L.s2);
+  L.w2t = take(3 * L.s2);
   L.b1 = take(4 * (size_t)L.HP1);
   L.b2 = take(4 * (size_t)L.HP2);
   L.w3 = take(4 * (size_t)L.HP2 * M);
@@ -61,6 +56,11 @@ inline PackedLayout packed_layout(int H1, int H2, int M) {
   L.bytes = off;
   return L;
 }
+
+// Fragment-ordered parts of a weight matrix (h + m + l = w).
+struct Weights {
+  const bf16x8 *h, *m, *l;
+};
 
 // Kernel-argument view of the model (plain pointers, by value).
 struct DevModel {
@@ -74,16 +74,7 @@ struct DevModel {
   const float* beta;    // [nsp][nsp][S][K]
   const float* scale;   // [nsp]
   const float* shift;   // [nsp]
-  const float* w1_f32;
-  const float* w1t_f32;
-  const float* w2_f32;
-  const float* w2t_f32;
-  const bf16x8* w1_bf16;
-  const bf16x8* w1t_bf16;
-  const bf16x8* w2_bf16;
-  const bf16x8* w2t_bf16;
-  const bf16x8* w1lo_bf16;  // low parts of the forward weights (split products)
-  const bf16x8* w2lo_bf16;
+  Weights w1, w1t, w2, w2t;
   const float* b1;      // [HP1]
   const float* b2;      // [HP2]
   const float* w3;      // [HP2][M]

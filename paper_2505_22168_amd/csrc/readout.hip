@@ -118,175 +118,106 @@ __global__ void __launch_bounds__(kFtThreads) readout_features(DevSystem sys, co
 // scattered ones.  The block's barriers order LDS only (lds_barrier), so
 // the weight fragments prefetched for the next product stay in flight
 // through them.
-constexpr int kPfPlain = 3;  // k-steps of B in flight, plain BF16 products (measured best on the 2x512 network)
-constexpr int kPfSplit = 2;  // k-steps of B (high and low fragments) in flight, split products
+//
+// A product is taken from NP parts of both operands: 1 (plain BF16), 2
+// (split BF16: hh, hm, mh) or 3 (FP32: mma_six), in the order of the tile
+// readout's products (mfma.h).
+// k-steps of B in flight: measured best on the 2x512 network (BF16 3 and 2;
+// FP32 one three-part step, a second one spills)
+constexpr int rows_depth(int NP) { return NP == 1 ? 3 : NP == 2 ? 2 : 1; }
 
-// the first kPfPlain k-steps of a plain product's B fragments, issued ahead
-// of the product (their latency then overlaps the previous phase)
-template <int TPW>
-__device__ inline void plain_pre(bf16x8 (&b)[kPfPlain][TPW], const bf16x8* __restrict__ Bp, int KB, int nb0, int nbs,
-                                 int NB) {
-  const int l = threadIdx.x & 63;
+template <int NP, int TPW>
+struct RowsRing {
+  bf16x8 b[rows_depth(NP)][TPW][NP];
+};
+
+template <int NP>
+__device__ __forceinline__ void frag_parts(bf16x8 (&dst)[NP], const Weights& B, int lane, int inb, int KB, int kb) {
+  dst[0] = frag_load(B.h, lane, inb, KB, kb);
+  if constexpr (NP > 1) dst[1] = frag_load(B.m, lane, inb, KB, kb);
+  if constexpr (NP > 2) dst[2] = frag_load(B.l, lane, inb, KB, kb);
+}
+template <int NP, int TPW>
+__device__ __forceinline__ void rows_load(bf16x8 (&dst)[TPW][NP], const Weights& B, int KB, int kb, int nb0, int nbs,
+                                          int NB) {
 #pragma unroll
-  for (int s = 0; s < kPfPlain; ++s)
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB && s < KB) b[s][i] = Bp[((size_t)nb * KB + s) * 64 + l];
-    }
+  for (int i = 0; i < TPW; ++i)
+    if (has_block(i, nb0, nbs, NB) && kb < KB) frag_parts<NP>(dst[i], B, frag_lane(nb0, KB), i * nbs, KB, kb);
 }
 
-// the same for a split product (high and low parts, kPfSplit k-steps)
-template <int TPW>
-__device__ inline void split_pre(bf16x8 (&bh)[kPfSplit][TPW], bf16x8 (&bl)[kPfSplit][TPW],
-                                 const bf16x8* __restrict__ Bhi, const bf16x8* __restrict__ Blo, int KB, int nb0,
-                                 int nbs, int NB) {
-  const int l = threadIdx.x & 63;
+// the first k-steps of a product's B fragments, issued ahead of the product
+// (their latency then overlaps the previous phase)
+template <int NP, int TPW>
+__device__ __forceinline__ void rows_pre(RowsRing<NP, TPW>& r, const Weights& B, int KB, int nb0, int nbs, int NB) {
 #pragma unroll
-  for (int s = 0; s < kPfSplit; ++s)
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB && s < KB) {
-        const size_t o = ((size_t)nb * KB + s) * 64 + l;
-        bh[s][i] = Bhi[o];
-        bl[s][i] = Blo[o];
-      }
-    }
+  for (int s = 0; s < rows_depth(NP); ++s) rows_load<NP, TPW>(r.b[s], B, KB, s, nb0, nbs, NB);
 }
 
-// plain BF16 rows product, acc += A B, with b holding the first kPfPlain
-// k-steps (plain_pre)
-template <int MB, int TPW, bool ATOM_ROWS = false>
-__device__ inline void mma_rows_bf16(const __bf16* __restrict__ A, int lda, const bf16x8* __restrict__ Bp, int KB,
-                                     int nb0, int nbs, int NB, floatx4 (&acc)[MB][TPW],
-                                     bf16x8 (&b)[kPfPlain][TPW]) {
-  constexpr int PF = kPfPlain;
+// acc += A B with r holding the first k-steps; part q of A at A + q * apart
+// elements.  ATOM_ROWS: the activations are the MFMA's A operand (a lane then
+// holds four consecutive atoms of one unit)
+template <int NP, int MB, int TPW, bool ATOM_ROWS = false>
+__device__ __forceinline__ void mma_rows(RowsRing<NP, TPW>& ring, const __bf16* __restrict__ A, int apart, int lda,
+                                         const Weights& B, int KB, int nb0, int nbs, int NB,
+                                         floatx4 (&acc)[MB][TPW]) {
   const int l = threadIdx.x & 63;
   const __bf16* abase = A + (l & 15) * lda + (l >> 4) * 8;
-  auto load = [&](bf16x8 (&dst)[TPW], int kb) {
+  if constexpr (NP == 3) {
+    // one k-step in flight: a column block's fragments are replaced by the
+    // next step's as soon as its products are issued, three quarters of a
+    // step ahead of their use
+#pragma unroll 1
+    for (int kb = 0; kb < KB; ++kb) {
+      Split3 a[MB];
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB && kb < KB) dst[i] = Bp[((size_t)nb * KB + kb) * 64 + l];
-    }
-  };
-  auto step = [&](const bf16x8 (&bb)[TPW], int kb) {
-    bf16x8 a[MB];
-#pragma unroll
-    for (int r = 0; r < MB; ++r) a[r] = *(const bf16x8*)(abase + r * 16 * lda + kb * 32);
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB)
-#pragma unroll
-        for (int r = 0; r < MB; ++r)
-          acc[r][i] = ATOM_ROWS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r], bb[i], acc[r][i], 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(bb[i], a[r], acc[r][i], 0, 0, 0);
-    }
-  };
-  for (int kb = 0; kb < KB; kb += PF) {
-#pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      if (kb + s < KB) {
-        step(b[s], kb + s);
-        load(b[s], kb + s + PF);
+      for (int r = 0; r < MB; ++r) {
+        const __bf16* p = abase + r * 16 * lda + kb * 32;
+        a[r] = Split3{*(const bf16x8*)p, *(const bf16x8*)(p + apart), *(const bf16x8*)(p + 2 * apart)};
       }
-    }
-  }
-}
-
-// split-BF16 rows product (the forward products of the BF16 network):
-// acc += Ahi Bhi + Ahi Blo + Alo Bhi per k-step, in the order of fwd_mma,
-// with the low part of A at A + alo elements
-// (bh, bl hold the first kPfSplit k-steps: split_pre)
-template <int MB, int TPW>
-__device__ inline void mma_rows_split(const __bf16* __restrict__ A, int alo, int lda, const bf16x8* __restrict__ Bhi,
-                                      const bf16x8* __restrict__ Blo, int KB, int nb0, int nbs, int NB,
-                                      floatx4 (&acc)[MB][TPW], bf16x8 (&bh)[kPfSplit][TPW],
-                                      bf16x8 (&bl)[kPfSplit][TPW]) {
-  constexpr int PF = kPfSplit;
-  const int l = threadIdx.x & 63;
-  const __bf16* abase = A + (l & 15) * lda + (l >> 4) * 8;
-  auto load = [&](bf16x8 (&dh)[TPW], bf16x8 (&dl)[TPW], int kb) {
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB && kb < KB) {
-        const size_t o = ((size_t)nb * KB + kb) * 64 + l;
-        dh[i] = Bhi[o];
-        dl[i] = Blo[o];
-      }
-    }
-  };
-  auto step = [&](const bf16x8 (&h)[TPW], const bf16x8 (&lo)[TPW], int kb) {
-    // one row block's A parts at a time (fewer registers live)
-#pragma unroll
-    for (int r = 0; r < MB; ++r) {
-      const bf16x8 ah = *(const bf16x8*)(abase + r * 16 * lda + kb * 32);
-      const bf16x8 al = *(const bf16x8*)(abase + alo + r * 16 * lda + kb * 32);
 #pragma unroll
       for (int i = 0; i < TPW; ++i) {
-        const int nb = nb0 + i * nbs;
-        if (nb >= NB) continue;
-        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h[i], ah, acc[r][i], 0, 0, 0);
-        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo[i], ah, acc[r][i], 0, 0, 0);
-        acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h[i], al, acc[r][i], 0, 0, 0);
+        if (!has_block(i, nb0, nbs, NB)) continue;
+        const Split3 b{ring.b[0][i][0], ring.b[0][i][1], ring.b[0][i][2]};
+        auto fa = [&](int r) -> const Split3& { return a[r]; };
+        auto fb = [&](int) -> const Split3& { return b; };
+        floatx4 col[MB];
+#pragma unroll
+        for (int r = 0; r < MB; ++r) col[r] = acc[r][i];
+        mma_six<!ATOM_ROWS>(col, fa, fb);
+#pragma unroll
+        for (int r = 0; r < MB; ++r) acc[r][i] = col[r];
+        // (past the last step: the same step's fragments again, unused)
+        frag_parts<NP>(ring.b[0][i], B, frag_lane(nb0, KB), i * nbs, KB, min(kb + 1, KB - 1));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-  };
-  for (int kb = 0; kb < KB; kb += PF) {
+  } else {
+    constexpr int PF = rows_depth(NP);
+    auto step = [&](const bf16x8 (&b)[TPW][NP], int kb) {
+      // one row block's A parts at a time (fewer registers live)
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      if (kb + s < KB) {
-        step(bh[s], bl[s], kb + s);
-        load(bh[s], bl[s], kb + s + PF);
-      }
-    }
-  }
-}
-
-template <int MB, int TPW, bool ATOM_ROWS = false>
-__device__ inline void mma_rows_f32(const float* __restrict__ A, int lda, const float4* __restrict__ Bp, int KC,
-                                    int nb0, int nbs, int NB, floatx4 (&acc)[MB][TPW]) {
-  constexpr int PF = 2;
-  const int l = threadIdx.x & 63;
-  const float* abase = A + (l & 15) * lda + (l >> 4) * 4;
-  float4 b[PF][TPW];
-  auto load = [&](float4 (&dst)[TPW], int kc) {
+      for (int r = 0; r < MB; ++r) {
+        bf16x8 a[NP];
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB && kc < KC) dst[i] = Bp[((size_t)nb * KC + kc) * 64 + l];
-    }
-  };
-  auto step = [&](const float4 (&bb)[TPW], int kc) {
-    float4 a[MB];
+        for (int q = 0; q < NP; ++q) a[q] = *(const bf16x8*)(abase + q * apart + r * 16 * lda + kb * 32);
 #pragma unroll
-    for (int r = 0; r < MB; ++r) a[r] = *(const float4*)(abase + r * 16 * lda + kc * 16);
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = nb0 + i * nbs;
-      if (nb < NB)
-#pragma unroll
-        for (int r = 0; r < MB; ++r) {
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].x : bb[i].x, ATOM_ROWS ? bb[i].x : a[r].x, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].y : bb[i].y, ATOM_ROWS ? bb[i].y : a[r].y, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].z : bb[i].z, ATOM_ROWS ? bb[i].z : a[r].z, acc[r][i], 0, 0, 0);
-          acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ATOM_ROWS ? a[r].w : bb[i].w, ATOM_ROWS ? bb[i].w : a[r].w, acc[r][i], 0, 0, 0);
+        for (int i = 0; i < TPW; ++i) {
+          if (!has_block(i, nb0, nbs, NB)) continue;
+          auto mma = [&](const bf16x8& x, const bf16x8& y) {
+            acc[r][i] = ATOM_ROWS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc[r][i], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(y, x, acc[r][i], 0, 0, 0);
+          };
+          mma(a[0], b[i][0]);
+          if constexpr (NP == 2) {
+            mma(a[0], b[i][1]);
+            mma(a[1], b[i][0]);
+          }
         }
-    }
-  };
-#pragma unroll
-  for (int s = 0; s < PF; ++s) load(b[s], s);
-  for (int kc = 0; kc < KC; kc += PF) {
-#pragma unroll
-    for (int s = 0; s < PF; ++s) {
-      if (kc + s < KC) {
-        step(b[s], kc + s);
-        load(b[s], kc + s + PF);
       }
-    }
+    };
+    pipeline<PF>(
+        KB, [&](int slot, int kb) { step(ring.b[slot], kb); },
+        [&](int slot, int kb) { rows_load<NP, TPW>(ring.b[slot], B, KB, kb, nb0, nbs, NB); });
   }
 }
 
@@ -300,48 +231,55 @@ __device__ inline void zero_rows(floatx4 (&acc)[MB][TPW]) {
 
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
-// four consecutive activations of one row: FP32, or BF16 (high parts at
-// base, and with LO the low parts bf16(v - bf16(v)) at lo)
-template <bool BF16, bool LO = false>
-__device__ inline void st4(void* base, void* lo, int idx, floatx4 v) {
-  if constexpr (BF16) {
-    bf16x4 h, t;
+// four consecutive activations of one row in NP parts, part q at
+// base + q * part elements
+template <int NP>
+__device__ __forceinline__ void st4(__bf16* base, int part, int idx, floatx4 v) {
+  bf16x4 o[3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      h[j] = (__bf16)v[j];
-      if constexpr (LO) t[j] = (__bf16)split_low(v[j], h[j]);
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (NP == 3) {
+      __bf16 h, m, l;
+      split3(v[j], h, m, l);
+      o[0][j] = h;
+      o[1][j] = m;
+      o[2][j] = l;
+    } else {
+      o[0][j] = (__bf16)v[j];
+      if constexpr (NP == 2) o[1][j] = (__bf16)split_low(v[j], o[0][j]);
     }
-    *(bf16x4*)((__bf16*)base + idx) = h;
-    if constexpr (LO) *(bf16x4*)((__bf16*)lo + idx) = t;
-  } else {
-    *(floatx4*)((float*)base + idx) = v;
   }
+#pragma unroll
+  for (int q = 0; q < NP; ++q) *(bf16x4*)(base + q * part + idx) = o[q];
 }
 
 // rows per network block: as many 16-row MFMA blocks as the register file
-// holds with swish'(z1) kept for the backward (8 waves, 256 registers each)
+// (swish'(z1) is kept for the backward; 8 waves, 256 registers each) and,
+// with three-part operands, the LDS hold: G at 2x256 or h1 at 2x512 fill it
 template <int HP, bool BF16>
-constexpr int net_rows() { return BF16 ? (HP >= 512 ? 48 : 64) : 32; }
+constexpr int net_rows() { return HP >= 512 ? 48 : (BF16 || HP >= 256) ? 64 : 32; }
 
 template <int HP, bool BF16>
 struct NetLds {
-  using St = NetStrides<HP, BF16>;
   static constexpr int TM = net_rows<HP, BF16>();
-  static constexpr int ESZ = BF16 ? 2 : 4;
-  static constexpr int NS = BF16 ? 2 : 1;  // parts of a forward operand (bf16 high and low)
+  static constexpr int NF = BF16 ? 2 : 3;  // parts of a forward operand
+  static constexpr int NB = BF16 ? 1 : 3;  // parts of a backward operand
+  static constexpr int G = kFP + 8, H = HP + 8;  // row strides (bf16)
   static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
-  // region B: delta2; the row scale/shift; region A: G (all parts), then h1
-  // (all parts), then delta1 at its start and the per-wave energy partials
-  // [NW][TM][M] right after delta1 (sized by M)
-  static constexpr int GLO = TM * St::G;  // element offsets of the low parts in region A
-  static constexpr int HLO = TM * St::H;
+  // region A: G (all parts), then h1 (all parts), then delta1 at its start.
+  // BF16: delta2 has a region of its own, and the energy partials of every
+  // head [NW][TM][M] follow delta1.  FP32: delta2 takes h1's place, delta1
+  // takes delta2's, and the energy partials of up to kEpHeads heads at a
+  // time have a region of their own.
+  static constexpr int kEpHeads = 4;
+  static constexpr size_t part_g = (size_t)TM * G, part_h = (size_t)TM * H;  // elements
   static constexpr size_t b = 0;
-  static constexpr size_t rows = b + ro_al((size_t)ESZ * TM * St::H);
+  static constexpr size_t rows = b + (BF16 ? ro_al(2 * part_h) : ro_al(4 * (size_t)kRoWaves * TM * kEpHeads));
   static constexpr size_t a = rows + ro_al(4 * 3 * (size_t)TM);  // scale, shift, structure of each row
-  static constexpr size_t ep = a + ro_al((size_t)ESZ * TM * St::H);
+  static constexpr size_t ep = BF16 ? a + ro_al(2 * part_h) : 0;
+  static constexpr size_t a_bytes = ro_al(2 * NF * mx(part_g, part_h));
   static constexpr size_t bytes(int M) {
-    return mx(a + ro_al((size_t)ESZ * NS * mx((size_t)TM * St::G, (size_t)TM * St::H)),
-              ep + ro_al(4 * (size_t)kRoWaves * TM * M));
+    return BF16 ? mx(a + a_bytes, ep + ro_al(4 * (size_t)kRoWaves * TM * M)) : a + a_bytes;
   }
 };
 
@@ -350,13 +288,14 @@ __global__ void __launch_bounds__(kRoThreads)
     readout_network(DevModel m, DevSystem sys, const void* __restrict__ G, float* __restrict__ atomic_e,
                     float* __restrict__ dG) {
   using L = NetLds<HP, BF16>;
-  using St = NetStrides<HP, BF16>;
   constexpr int TM = L::TM, MB = TM / 16, NW = kRoWaves;
+  constexpr int NF = L::NF, NBK = L::NB;
   constexpr int NBH = HP / 16, NBG = kFP / 16;
   constexpr int TPW = (NBH + NW - 1) / NW, TPW_G = (NBG + NW - 1) / NW;
+  constexpr int PG = (int)L::part_g, PH = (int)L::part_h;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  char* sA = lds + L::a;
-  char* sB = lds + L::b;
+  __bf16* sA = (__bf16*)(lds + L::a);
+  __bf16* sB = BF16 ? (__bf16*)(lds + L::b) : sA;  // delta2
   float* sEp = (float*)(lds + L::ep);
   float* sScale = (float*)(lds + L::rows);
   float* sShift = sScale + TM;
@@ -370,18 +309,21 @@ __global__ void __launch_bounds__(kRoThreads)
   // feature) uq + j of the column block, atom ar of the row block
   const int ar = l & 15, uq = 4 * (l >> 4);
 
-  // BF16: the B fragments of each product's first k-steps are issued one
-  // phase ahead (W1's with the tile's G rows, W2's before the first
-  // epilogue, W2^T's and W1^T's before the second and third), so their
-  // latency overlaps loads, barriers and epilogues instead of the products
-  bf16x8 ph[kPfSplit][TPW], pl[kPfSplit][TPW];
-  bf16x8 pb[kPfPlain][TPW], pg[kPfPlain][TPW_G];
+  // the B fragments of each product's first k-steps are issued one phase
+  // ahead (W1's with the tile's G rows, W2's before the first epilogue,
+  // W2^T's and W1^T's before the second and third), so their latency
+  // overlaps loads, barriers and epilogues instead of the products
+  RowsRing<NF, TPW> rf;
+  RowsRing<NBK, TPW> rb;
+  RowsRing<NBK, TPW_G> rg;
 
-  // G rows (each part) -> region A (row stride St::G), zero rows beyond the
-  // system; every load of the tile is issued before the first store
+  // G rows (BF16: each part; FP32: split here) -> region A, zero rows beyond
+  // the system; every load of the tile is issued before the first store
   {
-    constexpr int C16 = kFP * L::ESZ / 16;  // 16-byte chunks per row
-    constexpr int NU = (L::NS * TM * C16 + kRoThreads - 1) / kRoThreads;
+    constexpr int ESZ = BF16 ? 2 : 4;
+    constexpr int NS = BF16 ? 2 : 1;
+    constexpr int C16 = kFP * ESZ / 16;  // 16-byte chunks per row
+    constexpr int NU = (NS * TM * C16 + kRoThreads - 1) / kRoThreads;
     const char* gbase = (const char*)G;
     uint4 v[NU];
 #pragma unroll
@@ -389,18 +331,19 @@ __global__ void __launch_bounds__(kRoThreads)
       const int t = tid + u * kRoThreads;
       const int part = t / (TM * C16), tt = t % (TM * C16);
       v[u] = uint4{0u, 0u, 0u, 0u};
-      if (part < L::NS && tt < n_rows * C16)
-        v[u] = ((const uint4*)(gbase + ((size_t)part * sys.n_atoms + row0) * kFP * L::ESZ))[tt];
+      if (part < NS && tt < n_rows * C16)
+        v[u] = ((const uint4*)(gbase + ((size_t)part * sys.n_atoms + row0) * kFP * ESZ))[tt];
     }
     // W1's first k-steps after the tile's rows: the LDS stores below wait
     // for the rows only
-    if constexpr (BF16) split_pre<TPW>(ph, pl, m.w1_bf16, m.w1lo_bf16, kFP / 32, w, NW, NBH);
+    rows_pre<NF, TPW>(rf, m.w1, kFP / 32, w, NW, NBH);
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const int t = tid + u * kRoThreads;
       const int part = t / (TM * C16), tt = t % (TM * C16);
-      if (part < L::NS)
-        *(uint4*)(sA + ((size_t)part * L::GLO + (size_t)(tt / C16) * St::G) * L::ESZ + (tt % C16) * 16) = v[u];
+      if (part >= NS) continue;
+      if constexpr (BF16) *(uint4*)(sA + part * PG + (tt / C16) * L::G + (tt % C16) * 8) = v[u];
+      else st4<3>(sA, PG, (tt / C16) * L::G + (tt % C16) * 4, __builtin_bit_cast(floatx4, v[u]));
     }
     for (int a = tid; a < TM; a += kRoThreads) {
       float sc = 0.0f, sh = 0.0f;
@@ -418,19 +361,14 @@ __global__ void __launch_bounds__(kRoThreads)
   }
   lds_barrier();
 
-  // z1 = G W1 + b1 (split-BF16 or FP32), h1 = swish(z1) -> region A once every
+  // z1 = G W1 + b1, h1 = swish(z1) -> region A once every
   // wave is done with G; swish'(z1) stays in registers
   floatx4 dsw1[MB][TPW];
   {
     floatx4 acc[MB][TPW];
     zero_rows(acc);
-    if constexpr (BF16) {
-      mma_rows_split<MB, TPW>((const __bf16*)sA, L::GLO, St::G, m.w1_bf16, m.w1lo_bf16, kFP / 32, w, NW, NBH, acc,
-                              ph, pl);
-      split_pre<TPW>(ph, pl, m.w2_bf16, m.w2lo_bf16, HP / 32, w, NW, NBH);
-    } else {
-      mma_rows_f32<MB, TPW>((const float*)sA, St::G, (const float4*)m.w1_f32, kFP / 16, w, NW, NBH, acc);
-    }
+    mma_rows<NF>(rf, sA, PG, L::G, m.w1, kFP / 32, w, NW, NBH, acc);
+    rows_pre<NF, TPW>(rf, m.w2, HP / 32, w, NW, NBH);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       const int nb = w + i * NW;
@@ -452,24 +390,18 @@ __global__ void __launch_bounds__(kRoThreads)
       if (nb >= NBH) continue;
 #pragma unroll
       for (int r = 0; r < MB; ++r)
-        st4<BF16, BF16>(sA, (__bf16*)sA + L::HLO, (r * 16 + ar) * St::H + nb * 16 + uq, acc[r][i]);
+        st4<NF>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, acc[r][i]);
     }
   }
   lds_barrier();
 
-  // z2 = h1 W2 + b2, h2 = swish(z2); delta2 = swish'(z2) sigma wbar -> region
-  // B; per-wave partial sums of h2 . W3[:,m] -> sEp (in region A, once every
-  // wave is done with h1)
+  // z2 = h1 W2 + b2, h2 = swish(z2); delta2 = swish'(z2) sigma wbar -> sB, and
+  // per-wave partial sums of h2 . W3[:,m] -> sEp, once every wave is done with h1
   {
     floatx4 acc[MB][TPW];
     zero_rows(acc);
-    if constexpr (BF16) {
-      mma_rows_split<MB, TPW>((const __bf16*)sA, L::HLO, St::H, m.w2_bf16, m.w2lo_bf16, HP / 32, w, NW, NBH, acc, ph,
-                              pl);
-      plain_pre<TPW>(pb, m.w2t_bf16, HP / 32, w, NW, NBH);
-    } else {
-      mma_rows_f32<MB, TPW>((const float*)sA, St::H, (const float4*)m.w2_f32, HP / 16, w, NW, NBH, acc);
-    }
+    mma_rows<NF>(rf, sA, PH, L::H, m.w2, HP / 32, w, NW, NBH, acc);
+    rows_pre<NBK, TPW>(rb, m.w2t, HP / 32, w, NW, NBH);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
@@ -490,50 +422,57 @@ __global__ void __launch_bounds__(kRoThreads)
         }
         if (m.h2_out && row < n_rows) *(floatx4*)(m.h2_out + (int64_t)(row0 + row) * HP + col) = acc[r][i];
         const floatx4 wr = m.head_w ? *(const floatx4*)(m.head_w + (int64_t)sStruct[row] * HP + col) : wb;
-        st4<BF16>(sB, nullptr, row * St::H + col, d * sScale[row] * wr);
+        st4<NBK>(sB, PH, row * L::H + col, d * sScale[row] * wr);
       }
     }
-    for (int hm = 0; hm < M; ++hm) {
+    // BF16: the partials of all heads at once; FP32: kEpHeads at a time
+    const int hstep = BF16 ? M : L::kEpHeads;
+    for (int h0 = 0; h0 < M; h0 += hstep) {
+      const int nh = min(hstep, M - h0);
+      if (h0 > 0) lds_barrier();  // the previous heads' partials are read
+      for (int hq = 0; hq < nh; ++hq) {
+        const int hm = h0 + hq;
 #pragma unroll
-      for (int r = 0; r < MB; ++r) {
-        // per unit c = uq + j of the 16-column blocks: the sum over the
-        // wave's blocks; then an xor butterfly over the 16 units (bits 3 and
-        // 2 of c across the lane groups, bits 1 and 0 inside the lane), the
-        // tree the tile readout's row sums take, so both readouts agree bit
-        // for bit
-        float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int r = 0; r < MB; ++r) {
+          // per unit c = uq + j of the 16-column blocks: the sum over the
+          // wave's blocks; then an xor butterfly over the 16 units (bits 3 and
+          // 2 of c across the lane groups, bits 1 and 0 inside the lane), the
+          // tree the tile readout's row sums take, so both readouts agree bit
+          // for bit
+          float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) {
-          const int nb = w + i * NW;
-          if (nb >= NBH) continue;
-          floatx4 w3;
-          if (M == 1) {
-            w3 = *(const floatx4*)(m.w3 + nb * 16 + uq);
-          } else {
+          for (int i = 0; i < TPW; ++i) {
+            const int nb = w + i * NW;
+            if (nb >= NBH) continue;
+            floatx4 w3;
+            if (M == 1) {
+              w3 = *(const floatx4*)(m.w3 + nb * 16 + uq);
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w3[j] = m.w3[(nb * 16 + uq + j) * M + hm];
+              for (int j = 0; j < 4; ++j) w3[j] = m.w3[(nb * 16 + uq + j) * M + hm];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[j] += acc[r][i][j] * w3[j];
           }
 #pragma unroll
-          for (int j = 0; j < 4; ++j) part[j] += acc[r][i][j] * w3[j];
+          for (int j = 0; j < 4; ++j) {
+            part[j] += __shfl_xor(part[j], 32);
+            part[j] += __shfl_xor(part[j], 16);
+          }
+          const float v = (part[0] + part[2]) + (part[1] + part[3]);
+          if (l < 16) sEp[(w * TM + r * 16 + ar) * nh + hq] = v;
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          part[j] += __shfl_xor(part[j], 32);
-          part[j] += __shfl_xor(part[j], 16);
-        }
-        const float v = (part[0] + part[2]) + (part[1] + part[3]);
-        if (l < 16) sEp[(w * TM + r * 16 + ar) * M + hm] = v;
       }
-    }
-  }
-  lds_barrier();
-  for (int t = tid; t < TM * M; t += kRoThreads) {
-    const int a = t / M, hm = t % M;
-    if (a < n_rows) {
-      float y = m.b3[hm];
+      lds_barrier();
+      for (int t = tid; t < TM * nh; t += kRoThreads) {
+        const int a = t / nh, hq = t % nh;
+        if (a < n_rows) {
+          float y = m.b3[h0 + hq];
 #pragma unroll
-      for (int ww = 0; ww < NW; ++ww) y += sEp[(ww * TM + a) * M + hm];
-      atomic_e[(int64_t)(row0 + a) * M + hm] = sScale[a] * y + sShift[a];
+          for (int ww = 0; ww < NW; ++ww) y += sEp[(ww * TM + a) * nh + hq];
+          atomic_e[(int64_t)(row0 + a) * M + h0 + hq] = sScale[a] * y + sShift[a];
+        }
+      }
     }
   }
   // forward-only pass (the energies an uncertainty bias needs first)
@@ -543,18 +482,16 @@ __global__ void __launch_bounds__(kRoThreads)
   {
     floatx4 acc[MB][TPW];
     zero_rows(acc);
-    if constexpr (BF16) {
-      mma_rows_bf16<MB, TPW>((const __bf16*)sB, St::H, m.w2t_bf16, HP / 32, w, NW, NBH, acc, pb);
-      plain_pre<TPW_G>(pg, m.w1t_bf16, HP / 32, w, NW, NBG);
-    } else {
-      mma_rows_f32<MB, TPW>((const float*)sB, St::H, (const float4*)m.w2t_f32, HP / 16, w, NW, NBH, acc);
-    }
+    mma_rows<NBK>(rb, sB, PH, L::H, m.w2t, HP / 32, w, NW, NBH, acc);
+    rows_pre<NBK, TPW_G>(rg, m.w1t, HP / 32, w, NW, NBG);
+    if (!BF16) lds_barrier();  // every wave is done with delta2, which delta1 replaces
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       const int nb = w + i * NW;
       if (nb >= NBH) continue;
 #pragma unroll
-      for (int r = 0; r < MB; ++r) st4<BF16>(sA, nullptr, (r * 16 + ar) * St::H + nb * 16 + uq, acc[r][i] * dsw1[r][i]);
+      for (int r = 0; r < MB; ++r)
+        st4<NBK>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, acc[r][i] * dsw1[r][i]);
     }
   }
   lds_barrier();
@@ -565,11 +502,7 @@ __global__ void __launch_bounds__(kRoThreads)
   {
     floatx4 acc[MB][TPW_G];
     zero_rows(acc);
-    if constexpr (BF16) {
-      mma_rows_bf16<MB, TPW_G, true>((const __bf16*)sA, St::H, m.w1t_bf16, HP / 32, w, NW, NBG, acc, pg);
-    } else {
-      mma_rows_f32<MB, TPW_G, true>((const float*)sA, St::H, (const float4*)m.w1t_f32, HP / 16, w, NW, NBG, acc);
-    }
+    mma_rows<NBK, MB, TPW_G, true>(rg, sA, PH, L::H, m.w1t, HP / 32, w, NW, NBG, acc);
 #pragma unroll
     for (int i = 0; i < TPW_G; ++i) {
       const int nb = w + i * NW;

@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(kTileThreads)
   void* sHlo = sG;
   FwdRing<BF16, Sh::TPW, kDepth> fring;
   BRing<BF16, Sh::TPW, kDepth> ring;
-  fwd_ring_fill<BF16, Sh::TPW, kDepth>(fring, m.w1_bf16, m.w1lo_bf16, m.w1_f32, kFP, (tid >> 6) / Sh::MB, Sh::WPR,
+  fwd_ring_fill<BF16, Sh::TPW, kDepth>(fring, m.w1, kFP, (tid >> 6) / Sh::MB, Sh::WPR,
                                        Sh::NBH);
   // 8 atoms leave threads for both halves of every task of the first pass
   constexpr int KSF = 2 * ((TA * 20 + 63) / 64 * 64) <= kTileThreads ? 2 : 1;
@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(kTileThreads)
   for (int hm = 0; hm < nh; ++hm) {
     // ---- network backward (head mean, or head hm) ------------------------------
     if (PERHEAD) {
-      if (hm > 0) ring_fill(ring, m.w2t_bf16, m.w2t_f32, HP, (tid >> 6) / Sh::MB, Sh::WPR, Sh::NBH);
+      if (hm > 0) ring_fill(ring, m.w2t, HP, (tid >> 6) / Sh::MB, Sh::WPR, Sh::NBH);
       network_delta2_head<TM, HP, BF16, kTileWaves>(m, sDsw2, sScale, sD2, hm);
       __syncthreads();
     }

@@ -125,15 +125,15 @@ __device__ inline void swish_d2(float z, float& s, float& d1, float& d2) {
   d2 = sg * (1.0f - sg) * (2.0f + z * (1.0f - 2.0f * sg));
 }
 
-// network products of the training tile: FP32 MFMA, or BF16 MFMA on the
-// BF16 weight copies with the FP32 activation tile rounded on load
+// network products of the training tile: FP32 (three-part operands), or BF16
+// on the weights' high parts with the FP32 activation tile rounded on load:
 // one network product of the training tile (16 rows: primal + tangent) from
 // a ring filled ahead with the first k-steps of its weights
 template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void train_mma(BRing<BF16, TPW, DEPTH>& ring, const float* A, int lda, const bf16x8* Bbf,
-                                          const float* Bf, int K, int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
-  if constexpr (BF16) mma_bf16_a32_ring(ring, A, lda, 0, Bbf, K, nb0, nbs, NB, acc);
-  else mma_ring(ring, A, lda, 0, nullptr, Bf, K, nb0, nbs, NB, acc);
+__device__ __forceinline__ void train_mma(BRing<BF16, TPW, DEPTH>& ring, const float* A, int lda, const Weights& B,
+                                          int K, int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
+  if constexpr (BF16) mma_bf16_a32_ring(ring, A, lda, 0, B, K, nb0, nbs, NB, acc);
+  else mma_ring(ring, A, lda, 0, B, K, nb0, nbs, NB, acc);
 }
 
 template <int HP>
@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kTrainThreads)
   // product then fills the ring of the next one as soon as its own
   // fragments are consumed, ahead of its epilogue and barrier
   BRing<BF16, TPW> ring;
-  ring_fill(ring, m.w1_bf16, m.w1_f32, kFP, w, WPR, NBH);
+  ring_fill(ring, m.w1, kFP, w, WPR, NBH);
   // weight-product rows X1 = [G; Gdot]
   for (int t = tid; t < 16 * kFP; t += kTrainThreads) {
     const int r = t / kFP, f = t % kFP;
@@ -277,8 +277,8 @@ __global__ void __launch_bounds__(kTrainThreads)
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    train_mma(ring, sGT, L::LDG, m.w1_bf16, m.w1_f32, kFP, cw, WPR, NBH, acc);
-    ring_fill(ring, m.w2_bf16, m.w2_f32, HP, cw, WPR, NBH);
+    train_mma(ring, sGT, L::LDG, m.w1, kFP, cw, WPR, NBH, acc);
+    ring_fill(ring, m.w2, HP, cw, WPR, NBH);
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
       const int nb = cw + i * WPR;
@@ -307,8 +307,8 @@ __global__ void __launch_bounds__(kTrainThreads)
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    train_mma(ring, sH, L::LDH, m.w2_bf16, m.w2_f32, HP, cw, WPR, NBH, acc);
-    ring_fill(ring, m.w2t_bf16, m.w2t_f32, HP, cw, WPR, NBH);
+    train_mma(ring, sH, L::LDH, m.w2, HP, cw, WPR, NBH, acc);
+    ring_fill(ring, m.w2t, HP, cw, WPR, NBH);
     float ypart[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // primal lanes: h2 . w3bar, tangent lanes: h2dot . w3bar
     floatx4 d2out[TPW];
 #pragma unroll
@@ -374,8 +374,8 @@ __global__ void __launch_bounds__(kTrainThreads)
   {
     floatx4 acc[TPW];
     zero_acc(acc);
-    train_mma(ring, sH, L::LDH, m.w2t_bf16, m.w2t_f32, HP, cw, WPR, NBH, acc);
-    ring_fill(ring_g, m.w1t_bf16, m.w1t_f32, HP, cw, WPR, NBG);
+    train_mma(ring, sH, L::LDH, m.w2t, HP, cw, WPR, NBH, acc);
+    ring_fill(ring_g, m.w1t, HP, cw, WPR, NBG);
     __syncthreads();  // all reads of [z2bar; z2dotbar] done before the tile is overwritten
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
@@ -399,7 +399,7 @@ __global__ void __launch_bounds__(kTrainThreads)
   {
     floatx4 acc[TPW_G];
     zero_acc(acc);
-    train_mma(ring_g, sH, L::LDH, m.w1t_bf16, m.w1t_f32, HP, cw, WPR, NBG, acc);
+    train_mma(ring_g, sH, L::LDH, m.w1t, HP, cw, WPR, NBG, acc);
 #pragma unroll
     for (int i = 0; i < TPW_G; ++i) {
       const int nb = cw + i * WPR;
@@ -776,19 +776,44 @@ __global__ void __launch_bounds__(kPairBlock) pos_gather(DevSystem sys, const fl
 
 // ---------------------------------------------------------------------------
 // C[M][N] = sum_k A[k][M]^T B[k][N] over the rows k of chunk blockIdx.y
-// (split-K; partial[chunk][M][N]).  Each wave owns a 64 x 64 block of C as
-// 4 x 4 MFMA tiles, so every value loaded feeds four (SPLIT: twelve) MFMAs.
-// M and N are multiples of 64.
-//   SPLIT = false: FP32 MFMA 16x16x4, four k-steps of loads issued before
-//                  their MFMAs.
-//   SPLIT = true:  each FP32 operand x is split into hi = bf16(x) and
-//                  lo = bf16(x - hi) (nearest even), and a.b is taken as
-//                  hi.hi + hi.lo + lo.hi on BF16 MFMA 16x16x32 with FP32
-//                  accumulation: about 16 significant bits per product (the
-//                  dropped lo.lo is below 2^-16 of |a b|) at the BF16 rate.
+// (split-K; partial[chunk][M][N]), every FP32 operand taken in NP bf16 parts
+// on BF16 MFMA 16x16x32 with FP32 accumulation:
+//   NP = 2 (the BF16 network): hi.hi + hi.lo + lo.hi, about 16 significant
+//          bits per product (the dropped lo.lo is below 2^-16 of |a b|);
+//   NP = 3 (the FP32 network): the six products of mfma.h's FP32 form.
+// Each wave owns a 64 x 64 block of C as 4 x 4 MFMA tiles, so every value
+// loaded feeds twelve (24) MFMAs.  M and N are multiples of 64.
 constexpr int kWgRows = 1024;    // rows per split-K chunk
-constexpr int kWgRowsF32 = 512;  // rows per chunk of weight_grad_staged_f32 (twice the blocks)
-template <bool SPLIT>
+constexpr int kWgRowsF32 = 512;  // rows per chunk of the FP32 network's products (twice the blocks)
+
+// acc[c] += the NP-part products of one A fragment with four B fragments
+template <int NP>
+__device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&b)[4][NP], floatx4 (&acc)[4]) {
+  if constexpr (NP == 3) {
+    const Split3 x{a[0], a[1], a[2]};
+    mma_six(acc, [&](int) -> const Split3& { return x; },
+            [&](int c) { return Split3{b[c][0], b[c][1], b[c][2]}; });
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[c][0], acc[c], 0, 0, 0);
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[c][1], acc[c], 0, 0, 0);
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[c][0], acc[c], 0, 0, 0);
+    }
+  }
+}
+// the NP parts of a loaded value into element e of the fragments
+template <int NP>
+__device__ __forceinline__ void put_parts(float v, bf16x8 (&o)[NP], int e) {
+  const __bf16 h = (__bf16)v;
+  const float r = v - (float)h;
+  const __bf16 m = (__bf16)r;
+  o[0][e] = h;
+  o[1][e] = m;
+  if constexpr (NP == 3) o[2][e] = (__bf16)(r - (float)m);
+}
+
+template <int NP>
 __global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, int ldA, const float* __restrict__ B,
                                                    int ldB, int Mdim, int Ndim, int64_t K, int64_t kchunk,
                                                    float* __restrict__ partial) {
@@ -806,60 +831,30 @@ __global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, 
     for (int c = 0; c < 4; ++c) acc[r][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
   const float* ap = A + m0 + (l & 15);
   const float* bp = B + n0 + (l & 15);
-  if (!SPLIT) {
-    // lane l supplies A^T[m = l&15][k = l>>4] = A[k][m] and B[k = l>>4][n = l&15]
-    for (int64_t k = kb; k < ke; k += 16) {
-      float a[4][4], b[4][4];
+  // lane l supplies A^T[m = l&15][k = 8 (l>>4) + e] and B[k = 8 (l>>4) + e][n = l&15], e < 8
+  for (int64_t k = kb; k < ke; k += 32) {
+    float a[4][8], b[4][8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t kk = k + 4 * u + (l >> 4);
-        const bool ok = kk < ke;
+    for (int e = 0; e < 8; ++e) {
+      const int64_t kk = k + 8 * (l >> 4) + e;
+      const bool ok = kk < ke;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          a[u][r] = ok ? ap[kk * ldA + r * 16] : 0.0f;
-          b[u][r] = ok ? bp[kk * ldB + r * 16] : 0.0f;
-        }
+      for (int r = 0; r < 4; ++r) {
+        a[r][e] = ok ? ap[kk * ldA + r * 16] : 0.0f;
+        b[r][e] = ok ? bp[kk * ldB + r * 16] : 0.0f;
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b[u][c], acc[r][c], 0, 0, 0);
     }
-  } else {
-    // lane l supplies A^T[m = l&15][k = 8 (l>>4) + e] and B[k = 8 (l>>4) + e][n = l&15], e < 8
-    for (int64_t k = kb; k < ke; k += 32) {
-      float a[4][8], b[4][8];
+    bf16x8 bs[4][NP];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t kk = k + 8 * (l >> 4) + e;
-        const bool ok = kk < ke;
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          a[r][e] = ok ? ap[kk * ldA + r * 16] : 0.0f;
-          b[r][e] = ok ? bp[kk * ldB + r * 16] : 0.0f;
-        }
-      }
-      bf16x8 ah[4], al[4], bh[4], bl[4];
+      for (int e = 0; e < 8; ++e) put_parts<NP>(b[c][e], bs[c], e);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r) {
+      bf16x8 as[NP];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const __bf16 x = (__bf16)a[r][e], y = (__bf16)b[r][e];
-          ah[r][e] = x;
-          al[r][e] = (__bf16)(a[r][e] - (float)x);
-          bh[r][e] = y;
-          bl[r][e] = (__bf16)(b[r][e] - (float)y);
-        }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[r], bh[c], acc[r][c], 0, 0, 0);
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[r], bl[c], acc[r][c], 0, 0, 0);
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[r], bh[c], acc[r][c], 0, 0, 0);
-        }
+      for (int e = 0; e < 8; ++e) put_parts<NP>(a[r][e], as, e);
+      mma_parts<NP>(as, bs, acc[r]);
     }
   }
 #pragma unroll
@@ -873,20 +868,20 @@ __global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, 
       }
 }
 
-// The split product of weight_grad<true> for M and N multiples of 128, with
-// the operand rows staged through LDS: a block of 4 waves owns a 128 x 128
-// block of C (2 x 2 waves of 64 x 64, with the fragments and the MFMA
-// sequence of weight_grad<true>).  Per k-step of 32
-// rows every thread loads 16 rows of one column of A and of B, splits them
-// once for the whole block, and writes them to LDS as k-contiguous hi and lo
-// runs; the next k-step's loads are issued before the current step's MFMAs.
+// The same products for M and N multiples of 128, with the operand rows
+// staged through LDS: a block of 4 waves owns a 128 x 128 block of C (2 x 2
+// waves of 64 x 64).  Per k-step of 32 rows every thread loads 16 rows of one
+// column of A and of B, splits them once for the whole block, and writes them
+// to LDS as k-contiguous runs of each part; the next k-step's loads are
+// issued before the current step's MFMAs.
 constexpr int kWgBlk = 128;  // block tile edge
 constexpr int kWgLdk = 40;   // LDS row stride in bf16 (32 k + 8 pad)
+template <int NP>
 __global__ void __launch_bounds__(256) weight_grad_staged(const float* __restrict__ A, int ldA,
                                                           const float* __restrict__ B, int ldB, int Mdim, int Ndim,
                                                           int64_t K, int64_t kchunk, float* __restrict__ partial) {
-  // [Ahi, Alo, Bhi, Blo][column][k]
-  __shared__ __attribute__((aligned(16))) __bf16 sm[4][kWgBlk * kWgLdk];
+  // [A parts, B parts][column][k]
+  __shared__ __attribute__((aligned(16))) __bf16 sm[2 * NP][kWgBlk * kWgLdk];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int tiles_n = Ndim / kWgBlk;
   const int mb = (blockIdx.x / tiles_n) * kWgBlk, nb = (blockIdx.x % tiles_n) * kWgBlk;
@@ -917,129 +912,37 @@ __global__ void __launch_bounds__(256) weight_grad_staged(const float* __restric
     __syncthreads();  // the previous step's fragment reads are done
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      bf16x8 ah, al, bh, bl;
+      bf16x8 a[NP], b[NP];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float x = ra[8 * half + e], y = rb[8 * half + e];
-        const __bf16 xh = (__bf16)x, yh = (__bf16)y;
-        ah[e] = xh;
-        al[e] = (__bf16)(x - (float)xh);
-        bh[e] = yh;
-        bl[e] = (__bf16)(y - (float)yh);
+        put_parts<NP>(ra[8 * half + e], a, e);
+        put_parts<NP>(rb[8 * half + e], b, e);
       }
       const int o = col * kWgLdk + 16 * h + 8 * half;
-      *(bf16x8*)&sm[0][o] = ah;
-      *(bf16x8*)&sm[1][o] = al;
-      *(bf16x8*)&sm[2][o] = bh;
-      *(bf16x8*)&sm[3][o] = bl;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        *(bf16x8*)&sm[q][o] = a[q];
+        *(bf16x8*)&sm[NP + q][o] = b[q];
+      }
     }
     __syncthreads();
     if (k + 32 < ke) fetch(k + 32);
     // lane l supplies A^T[m = l&15][k = 8 (l>>4) + e] and B[k = 8 (l>>4) + e][n = l&15]
-    bf16x8 bh[4], bl[4];
+    bf16x8 b[4][NP];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int o = (n0 + 16 * c + (l & 15)) * kWgLdk + 8 * (l >> 4);
-      bh[c] = *(const bf16x8*)&sm[2][o];
-      bl[c] = *(const bf16x8*)&sm[3][o];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) b[c][q] = *(const bf16x8*)&sm[NP + q][o];
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int o = (m0 + 16 * r + (l & 15)) * kWgLdk + 8 * (l >> 4);
-      const bf16x8 ah = *(const bf16x8*)&sm[0][o];
-      const bf16x8 al = *(const bf16x8*)&sm[1][o];
+      bf16x8 a[NP];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[c], acc[r][c], 0, 0, 0);
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[c], acc[r][c], 0, 0, 0);
-        acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[c], acc[r][c], 0, 0, 0);
-      }
+      for (int q = 0; q < NP; ++q) a[q] = *(const bf16x8*)&sm[q][o];
+      mma_parts<NP>(a, b, acc[r]);
     }
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = mb + m0 + r * 16 + 4 * (l >> 4) + j, cc = nb + n0 + c * 16 + (l & 15);
-        partial[((int64_t)blockIdx.y * Mdim + row) * Ndim + cc] = acc[r][c][j];
-      }
-}
-
-// The FP32 product of weight_grad<false> for M and N multiples of 128,
-// staged through LDS like weight_grad_staged (128 x 128 block tile, 2 x 2
-// waves of 64 x 64, k-steps of 32 rows, the next step's rows in flight
-// during the MFMAs).  A column's 32 rows are stored permuted, row k at
-// 8 (k % 4) + k / 4, so that the 8 values lane l supplies over the step's
-// eight 16x16x4 products (rows 4 u + (l >> 4), u < 8) are contiguous.  The
-// MFMA sequence per element is weight_grad<false>'s.
-constexpr int kWgLdkF = 36;  // LDS row stride in floats (32 k + 4 pad)
-__global__ void __launch_bounds__(256) weight_grad_staged_f32(const float* __restrict__ A, int ldA,
-                                                              const float* __restrict__ B, int ldB, int Mdim,
-                                                              int Ndim, int64_t K, int64_t kchunk,
-                                                              float* __restrict__ partial) {
-  // [A, B][column][permuted k]
-  __shared__ __attribute__((aligned(16))) float sm[2][kWgBlk * kWgLdkF];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-  const int tiles_n = Ndim / kWgBlk;
-  const int mb = (blockIdx.x / tiles_n) * kWgBlk, nb = (blockIdx.x % tiles_n) * kWgBlk;
-  const int m0 = (w >> 1) * 64, n0 = (w & 1) * 64;
-  const int64_t kb = (int64_t)blockIdx.y * kchunk;
-  const int64_t ke = min(K, kb + kchunk);
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[r][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int col = tid & (kWgBlk - 1), h = tid >> 7;
-  const float* ap = A + mb + col;
-  const float* bp = B + nb + col;
-  float ra[16], rb[16];
-  auto fetch = [&](int64_t k) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int64_t kk = k + 16 * h + e;
-      const bool ok = kk < ke;
-      ra[e] = ok ? ap[kk * ldA] : 0.0f;
-      rb[e] = ok ? bp[kk * ldB] : 0.0f;
-    }
-  };
-  if (kb < ke) fetch(kb);
-  for (int64_t k = kb; k < ke; k += 32) {
-    __syncthreads();  // the previous step's fragment reads are done
-    // rows 16 h + e, e = q + 4 j (j < 4), go to 8 q + 4 h + j: one float4 per q
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int o = col * kWgLdkF + 8 * q + 4 * h;
-      *(floatx4*)&sm[0][o] = floatx4{ra[q], ra[q + 4], ra[q + 8], ra[q + 12]};
-      *(floatx4*)&sm[1][o] = floatx4{rb[q], rb[q + 4], rb[q + 8], rb[q + 12]};
-    }
-    __syncthreads();
-    if (k + 32 < ke) fetch(k + 32);
-    // lane l's values for products u < 8: rows 4 u + (l >> 4), stored at 8 (l >> 4) + u
-    floatx4 bf[4][2];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int o = (n0 + 16 * c + (l & 15)) * kWgLdkF + 8 * (l >> 4);
-      bf[c][0] = *(const floatx4*)&sm[1][o];
-      bf[c][1] = *(const floatx4*)&sm[1][o + 4];
-    }
-    floatx4 af[4][2];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int o = (m0 + 16 * r + (l & 15)) * kWgLdkF + 8 * (l >> 4);
-      af[r][0] = *(const floatx4*)&sm[0][o];
-      af[r][1] = *(const floatx4*)&sm[0][o + 4];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[r][u >> 2][u & 3], bf[c][u >> 2][u & 3], acc[r][c], 0,
-                                                           0, 0);
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r)
@@ -1363,28 +1266,20 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
   const int64_t wg_rows = (staged && !bf16) ? kWgRowsF32 : kWgRows;
   const int kch = (int)((L.K + wg_rows - 1) / wg_rows);
   {
-    const int t1 = (kFP / 64) * (HP / 64);
-    const int t2 = (HP / 64) * (HP / 64);
     if (kch > 0) {
-      // the BF16 path takes the split-BF16 products, the FP32 path plain FP32
-      if (bf16 && staged) {
-        // kFP and HP are multiples of the staged kernel's 128-wide block tile
-        hipLaunchKernelGGL(weight_grad_staged, dim3((kFP / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s,
-                           X1, kFP, Y1, HP, kFP, HP, L.K, wg_rows, part1);
-        hipLaunchKernelGGL(weight_grad_staged, dim3((HP / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s,
-                           X2, HP, Y2, HP, HP, HP, L.K, wg_rows, part2);
-      } else if (staged) {
-        hipLaunchKernelGGL(weight_grad_staged_f32, dim3((kFP / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0,
-                           s, X1, kFP, Y1, HP, kFP, HP, L.K, wg_rows, part1);
-        hipLaunchKernelGGL(weight_grad_staged_f32, dim3((HP / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0,
-                           s, X2, HP, Y2, HP, HP, HP, L.K, wg_rows, part2);
-      } else {
-        auto wg = bf16 ? weight_grad<true> : weight_grad<false>;
-        hipLaunchKernelGGL(wg, dim3((t1 + 3) / 4, kch), dim3(256), 0, s, X1, kFP, Y1, HP, kFP, HP, L.K,
-                           wg_rows, part1);
-        hipLaunchKernelGGL(wg, dim3((t2 + 3) / 4, kch), dim3(256), 0, s, X2, HP, Y2, HP, HP, HP, L.K,
-                           wg_rows, part2);
-      }
+      // two parts per operand on the BF16 path, three on the FP32 path; widths
+      // that are multiples of the staged kernel's block tile take it
+      auto product = [&](const float* X, int ldx, const float* Y, float* part) {
+        if (staged)
+          hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
+                             dim3((ldx / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K,
+                             wg_rows, part);
+        else
+          hipLaunchKernelGGL(bf16 ? weight_grad<2> : weight_grad<3>, dim3(((ldx / 64) * (HP / 64) + 3) / 4, kch),
+                             dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K, wg_rows, part);
+      };
+      product(X1, kFP, Y1, part1);
+      product(X2, HP, Y2, part2);
     }
     const int64_t n1 = (int64_t)kFP * HP, n2 = (int64_t)HP * HP;
     // [kFP][HP] and [HP][HP] partials summed straight into the caller's [F][H1] and [H1][H2]
