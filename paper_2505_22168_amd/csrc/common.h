@@ -155,38 +155,4 @@ __device__ inline int wave_incl_scan(int v) {
 
 __device__ inline void raise_flag(uint32_t* status, uint32_t f) { atomicOr(status, f); }
 
-// ---------------------------------------------------------------------------
-// block-level exclusive scan of `n` int32 counts into int64 offsets (n+1
-// entries, out[n] = total).  One block; every thread of the block calls it.
-// ---------------------------------------------------------------------------
-template <int BLOCK>
-__device__ inline void block_exclusive_scan(const int32_t* __restrict__ in, int64_t* __restrict__ out,
-                                            int64_t n, int64_t* total_out) {
-  __shared__ int64_t sums[BLOCK];
-  const int t = threadIdx.x;
-  const int64_t chunk = (n + BLOCK - 1) / BLOCK;
-  const int64_t b0 = t * chunk;
-  const int64_t b1 = (b0 + chunk < n) ? b0 + chunk : n;
-  int64_t s = 0;
-  for (int64_t k = b0; k < b1; ++k) s += in[k];
-  sums[t] = s;
-  __syncthreads();
-  // Hillis-Steele over BLOCK partial sums
-  for (int o = 1; o < BLOCK; o <<= 1) {
-    int64_t v = (t >= o) ? sums[t - o] : 0;
-    __syncthreads();
-    sums[t] += v;
-    __syncthreads();
-  }
-  int64_t run = (t == 0) ? 0 : sums[t - 1];
-  for (int64_t k = b0; k < b1; ++k) {
-    out[k] = run;
-    run += in[k];
-  }
-  if (t == BLOCK - 1) {
-    out[n] = sums[BLOCK - 1];
-    if (total_out) *total_out = sums[BLOCK - 1];
-  }
-}
-
 }  // namespace gmnn

@@ -6,6 +6,7 @@
 namespace gmnn {
 
 constexpr int kMaxCellsPerAxis = 1024;
+constexpr double kCellsPerRadius = 2.0;  // cells along the list radius (stencils of 5 cells per axis)
 
 // cell grid of one structure, computed on the device by nl_setup
 struct StructGrid {
@@ -21,7 +22,7 @@ struct StructGrid {
 struct NlLayout {
   int64_t cell_capacity = 0;
   size_t off_grids = 0, off_cell_count = 0, off_cell_fill = 0, off_cell_start = 0, off_cells_total = 0;
-  size_t off_atom_cell = 0, off_atom_img = 0, off_cell_atoms = 0, off_row_count = 0, off_go = 0;
+  size_t off_atom_cell = 0, off_atom_img = 0, off_cell_atoms = 0, off_cell_img = 0, off_scan = 0, off_row_count = 0, off_go = 0;
   size_t bytes = 0;
 };
 

@@ -7,15 +7,30 @@
 // image.  The list is canonical (rows by i, inside a row by (j, Sx, Sy, Sz)),
 // so it is bit-identical whatever order the atoms land in their cells.
 //
-// Kernels (one build = 8 launches, all on the caller's stream):
+// Kernels (one build = 8 launches, 2 more above kScanOne elements a scan, all
+// on the caller's stream):
 //   nl_setup     one block: per-structure cell grid, cell offsets, clears
 //   nl_bin       thread/atom: fractional coords, image, cell, cell counts
-//   scan         one block: cell counts -> cell starts
-//   nl_cellfill  thread/atom: atoms into their cell slots
+//   scan         cell counts -> cell starts
+//   nl_cellfill  thread/atom: positions and images into cell order
 //   nl_rows<0>   wave/atom: count neighbours (FP64 inclusion test)
-//   scan         one block: row counts -> row_ptr, n_pairs
+//   scan         row counts -> row_ptr, n_pairs
 //   nl_rows<1>   wave/atom: collect, rank-sort in LDS, write the row
-//   nl_reverse   wave/atom: index of the reverse pair by binary search
+//   nl_reverse   wave/atom: index of the reverse pair, guessed, then searched
+//
+// What bounds it.  The 11.0M pairs of the 100k solid are 135 MB of output,
+// about 30 us; the build is bound by its candidates (instructions per tested
+// pair, dependent loads) and by the lanes' scattered loads of the reverse
+// search.  Cells of half the list radius (125 of them hold 430 candidates per
+// atom at that density, 27 whole ones 740) and candidates stored in cell
+// order, so that a run of cells along the third axis is one contiguous read,
+// took the two row passes from 433 and 622 us to 207 and 323 us (with the
+// 32-bit rank sort); the mirrored first guess of the reverse search (45% of
+// the pairs of a jittered lattice) took it from 456 to 255 us, the scans from
+// 94 to 9 us.  The build: 1.77 -> 0.85 ms.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 #include "neighbors.h"
 
@@ -24,7 +39,17 @@ namespace gmnn {
 // ---------------------------------------------------------------------------
 // per-structure grid (device)
 // ---------------------------------------------------------------------------
-__device__ inline void grid_of_structure(const double* h, const uint8_t* pbc, double rbin, StructGrid& g) {
+__host__ __device__ inline int cells_on_axis(double x) {
+  const double f = floor(x);
+  return f < 1.0 ? 1 : f > (double)kMaxCellsPerAxis ? kMaxCellsPerAxis : (int)f;
+}
+// a structure takes the fine grid while its cells stay within a few per atom
+// (clearing and scanning the cells of a mostly empty box would cost more than
+// the candidates saved)
+__host__ __device__ inline long long max_fine_cells(int64_t n_atoms) { return 8 * (long long)n_atoms + 1024; }
+
+__device__ inline void grid_of_structure(const double* h, const uint8_t* pbc, double rbin, int64_t n_atoms,
+                                         StructGrid& g) {
   for (int k = 0; k < 9; ++k) g.h[k] = h[k];
   // inverse of the row-vector lattice: frac_k = sum_c x_c inv[c][k]
   const double a00 = h[0], a01 = h[1], a02 = h[2];
@@ -41,14 +66,19 @@ __device__ inline void grid_of_structure(const double* h, const uint8_t* pbc, do
   g.inv[6] = c02 * id; g.inv[7] = c12 * id; g.inv[8] = c22 * id;
   const double vol = fabs(det);
   const double cr[3][3] = {{c00, c01, c02}, {c10, c11, c12}, {c20, c21, c22}};
-  long long cells = 1;
+  double width[3];
   for (int k = 0; k < 3; ++k) {
     // |h_{k+1} x h_{k+2}| = |cofactor row k|; width = vol / that
     const double nrm = sqrt(cr[k][0] * cr[k][0] + cr[k][1] * cr[k][1] + cr[k][2] * cr[k][2]);
-    const double width = vol / nrm;
-    double fnc = floor(width / rbin);
-    int nc = (fnc < 1.0) ? 1 : (fnc > (double)kMaxCellsPerAxis ? kMaxCellsPerAxis : (int)fnc);
-    int m = (int)ceil(rbin * (double)nc / width);
+    width[k] = vol / nrm;
+  }
+  long long cells = 1;
+  for (int k = 0; k < 3; ++k) cells *= cells_on_axis(kCellsPerRadius * width[k] / rbin);
+  const double fine = cells <= max_fine_cells(n_atoms) ? kCellsPerRadius : 1.0;
+  cells = 1;
+  for (int k = 0; k < 3; ++k) {
+    const int nc = cells_on_axis(fine * width[k] / rbin);
+    int m = (int)ceil(rbin * (double)nc / width[k]);
     if (m < 1) m = 1;
     g.nc[k] = nc;
     g.m[k] = m;
@@ -62,7 +92,7 @@ __device__ inline void grid_of_structure(const double* h, const uint8_t* pbc, do
 // build (float bits); the build runs only if it exceeds thresh2 (the go flag
 // every later kernel of the build checks)
 __global__ void __launch_bounds__(1024) nl_setup(const double* __restrict__ cell, const uint8_t* __restrict__ pbc,
-                                                 int n_structs, double rbin, StructGrid* __restrict__ grids,
+                                                 const int64_t* __restrict__ atom_ptr, int n_structs, double rbin, StructGrid* __restrict__ grids,
                                                  int64_t cell_capacity, int32_t* __restrict__ cell_count,
                                                  int32_t* __restrict__ cell_fill, int64_t* __restrict__ n_cells_total,
                                                  uint32_t* __restrict__ status, const uint32_t* __restrict__ disp_bits,
@@ -85,7 +115,7 @@ __global__ void __launch_bounds__(1024) nl_setup(const double* __restrict__ cell
     StructGrid g;
     int64_t nc = 0;
     if (b < n_structs) {
-      grid_of_structure(cell + 9 * (int64_t)b, pbc + 3 * (int64_t)b, rbin, g);
+      grid_of_structure(cell + 9 * (int64_t)b, pbc + 3 * (int64_t)b, rbin, atom_ptr[b + 1] - atom_ptr[b], g);
       nc = g.n_cells;
     }
     part[t] = nc;
@@ -172,35 +202,151 @@ __global__ void nl_bin(const float* __restrict__ pos, const int64_t* __restrict_
   atomicAdd(&cell_count[cid], 1);
 }
 
-__global__ void __launch_bounds__(1024) scan_i32(const int32_t* __restrict__ in, int64_t* __restrict__ out,
-                                                 const int64_t* __restrict__ n_dev, int64_t n_host,
-                                                 int64_t* __restrict__ total, const int* __restrict__ go,
-                                                 int64_t cap) {
+// ---------------------------------------------------------------------------
+// Exclusive scans of int32 counts into int64 offsets (n + 1 entries).  n_dev
+// (if given) is clamped to n_host, the length of `in`.  cap >= 0: offsets
+// beyond the pair capacity would send the pair kernels past the list arrays,
+// so an overflowing list is left empty (the total still reports the size
+// needed, and the capacity flag is raised later).  Up to kScanOne elements
+// one block walks over them (a launch less); above, every block of
+// kScanTile elements is summed first, and then scanned behind the sum of the
+// blocks before it.
+constexpr int kScanThreads = 1024;
+constexpr int kScanTile = 4 * kScanThreads;
+constexpr int64_t kScanOne = 4 * kScanTile;
+
+__device__ inline int64_t scan_length(const int64_t* n_dev, int64_t n_host) {
+  return n_dev && *n_dev < n_host ? *n_dev : n_host;
+}
+__device__ inline int4 scan_load(const int32_t* __restrict__ in, int64_t e, int64_t n) {
+  int4 v = {0, 0, 0, 0};
+  if (e + 4 <= n) return *(const int4*)(in + e);
+  if (e < n) v.x = in[e];
+  if (e + 1 < n) v.y = in[e + 1];
+  if (e + 2 < n) v.z = in[e + 2];
+  return v;
+}
+// exclusive prefix of v over the block's threads; total: the block's sum
+__device__ inline int block_prefix(int v, int* sums, int& total) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int incl = wave_incl_scan(v);
+  __syncthreads();  // the previous use of sums is read
+  if (l == 63) sums[w] = incl;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+  for (int k = 0; k < kScanThreads / 64; ++k) {
+    if (k < w) before += sums[k];
+    total += sums[k];
+  }
+  return before + incl - v;
+}
+__device__ inline void scan_store(int64_t* __restrict__ out, int64_t e, int64_t n, int64_t base, int4 v, bool zero) {
+  const int64_t o[4] = {base, base + v.x, base + v.x + v.y, base + v.x + v.y + v.z};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (e + k < n) out[e + k] = zero ? 0 : o[k];
+}
+
+__global__ void __launch_bounds__(kScanThreads) scan_one(const int32_t* __restrict__ in, int64_t* __restrict__ out,
+                                                         const int64_t* __restrict__ n_dev, int64_t n_host,
+                                                         int64_t* __restrict__ total, const int* __restrict__ go,
+                                                         int64_t cap) {
   if (!*go) return;
-  // n_dev (if given) is clamped to n_host, the length of `in`
-  int64_t n = n_host;
-  if (n_dev && *n_dev < n_host) n = *n_dev;
-  block_exclusive_scan<1024>(in, out, n, total);
-  // cap >= 0: offsets beyond the pair capacity would send the pair kernels
-  // past the list arrays, so an overflowing list is left empty (the total
-  // still reports the size needed, and the capacity flag is raised later)
-  if (cap >= 0) {
+  __shared__ int sums[kScanThreads / 64];
+  const int64_t n = scan_length(n_dev, n_host);
+  int64_t base = 0;
+  for (int64_t t0 = 0; t0 < n; t0 += kScanTile) {
+    const int64_t e = t0 + 4 * (int64_t)threadIdx.x;
+    const int4 v = scan_load(in, e, n);
+    int sum;
+    const int before = block_prefix(v.x + v.y + v.z + v.w, sums, sum);
+    scan_store(out, e, n, base + before, v, false);
+    base += sum;
+  }
+  const bool over = cap >= 0 && base > cap;
+  if (over) {
     __syncthreads();
-    if (out[n] > cap)
-      for (int64_t k = threadIdx.x; k <= n; k += 1024) out[k] = 0;
+    for (int64_t k = threadIdx.x; k < n; k += kScanThreads) out[k] = 0;
+  }
+  if (threadIdx.x == 0) {
+    out[n] = over ? 0 : base;
+    if (total) *total = base;
   }
 }
 
-__global__ void nl_cellfill(int n_atoms, const int32_t* __restrict__ atom_cell, const int64_t* __restrict__ cell_start,
+__global__ void __launch_bounds__(kScanThreads) scan_sums(const int32_t* __restrict__ in,
+                                                          const int64_t* __restrict__ n_dev, int64_t n_host,
+                                                          int32_t* __restrict__ part, const int* __restrict__ go) {
+  if (!*go) return;
+  __shared__ int sums[kScanThreads / 64];
+  const int64_t n = scan_length(n_dev, n_host);
+  const int4 v = scan_load(in, (int64_t)blockIdx.x * kScanTile + 4 * (int64_t)threadIdx.x, n);
+  int sum;
+  (void)block_prefix(v.x + v.y + v.z + v.w, sums, sum);
+  if (threadIdx.x == 0) part[blockIdx.x] = sum;
+}
+
+__global__ void __launch_bounds__(kScanThreads) scan_write(const int32_t* __restrict__ in, int64_t* __restrict__ out,
+                                                           const int64_t* __restrict__ n_dev, int64_t n_host,
+                                                           const int32_t* __restrict__ part,
+                                                           int64_t* __restrict__ total, const int* __restrict__ go,
+                                                           int64_t cap) {
+  if (!*go) return;
+  __shared__ int sums[kScanThreads / 64];
+  __shared__ int64_t wide[2][kScanThreads / 64];
+  const int64_t n = scan_length(n_dev, n_host);
+  const int nb = gridDim.x;
+  // the sums of the blocks before this one, and of all
+  int64_t mine = 0, all = 0;
+  for (int k = threadIdx.x; k < nb; k += kScanThreads) {
+    const int64_t x = part[k];
+    all += x;
+    if (k < (int)blockIdx.x) mine += x;
+  }
+  mine = wave_sum(mine);
+  all = wave_sum(all);
+  if ((threadIdx.x & 63) == 0) {
+    wide[0][threadIdx.x >> 6] = mine;
+    wide[1][threadIdx.x >> 6] = all;
+  }
+  __syncthreads();
+  int64_t base = 0, sum_all = 0;
+  for (int k = 0; k < kScanThreads / 64; ++k) {
+    base += wide[0][k];
+    sum_all += wide[1][k];
+  }
+  const bool over = cap >= 0 && sum_all > cap;
+  const int64_t e = (int64_t)blockIdx.x * kScanTile + 4 * (int64_t)threadIdx.x;
+  const int4 v = scan_load(in, e, n);
+  int sum;
+  const int before = block_prefix(v.x + v.y + v.z + v.w, sums, sum);
+  scan_store(out, e, n, base + before, v, over);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    out[n] = over ? 0 : sum_all;
+    if (total) *total = sum_all;
+  }
+}
+
+// positions and images of the atoms in cell order: {x, y, z, atom} and the
+// image (three ints); the order inside a cell is arbitrary (rows are sorted)
+struct CellAtom {
+  float x, y, z;
+  int j;
+};
+__global__ void nl_cellfill(int n_atoms, const float* __restrict__ pos, const int32_t* __restrict__ atom_cell,
+                            const int4* __restrict__ atom_img, const int64_t* __restrict__ cell_start,
                             const int64_t* __restrict__ n_cells_total, int64_t cell_capacity,
-                            int32_t* __restrict__ cell_fill, int32_t* __restrict__ cell_atoms, const int* __restrict__ go) {
+                            int32_t* __restrict__ cell_fill, CellAtom* __restrict__ cell_atoms,
+                            int4* __restrict__ cell_img, const int* __restrict__ go) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_atoms) return;
   if (!*go) return;
   if (*n_cells_total > cell_capacity) return;
   const int c = atom_cell[i];
-  const int slot = atomicAdd(&cell_fill[c], 1);
-  cell_atoms[cell_start[c] + slot] = i;
+  const int64_t slot = cell_start[c] + atomicAdd(&cell_fill[c], 1);
+  cell_atoms[slot] = CellAtom{pos[3 * (int64_t)i], pos[3 * (int64_t)i + 1], pos[3 * (int64_t)i + 2], i};
+  cell_img[slot] = atom_img[i];
 }
 
 __device__ inline int floor_div(int a, int b) {
@@ -220,22 +366,35 @@ __device__ inline double pair_d2(const double xi[3], const double xj[3], const d
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-constexpr int kRowsWaves = 4;  // waves per block in nl_rows / nl_reverse
+// the same without a shift: adding the zero shift to the separation rounds
+// to the separation itself
+__device__ inline double pair_d2_home(const double xi[3], const double xj[3]) {
+#pragma clang fp contract(off)
+  const double dx = xj[0] - xi[0], dy = xj[1] - xi[1], dz = xj[2] - xi[2];
+  return (dx * dx + dy * dy) + dz * dz;
+}
 
+constexpr int kRowsWaves = 4;    // waves per block in nl_rows / nl_reverse
+constexpr int kRowKeys = 512;    // keys of a row sorted in LDS; longer rows are sorted from the output arrays
+
+// The candidates of atom i: runs of cells along the third axis, contiguous in
+// cell order.  Run t of (2 m0 + 1)(2 m1 + 1) K: the column (o0, o1), and of
+// the cells c2 - m2 .. c2 + m2 those in image s2_lo + t % K.
+//
 // MODE 0: count neighbours of every atom; MODE 1: collect, sort, write.
 template <int MODE>
 __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
     const float* __restrict__ pos, int n_atoms, const StructGrid* __restrict__ grids,
     const int32_t* __restrict__ atom_struct, const int4* __restrict__ atom_img,
-    const int64_t* __restrict__ cell_start, const int32_t* __restrict__ cell_atoms,
-    const int64_t* __restrict__ n_cells_total, int64_t cell_capacity, double rc2,
+    const int64_t* __restrict__ cell_start, const CellAtom* __restrict__ cell_atoms,
+    const int4* __restrict__ cell_img, const int64_t* __restrict__ n_cells_total, int64_t cell_capacity, double rc2,
     int32_t* __restrict__ row_count, const int64_t* __restrict__ row_ptr, const int64_t* __restrict__ n_pairs,
     int64_t capacity, int32_t* __restrict__ out_j, int32_t* __restrict__ out_shift, uint32_t* __restrict__ status,
     const int* __restrict__ go) {
   __shared__ int s_excl[kRowsWaves][64];
   __shared__ int s_start[kRowsWaves][64];
   __shared__ int s_sw[kRowsWaves][64];
-  __shared__ uint64_t s_keys[MODE ? kRowsWaves : 1][MODE ? GMNN_MAX_ROW : 1];
+  __shared__ __attribute__((aligned(16))) uint64_t s_keys[MODE ? kRowsWaves : 1][MODE ? kRowKeys : 1];
   const int w = threadIdx.x >> 6;
   const int l = threadIdx.x & 63;
   const int i = xcd_block(blockIdx.x, gridDim.x) * kRowsWaves + w;
@@ -251,79 +410,93 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
   const int4 ii = atom_img[i];
   const int ci[3] = {(ii.w >> 20) & 1023, (ii.w >> 10) & 1023, ii.w & 1023};
   const double xi[3] = {(double)pos[3 * (int64_t)i], (double)pos[3 * (int64_t)i + 1], (double)pos[3 * (int64_t)i + 2]};
-  const int w0 = 2 * g.m[0] + 1, w1 = 2 * g.m[1] + 1, w2 = 2 * g.m[2] + 1;
-  const int T = w0 * w1 * w2;
+  const int w1 = 2 * g.m[1] + 1;
+  const int lo2 = ci[2] - g.m[2], hi2 = ci[2] + g.m[2];
+  const int s2_lo = g.pbc[2] ? floor_div(lo2, g.nc[2]) : 0;
+  const int K = (g.pbc[2] ? floor_div(hi2, g.nc[2]) : 0) - s2_lo + 1;
+  const int T = (2 * g.m[0] + 1) * w1 * K;
+  const float inv_k = 1.0f / (float)K, inv_w = 1.0f / (float)w1;
   int count = 0;
   int base = 0;         // MODE 1: keys collected so far
-  bool overflow = false;
+  int n = 0;            // MODE 1: the row's length
+  int64_t r0 = 0;
   bool coincident = false;
   bool shift_range = false;
-  if (MODE == 1 && row_count[i] > GMNN_MAX_ROW) {
-    // flagged by the count pass; the row's slots take self pairs (zero
-    // separation: every kernel skips them) so the list stays well formed
-    const int64_t r0 = row_ptr[i];
-    for (int e = l; e < row_count[i]; e += 64) {
-      out_j[r0 + e] = i;
-      out_shift[r0 + e] = 0;
-    }
-    return;
+  bool wide = false;    // a key that does not fit the 32-bit form
+  if (MODE == 1) {
+    r0 = row_ptr[i];
+    n = row_count[i];
   }
+  const bool in_lds = n <= kRowKeys;
   for (int t0 = 0; t0 < T; t0 += 64) {
     const int t = t0 + l;
     int cnt = 0, start = 0, swp = 0;
     if (t < T) {
-      const int o2 = t % w2 - g.m[2];
-      const int o1 = (t / w2) % w1 - g.m[1];
-      const int o0 = t / (w2 * w1) - g.m[0];
-      const int oo[3] = {o0, o1, o2};
-      int cc[3], sw[3];
+      // t = (o0 * w1 + o1) * K + o2 (exact in FP32: a handful of runs)
+      const int q0 = (int)(((float)t + 0.5f) * inv_k), o2 = t - q0 * K;
+      const int q1 = (int)(((float)q0 + 0.5f) * inv_w), o1 = q0 - q1 * w1;
+      const int cell[2] = {ci[0] + q1 - g.m[0], ci[1] + o1 - g.m[1]};
+      int cc[2], sw[3];
       bool ok = true;
-      for (int k = 0; k < 3; ++k) {
-        const int c = ci[k] + oo[k];
+      for (int k = 0; k < 2; ++k) {
         if (g.pbc[k]) {
-          sw[k] = floor_div(c, g.nc[k]);
-          cc[k] = c - sw[k] * g.nc[k];
+          // at most one image away while the stencil is narrower than the grid
+          sw[k] = g.m[k] <= g.nc[k] ? (cell[k] < 0 ? -1 : cell[k] >= g.nc[k] ? 1 : 0) : floor_div(cell[k], g.nc[k]);
+          cc[k] = cell[k] - sw[k] * g.nc[k];
         } else {
           sw[k] = 0;
-          cc[k] = c;
-          if (c < 0 || c >= g.nc[k]) ok = false;
+          cc[k] = cell[k];
+          if (cell[k] < 0 || cell[k] >= g.nc[k]) ok = false;
         }
       }
-      if (ok) {
-        const int cid = g.cell_offset + (cc[0] * g.nc[1] + cc[1]) * g.nc[2] + cc[2];
-        start = (int)cell_start[cid];
-        cnt = (int)(cell_start[cid + 1] - cell_start[cid]);
+      sw[2] = s2_lo + o2;
+      const int c_lo = max(lo2 - sw[2] * g.nc[2], 0), c_hi = min(hi2 - sw[2] * g.nc[2], g.nc[2] - 1);
+      if (ok && c_lo <= c_hi) {
+        const int64_t cid = g.cell_offset + (int64_t)(cc[0] * g.nc[1] + cc[1]) * g.nc[2];
+        start = (int)cell_start[cid + c_lo];
+        cnt = (int)cell_start[cid + c_hi + 1] - start;
         swp = pack_shift(sw[0], sw[1], sw[2]);
       }
     }
     const int incl = wave_incl_scan(cnt);
     const int total = __shfl(incl, 63, 64);
     s_excl[w][l] = incl - cnt;
-    s_start[w][l] = start;
+    s_start[w][l] = start - (incl - cnt);
     s_sw[w][l] = swp;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // a lane's candidate: last run k with excl[k] <= c; the next step's
+    // candidate is loaded before this one is tested
+    auto fetch = [&](int c, CellAtom& a, int4& img, int& sw) {
+      int lo = 0;
+#pragma unroll
+      for (int h = 32; h > 0; h >>= 1)
+        if (s_excl[w][lo + h] <= c) lo += h;
+      const int slot = s_start[w][lo] + c;
+      a = cell_atoms[slot];
+      img = cell_img[slot];
+      sw = s_sw[w][lo];
+    };
+    CellAtom na;
+    int4 nimg;
+    int nsw = 0;
+    if (l < total) fetch(l, na, nimg, nsw);
     for (int c0 = 0; c0 < total; c0 += 64) {
-      const int c = c0 + l;
+      const CellAtom ca = na;
+      const int4 jj = nimg;
+      const int csw = nsw;
+      if (c0 + 64 + l < total) fetch(c0 + 64 + l, na, nimg, nsw);
       bool acc = false;
       uint64_t key = 0;
-      if (c < total) {
-        // last offset slot k with excl[k] <= c
-        int lo = 0, hi = 63;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_excl[w][mid] <= c) lo = mid; else hi = mid - 1;
-        }
-        const int j = cell_atoms[s_start[w][lo] + (c - s_excl[w][lo])];
+      if (c0 + l < total) {
         int swx, swy, swz;
-        unpack_shift(s_sw[w][lo], swx, swy, swz);
-        const int4 jj = atom_img[j];
+        unpack_shift(csw, swx, swy, swz);
+        const int j = ca.j;
         const int sx = swx - jj.x + ii.x, sy = swy - jj.y + ii.y, sz = swz - jj.z + ii.z;
         if (!(j == i && sx == 0 && sy == 0 && sz == 0)) {
-          const double xj[3] = {(double)pos[3 * (int64_t)j], (double)pos[3 * (int64_t)j + 1],
-                                (double)pos[3 * (int64_t)j + 2]};
-          const double d2 = pair_d2(xi, xj, g.h, sx, sy, sz);
+          const double xj[3] = {(double)ca.x, (double)ca.y, (double)ca.z};
+          const double d2 = (sx | sy | sz) == 0 ? pair_d2_home(xi, xj) : pair_d2(xi, xj, g.h, sx, sy, sz);
           if (d2 < rc2) {
             if (d2 == 0.0) {
               coincident = true;
@@ -332,8 +505,9 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
               if (sx < -127 || sx > 127 || sy < -127 || sy > 127 || sz < -127 || sz > 127) {
                 shift_range = true;
                 acc = false;
-              } else {
+              } else if (MODE == 1) {
                 key = pair_key(j, sx, sy, sz);
+                wide |= sx < -2 || sx > 1 || sy < -2 || sy > 1 || sz < -2 || sz > 1;
               }
             }
           }
@@ -343,10 +517,14 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
         count += acc ? 1 : 0;
       } else {
         const uint64_t bal = __ballot(acc);
-        const int pre = __popcll(bal & ((1ull << l) - 1ull));
-        if (acc) {
-          const int slot = base + pre;
-          if (slot < GMNN_MAX_ROW) s_keys[w][slot] = key; else overflow = true;
+        const int slot = base + __popcll(bal & ((1ull << l) - 1ull));
+        // (a row past the limit was truncated by the count pass)
+        if (acc && slot < n) {
+          if (in_lds) s_keys[w][slot] = key;
+          else {
+            out_j[r0 + slot] = (int)(key >> 24);
+            out_shift[r0 + slot] = (int)(key & 0xffffff);
+          }
         }
         base += __popcll(bal);
       }
@@ -365,24 +543,101 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
     }
     return;
   }
-  if (overflow) raise_flag(status, GMNN_FLAG_ROW_TOO_LONG);
+  auto put = [&](uint64_t k, int rank) {
+    out_j[r0 + rank] = (int)(k >> 24);
+    out_shift[r0 + rank] = pack_shift((int)((k >> 16) & 0xff) - 128, (int)((k >> 8) & 0xff) - 128,
+                                      (int)(k & 0xff) - 128);
+  };
+  // rank sort (keys are unique inside a row)
+  if (!in_lds) {
+    // a long row: its keys back from the output arrays, all of a lane's in
+    // registers before the first one is overwritten
+    __threadfence_block();
+    constexpr int Q = GMNN_MAX_ROW / 64;
+    uint64_t k[Q];
+    int rank[Q];
+    auto at = [&](int e) {
+      return ((uint64_t)(uint32_t)__builtin_nontemporal_load(out_j + r0 + e) << 24) |
+             (uint32_t)__builtin_nontemporal_load(out_shift + r0 + e);
+    };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      k[q] = l + 64 * q < n ? at(l + 64 * q) : 0;
+      rank[q] = 0;
+    }
+    for (int e = 0; e < n; ++e) {
+      const uint64_t x = at(e);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) rank[q] += x < k[q] ? 1 : 0;
+    }
+    __threadfence_block();
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (l + 64 * q < n) put(k[q], rank[q]);
+    return;
+  }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int n = base < GMNN_MAX_ROW ? base : GMNN_MAX_ROW;
-  const int64_t r0 = row_ptr[i];
-  // rank sort (keys are unique inside a row)
+  if (__ballot(wide) == 0ull && n_atoms < (1 << 25)) {
+    // images within [-2, 1] and fewer than 2^25 atoms: the order is that of
+    // 32-bit keys (j, and two bits per image component), half the work per
+    // comparison; four keys a read, the row padded with the largest
+    uint32_t* s32 = (uint32_t*)s_keys[w];
+    uint64_t k[kRowKeys / 64];
+    uint32_t k32[kRowKeys / 64];
+#pragma unroll
+    for (int q = 0; q < kRowKeys / 64; ++q)
+      if (l + 64 * q < n) k[q] = s_keys[w][l + 64 * q];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < kRowKeys / 64; ++q) {
+      const int e = l + 64 * q;
+      if (64 * q >= n + 3) break;
+      const uint64_t x = k[q];
+      k32[q] = ((uint32_t)(x >> 24) << 6) | ((uint32_t)((x >> 16) & 0xff) - 126) << 4 |
+               ((uint32_t)((x >> 8) & 0xff) - 126) << 2 | ((uint32_t)(x & 0xff) - 126);
+      if (e >= n) k32[q] = 0xffffffffu;
+      s32[e] = k32[q];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    auto ranks = [&](auto QN) {
+      constexpr int Q = decltype(QN)::value;
+      int rank[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) rank[q] = 0;
+      for (int e = 0; e < n; e += 4) {
+        const uint4 x = *(const uint4*)(s32 + e);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          rank[q] += (x.x < k32[q] ? 1 : 0) + (x.y < k32[q] ? 1 : 0) + (x.z < k32[q] ? 1 : 0) + (x.w < k32[q] ? 1 : 0);
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (l + 64 * q < n) put(k[q], rank[q]);
+    };
+    if (n <= 64) ranks(std::integral_constant<int, 1>());
+    else if (n <= 128) ranks(std::integral_constant<int, 2>());
+    else if (n <= 256) ranks(std::integral_constant<int, 4>());
+    else ranks(std::integral_constant<int, kRowKeys / 64>());
+    return;
+  }
   for (int e = l; e < n; e += 64) {
     const uint64_t k = s_keys[w][e];
     int rank = 0;
     for (int q = 0; q < n; ++q) rank += (s_keys[w][q] < k) ? 1 : 0;
-    const int j = (int)(k >> 24);
-    const int sx = (int)((k >> 16) & 0xff) - 128, sy = (int)((k >> 8) & 0xff) - 128, sz = (int)(k & 0xff) - 128;
-    out_j[r0 + rank] = j;
-    out_shift[r0 + rank] = pack_shift(sx, sy, sz);
+    put(k, rank);
   }
 }
 
+struct __attribute__((packed, aligned(4))) Int4u {
+  int x, y, z, w;
+};
+struct __attribute__((packed, aligned(8))) Ptr2 {
+  int64_t x, y;
+};
 __global__ void __launch_bounds__(64 * kRowsWaves) nl_reverse(int n_atoms, const int64_t* __restrict__ row_ptr,
                                                              const int32_t* __restrict__ nj,
                                                              const int32_t* __restrict__ nshift,
@@ -396,20 +651,54 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_reverse(int n_atoms, const
   if (!*go) return;
   if (*n_pairs > capacity) return;
   const int64_t p0 = row_ptr[i], p1 = row_ptr[i + 1];
+  const int ni = (int)(p1 - p0);
   for (int64_t p = p0 + l; p < p1; p += 64) {
     const int j = nj[p];
-    int sx, sy, sz;
-    unpack_shift(nshift[p], sx, sy, sz);
-    const uint64_t want = pair_key(i, -sx, -sy, -sz);
-    int64_t lo = row_ptr[j], hi = row_ptr[j + 1] - 1;
-    int64_t found = -1;
-    while (lo <= hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      int ax, ay, az;
-      unpack_shift(nshift[mid], ax, ay, az);
-      const uint64_t k = pair_key(nj[mid], ax, ay, az);
-      if (k == want) { found = mid; break; }
-      if (k < want) lo = mid + 1; else hi = mid - 1;
+    const Ptr2 rp = *(const Ptr2*)(row_ptr + j);
+    const int64_t r0 = rp.x;
+    const int n = (int)(rp.y - r0);
+    const int32_t* __restrict__ row = nj + r0;
+    // first slot of row j that holds atom i or a later one.  In a spatially
+    // ordered system the rows mirror each other (j early in row i puts i late
+    // in row j), so eight slots around the mirrored place (two 16-byte loads)
+    // are looked at first; where they miss, the rest is halved as usual
+    int lo = 0, hi = n;
+    bool sole = false;  // the window shows that no second image of i follows
+    if (n >= 8) {
+      const int guess = n - 1 - (int)((float)(int)(p - p0) * (float)n / (float)ni);
+      const int g0 = max(0, min(guess - 3, n - 8));
+      const Int4u a = *(const Int4u*)(row + g0), b = *(const Int4u*)(row + g0 + 4);
+      const int v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+      int below = 0, equal = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        below += v[e] < i ? 1 : 0;
+        equal += v[e] == i ? 1 : 0;
+      }
+      if (below == 8) {
+        lo = g0 + 8;
+      } else if (below > 0 || g0 == 0) {
+        lo = hi = g0 + below;
+        sole = equal == 1 && below < 7;
+      } else {
+        hi = g0;
+      }
+    }
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (row[mid] < i) lo = mid + 1; else hi = mid;
+    }
+    int64_t found = sole ? r0 + lo : -1;
+    if (!sole) {
+      // several images of i: the one with the opposite shift
+      int sx, sy, sz;
+      unpack_shift(nshift[p], sx, sy, sz);
+      const int32_t want = pack_shift(-sx, -sy, -sz);
+      for (int e = lo; e < n && row[e] == i; ++e)
+        if (nshift[r0 + e] == want) {
+          found = r0 + e;
+          break;
+        }
     }
     if (found < 0) {
       raise_flag(status, GMNN_FLAG_ROW_TOO_LONG);
@@ -422,8 +711,8 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_reverse(int n_atoms, const
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-static int host_cells_bound(const double* h, const uint8_t* pbc, double rbin) {
-  (void)pbc;
+// at least the cells the device's grid has, whichever way its roundings fall
+static int host_cells_bound(const double* h, double rbin, int64_t n_atoms) {
   const double a[3][3] = {{h[0], h[1], h[2]}, {h[3], h[4], h[5]}, {h[6], h[7], h[8]}};
   double cr[3][3];
   for (int k = 0; k < 3; ++k) {
@@ -435,21 +724,25 @@ static int host_cells_bound(const double* h, const uint8_t* pbc, double rbin) {
   }
   const double det = a[0][0] * cr[0][0] + a[0][1] * cr[0][1] + a[0][2] * cr[0][2];
   const double vol = fabs(det);
-  long long cells = 1;
+  long long fewest = 1, fine = 1, coarse = 1;
   for (int k = 0; k < 3; ++k) {
     const double nrm = sqrt(cr[k][0] * cr[k][0] + cr[k][1] * cr[k][1] + cr[k][2] * cr[k][2]);
-    double fnc = floor(vol / nrm / rbin);
-    int nc = (fnc < 1.0) ? 1 : (fnc > (double)kMaxCellsPerAxis ? kMaxCellsPerAxis : (int)fnc);
+    const int nf = cells_on_axis(kCellsPerRadius * (vol / nrm) / rbin);
+    fewest *= std::max(nf - 1, 1);
     // +1 per axis absorbs any rounding difference between host and device
-    cells *= (nc + 1);
+    fine *= nf + 1;
+    coarse *= cells_on_axis(vol / nrm / rbin) + 1;
   }
+  const long long cells = fewest <= max_fine_cells(n_atoms) ? std::max(fine, coarse) : coarse;
   return (int)(cells > (1LL << 30) ? (1LL << 30) : cells);
 }
 
 NlLayout nl_layout(const gmnn_system* sys, double rbin) {
   NlLayout L;
   int64_t cells = 0;
-  for (int b = 0; b < sys->n_structs; ++b) cells += host_cells_bound(sys->cell_host + 9 * b, sys->pbc_host + 3 * b, rbin);
+  for (int b = 0; b < sys->n_structs; ++b)
+    cells += host_cells_bound(sys->cell_host + 9 * (int64_t)b, rbin,
+                              sys->atom_ptr_host[b + 1] - sys->atom_ptr_host[b]);
   L.cell_capacity = cells;
   const int64_t N = sys->n_atoms;
   const int64_t B = sys->n_structs;
@@ -466,7 +759,9 @@ NlLayout nl_layout(const gmnn_system* sys, double rbin) {
   L.off_cells_total = take(8 * 2);
   L.off_atom_cell = take(4 * (size_t)N);
   L.off_atom_img = take(16 * (size_t)N);
-  L.off_cell_atoms = take(4 * (size_t)N);
+  L.off_cell_atoms = take(sizeof(CellAtom) * (size_t)N);
+  L.off_cell_img = take(16 * (size_t)N);
+  L.off_scan = take(4 * (size_t)((std::max<int64_t>(cells, N) + kScanTile - 1) / kScanTile));
   L.off_row_count = take(4 * (size_t)N + 4);
   L.off_go = take(4);
   L.bytes = off;
@@ -487,7 +782,9 @@ gmnn_status nl_build(const gmnn_system* sys, float cutoff, float skin, gmnn_neig
   int64_t* cells_total = (int64_t*)(w + L.off_cells_total);
   int32_t* atom_cell = (int32_t*)(w + L.off_atom_cell);
   int4* atom_img = (int4*)(w + L.off_atom_img);
-  int32_t* cell_atoms = (int32_t*)(w + L.off_cell_atoms);
+  CellAtom* cell_atoms = (CellAtom*)(w + L.off_cell_atoms);
+  int4* cell_img = (int4*)(w + L.off_cell_img);
+  int32_t* part = (int32_t*)(w + L.off_scan);
   int32_t* row_count = (int32_t*)(w + L.off_row_count);
   int* go = (int*)(w + L.off_go);
   const int N = sys->n_atoms;
@@ -496,7 +793,7 @@ gmnn_status nl_build(const gmnn_system* sys, float cutoff, float skin, gmnn_neig
   const double rc2 = (double)rlf * (double)rlf;
   nl->cutoff = rlf;
 
-  hipLaunchKernelGGL(nl_setup, dim3(1), dim3(1024), 0, stream, sys->cell, sys->pbc, B, rbin, grids,
+  hipLaunchKernelGGL(nl_setup, dim3(1), dim3(1024), 0, stream, sys->cell, sys->pbc, sys->atom_ptr, B, rbin, grids,
                      L.cell_capacity, cell_count, cell_fill, cells_total, nl->status, disp_bits, thresh2, go);
   const int tb = 256;
   const int nb_atoms = (N + tb - 1) / tb;
@@ -505,26 +802,34 @@ gmnn_status nl_build(const gmnn_system* sys, float cutoff, float skin, gmnn_neig
                        cells_total, L.cell_capacity, nl->atom_struct, atom_cell, atom_img, cell_count, nl->status, go,
                        ref_pos);
   }
-  hipLaunchKernelGGL(scan_i32, dim3(1), dim3(1024), 0, stream, cell_count, cell_start, cells_total,
-                     (int64_t)L.cell_capacity, (int64_t*)nullptr, (const int*)go, (int64_t)-1);
+  auto scan = [&](const int32_t* in, int64_t* out, const int64_t* n_dev, int64_t n, int64_t* total, int64_t cap) {
+    if (n <= kScanOne) {
+      hipLaunchKernelGGL(scan_one, dim3(1), dim3(kScanThreads), 0, stream, in, out, n_dev, n, total, (const int*)go,
+                         cap);
+      return;
+    }
+    const dim3 grid((unsigned)((n + kScanTile - 1) / kScanTile));
+    hipLaunchKernelGGL(scan_sums, grid, dim3(kScanThreads), 0, stream, in, n_dev, n, part, (const int*)go);
+    hipLaunchKernelGGL(scan_write, grid, dim3(kScanThreads), 0, stream, in, out, n_dev, n, (const int32_t*)part, total,
+                       (const int*)go, cap);
+  };
+  scan(cell_count, cell_start, cells_total, L.cell_capacity, nullptr, -1);
   if (N > 0) {
-    hipLaunchKernelGGL(nl_cellfill, dim3(nb_atoms), dim3(tb), 0, stream, N, atom_cell, cell_start, cells_total,
-                       L.cell_capacity, cell_fill, cell_atoms, (const int*)go);
+    hipLaunchKernelGGL(nl_cellfill, dim3(nb_atoms), dim3(tb), 0, stream, N, sys->pos, atom_cell, atom_img, cell_start,
+                       cells_total, L.cell_capacity, cell_fill, cell_atoms, cell_img, (const int*)go);
     const int nb_rows = (N + kRowsWaves - 1) / kRowsWaves;
     hipLaunchKernelGGL(nl_rows<0>, dim3(nb_rows), dim3(64 * kRowsWaves), 0, stream, sys->pos, N, grids,
-                       nl->atom_struct, atom_img, cell_start, cell_atoms, cells_total, L.cell_capacity, rc2, row_count,
+                       nl->atom_struct, atom_img, cell_start, cell_atoms, cell_img, cells_total, L.cell_capacity, rc2, row_count,
                        (const int64_t*)nullptr, (const int64_t*)nullptr, nl->capacity, (int32_t*)nullptr,
                        (int32_t*)nullptr, nl->status, (const int*)go);
-    hipLaunchKernelGGL(scan_i32, dim3(1), dim3(1024), 0, stream, row_count, nl->row_ptr, (const int64_t*)nullptr,
-                       (int64_t)N, nl->n_pairs, (const int*)go, (int64_t)nl->capacity);
+    scan(row_count, nl->row_ptr, nullptr, N, nl->n_pairs, nl->capacity);
     hipLaunchKernelGGL(nl_rows<1>, dim3(nb_rows), dim3(64 * kRowsWaves), 0, stream, sys->pos, N, grids,
-                       nl->atom_struct, atom_img, cell_start, cell_atoms, cells_total, L.cell_capacity, rc2, row_count,
+                       nl->atom_struct, atom_img, cell_start, cell_atoms, cell_img, cells_total, L.cell_capacity, rc2, row_count,
                        nl->row_ptr, nl->n_pairs, nl->capacity, nl->j, nl->shift, nl->status, (const int*)go);
     hipLaunchKernelGGL(nl_reverse, dim3(nb_rows), dim3(64 * kRowsWaves), 0, stream, N, nl->row_ptr, nl->j, nl->shift,
                        nl->n_pairs, nl->capacity, nl->rev, nl->status, (const int*)go);
   } else {
-    hipLaunchKernelGGL(scan_i32, dim3(1), dim3(1024), 0, stream, row_count, nl->row_ptr, (const int64_t*)nullptr,
-                       (int64_t)0, nl->n_pairs, (const int*)go, (int64_t)nl->capacity);
+    scan(row_count, nl->row_ptr, nullptr, 0, nl->n_pairs, nl->capacity);
   }
   return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
 }
