@@ -58,7 +58,7 @@ typedef int32_t gmnn_status;
 #define GMNN_MAX_ROW 1024          /* neighbours per atom handled by the list build */
 
 /* flags of gmnn_energy_forces / gmnn_backward */
-#define GMNN_PREC_FP32 0u          /* network products in FP32 (MFMA f32) */
+#define GMNN_PREC_FP32 0u          /* network products in FP32 (exact three-part operands on BF16 MFMA) */
 #define GMNN_PREC_BF16 1u          /* network products in BF16 on MFMA, FP32 accumulate */
 #define GMNN_WANT_STRESS 2u        /* fill outputs->stress */
 #define GMNN_WANT_FORCE_VAR 4u     /* fill outputs->force_var (one backward per head) */
@@ -263,16 +263,21 @@ gmnn_status gmnn_energy_forces_noalloc(const gmnn_model* m, const gmnn_system* s
  *   FUSED  one tile kernel computes the moments, the readout and the pair
  *          backward of a tile of tile_atoms atoms (16, or 8: twice the
  *          blocks, each with half the pair and invariant work and the same
- *          network products), then one kernel gathers the forces and sums
- *          per structure (latency-bound small systems; needs <= 8 species,
- *          no force variance, every structure <= 16384 atoms);
+ *          network products; in FP32, 8-atom tiles that would number more
+ *          than the compute units run as 16-atom ones), then one kernel
+ *          gathers the forces and sums per structure (latency-bound small
+ *          systems; needs <= 8 species, no force variance, every structure
+ *          <= 16384 atoms);
  *   SPLIT  pair moments -> readout -> pair backward -> gather/sums, with the
  *          readout (invariants, network, their backward) either
- *            TILE    one kernel per 16 atoms, or
- *            STREAM  three kernels: invariants of 16 atoms -> network on
- *                    row tiles of 32 to 64 atoms -> invariant backward; G
- *                    and dE/dG pass through the workspace (the head-mean
- *                    backward only: not with GMNN_WANT_FORCE_VAR).
+ *            TILE    invariants and network in one kernel per 16 atoms,
+ *                    then the invariant backward (systems that need several
+ *                    rounds of such tiles run STREAM's kernels: the results
+ *                    are the same bit for bit), or
+ *            STREAM  three kernels: invariants -> network on row tiles of 32
+ *                    to 64 atoms -> invariant backward; G and dE/dG pass
+ *                    through the workspace (the head-mean backward only: not
+ *                    with GMNN_WANT_FORCE_VAR).
  * lanes_per_atom (8, 16, 32 or 64) is the number of lanes that share one atom's
  * neighbour row in the pair and gather kernels.  Zero fields mean "built-in
  * choice": FUSED with 64 lanes below 16384 atoms where it is allowed (else

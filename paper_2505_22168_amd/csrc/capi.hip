@@ -98,6 +98,26 @@ static bool fused_allowed(const gmnn_model* m, const gmnn_system* sys, uint32_t 
          largest_structure(sys) <= kFusedMaxAtoms;
 }
 
+// The TILE readout's work (invariants and network) on the streamed kernels
+// instead of 16-atom tiles: the results are the same bit for bit, and the
+// taller network tiles win once the 16-atom ones need a second round of the
+// compute units at 2x512 (6000 atoms, FP32 and BF16: 151 and 107 us against
+// 166 and 117), a third at smaller widths (2x256 at 10,600 atoms: 130 and
+// 108 us against 154 and 115; at 6000 atoms 114 and 90 against 110 and 87).
+static bool tall_tiles(const gmnn_model* m, int n_atoms) {
+  const int rounds = (n_atoms + 16 * kComputeUnits - 1) / (16 * kComputeUnits);
+  return rounds > (packed_layout(m->hidden1, m->hidden2, m->n_heads).HP1 >= 512 ? 1 : 2);
+}
+
+// Atoms per fused tile at launch: a second round of 8-atom tiles takes longer
+// than one of 16-atom tiles (FP32 2x256, 3000 atoms: 90.5 against 51.3 us per
+// evaluation; 2000 atoms, one round: 51.2 against 49.6).  BF16 keeps the
+// plan's size: the two sum an atom's pairs in different orders, which the
+// rounding of the backward operands to BF16 would amplify to 1e-4 in the forces.
+static int launch_tile_atoms(int ta, bool bf16, int n_atoms) {
+  return ta == 8 && !bf16 && (n_atoms + 7) / 8 > kComputeUnits ? 16 : ta;
+}
+
 // fills the AUTO fields of `in` (built-in heuristic: the fused schedule for
 // systems of fewer than kFusedMaxAtoms atoms, 64 lanes per atom there and for
 // split systems below kWideLanesMaxAtoms, 16 beyond, 8-atom fused tiles below
@@ -571,6 +591,8 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   float* head_c = (float*)(W + L.head_c);
   float* head_w = (float*)(W + L.head_w);
   const bool fused = P.fused;
+  const int ta = launch_tile_atoms(P.ta, bf16, N);
+  const bool stream_readout = P.stream || (!fused && !var && tall_tiles(m, N));
   const int lpa = P.lpa;
   // the fused schedule sums each structure in one block from the tiles'
   // records; the split one from per-atom values in chunks of kReduceChunk
@@ -581,7 +603,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   if (N > 0) {
     if (fused) {
       mark(0);
-      st = launch_tile(true, false, P.ta, dm, ds, bf16, nullptr, atomic_e, nullptr, gpair, virial, gstride, tilerec, s);
+      st = launch_tile(true, false, ta, dm, ds, bf16, nullptr, atomic_e, nullptr, gpair, virial, gstride, tilerec, s);
       if (st != GMNN_OK) return st;
       for (int k = 1; k < 10; ++k) mark(k);
     } else {
@@ -602,7 +624,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
         // structure; then the head weights c_m and the weighted W3 vectors
         DevModel da = dm;
         da.fwd_only = 1;
-        if (P.stream)
+        if (stream_readout)
           st = launch_stream(da, ds, bf16, psi, W + L.g, (float*)(W + L.dg), atomic_e, psibar, s, nullptr, 3);
         else
           st = launch_tile(false, var, 16, da, ds, bf16, psi, atomic_e, psibar, nullptr, nullptr, gstride, nullptr, s);
@@ -627,7 +649,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
         // the pair counters of the chunked sums were used by pass 1's
         // reduction, which leaves them cleared
       }
-      if (P.stream) {
+      if (stream_readout) {
         st = launch_stream(db, ds, bf16, psi, W + L.g, (float*)(W + L.dg), atomic_e, psibar, s, ev ? ev + 2 : nullptr,
                            phases);
       } else {
@@ -665,7 +687,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
 #define FINISH(LPA, VAR)                                                                                       \
   hipLaunchKernelGGL((finish<LPA, VAR>), fgrid, dim3(kPairThreads), 0, s, m->n_heads, ds, gpair, atomic_e, virial, \
                      want_stress, nbg, gstride, nchunk, partial, counters, out->forces, out->force_var, out->energy, \
-                     out->energy_var, out->energy_mean, out->stress, fused ? tilerec : nullptr, fused ? P.ta : 0, \
+                     out->energy_var, out->energy_mean, out->stress, fused ? tilerec : nullptr, fused ? ta : 0, \
                      (udd && var) ? head_c : nullptr, var ? out->forces_heads : nullptr)
   if (lpa == 64) {
     if (var) FINISH(64, true);
@@ -874,7 +896,7 @@ gmnn_status gmnn_last_layer_features(const gmnn_model* m, const gmnn_system* sys
     else if (lpa == 16) MOMENTS(16);
     else MOMENTS(8);
 #undef MOMENTS
-    if (P.stream)
+    if (P.stream || tall_tiles(m, N))
       st = launch_stream(dm, ds, bf16, psi, W + L.g, (float*)(W + L.dg), atomic_e, psibar, s, nullptr, 3);
     else
       st = launch_tile(false, false, 16, dm, ds, bf16, psi, atomic_e, psibar, nullptr, nullptr, nl->capacity, nullptr,
