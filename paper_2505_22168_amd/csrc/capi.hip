@@ -40,14 +40,14 @@ size_t tile_lds_bytes(int hp, bool bf16, bool fused, bool perhead);
 __global__ void ll_features(DevModel m, DevSystem sys, int H2, const float* h2, double* phi);
 bool train_supported(const DevModel& m);
 size_t train_workspace_bytes(int n_atoms, int HP, int nsp);
-size_t heads_backward_extra_bytes(const DevModel& m, int H1, int H2, int n_structs);
+size_t heads_backward_extra_bytes(const DevModel& m, int n_structs);
 gmnn_status train_backward_heads(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                                  int n_structs, const double* dE, const float* dF, gmnn_param_grads* g, void* ws,
                                  size_t train_bytes, char* head_ws, size_t head_bytes, float* dL_dpos, float* gpos,
                                  hipStream_t s);
 gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                            const double* ebar, const float* lambda, gmnn_param_grads* g, void* ws, size_t ws_bytes,
-                           float* dL_dpos, float* gpos, bool accumulate_pos, hipStream_t s);
+                           float* dL_dpos, float* gpos, int head, int heads, hipStream_t s);
 
 constexpr int kPairThreads = 256;
 // below this many atoms the built-in plan takes the fused (latency) schedule,
@@ -454,7 +454,7 @@ static BwLayout bw_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   L.gpos = L.train;
   L.heads = L.gpos + al(12 * (size_t)std::max<int64_t>(nl->capacity, 0));
   L.bytes = L.heads + ((flags & GMNN_BACKWARD_PER_HEAD)
-                           ? heads_backward_extra_bytes(dev_model(m), m->hidden1, m->hidden2, sys->n_structs)
+                           ? heads_backward_extra_bytes(dev_model(m), sys->n_structs)
                            : 0);
   return L;
 }
@@ -936,7 +936,7 @@ gmnn_status gmnn_backward(const gmnn_model* m, const gmnn_system* sys, const gmn
                               W, L.train, W + L.heads, L.bytes - L.heads, dL_dpos, gpos, s);
   else
     st = train_backward(dm, ds, bf16, lanes16, m->hidden1, m->hidden2, dL_dE, dL_dF, grads, W, L.train, dL_dpos,
-                        gpos, false, s);
+                        gpos, -1, m->n_heads, s);
   if (st != GMNN_OK) return st;
   if ((flags & GMNN_SYNC) && hipStreamSynchronize(s) != hipSuccess) return GMNN_ERR_HIP;
   return GMNN_OK;

@@ -300,7 +300,7 @@ __device__ inline void contract_forward_b(const float* __restrict__ P, const flo
 // primal passes.  Phase A writes the tangent intermediates Id (stride IDS:
 // T7, V8, M5, v6 at the primal offsets) and the tangents of families 1-4;
 // phase B the tangents of families 5-8 from the primal intermediates I
-// (stride IS) and Id.  Gd is FP32 with row stride ldg; the padding features
+// (stride ISTR) and Id.  Gd is FP32 with row stride ldg; the padding features
 // are zeroed.
 #define GM_D1(a, s, i) Pd[(a) * PS + (s) * kFull + 1 + (i)]
 #define GM_D2(a, s, ij) Pd[(a) * PS + (s) * kFull + 4 + (ij)]
@@ -433,11 +433,10 @@ __device__ inline void contract_forward_a_dual(const float* __restrict__ P, cons
   }
 }
 
-template <int TM, int NT, int IDS>
+template <int TM, int NT, int IDS, int ISTR = IS>
 __device__ inline void contract_forward_b_dual(const float* __restrict__ P, const float* __restrict__ Pd,
                                                const float* __restrict__ I, const float* __restrict__ Id,
                                                float* __restrict__ Gd, int ldg, const Tables& tb) {
-  constexpr int ISTR = IS;
   constexpr int np = TM * 15, ns = TM * kS;
   for (int t = threadIdx.x; t < np + ns; t += NT) {
     if (t < np) {

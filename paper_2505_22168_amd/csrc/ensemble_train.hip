@@ -8,10 +8,8 @@
 //   loss_finish     the two terms summed in block order (FP64)
 //   adam_update     one Adam step over all parameter arrays, one learning
 //                   rate per parameter group
-//   head_view / head_accumulate
-//                   per-head double backward: the head's W3 column as a
-//                   one-head model, and the head's gradients added into the
-//                   result in head order
+//   head_views      per-head double backward: every head's W3 column as a
+//                   one-head model (train_sums adds the heads' gradients)
 //
 // Derivatives of one term l(xbar, s2) with u = xbar - x_ref, s2 = variance
 // + floor, s = sqrt(s2), z = |u| / s:
@@ -185,112 +183,50 @@ __global__ void __launch_bounds__(256) adam_update(AdamArgs a) {
 // ---------------------------------------------------------------------------
 // per-head double backward
 // ---------------------------------------------------------------------------
-// head h of the packed W3 [HP2][M] as a one-head vector [HP2], and column h
-// of dL/dE [B][M] as the one-head upstream gradient [B]
-__global__ void head_view(const float* __restrict__ w3, int HP2, int M, int h, const double* __restrict__ dE, int B,
-                          float* __restrict__ w3h, double* __restrict__ dEh) {
+// every head h of the packed W3 [HP2][M] as a one-head vector w3h[h][HP2], and
+// column h of dL/dE [B][M] as the one-head upstream gradient dEh[h][B]
+__global__ void head_views(const float* __restrict__ w3, int HP2, int M, const double* __restrict__ dE, int B,
+                           float* __restrict__ w3h, double* __restrict__ dEh) {
+  const int h = blockIdx.y;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < HP2) w3h[t] = w3[(int64_t)t * M + h];
-  if (t < B) dEh[t] = dE[(int64_t)t * M + h];
-}
-
-struct GradSegs {
-  const float* src[9];
-  float* dst[9];
-  int64_t n[9];
-};
-
-// head h's gradients into the result: the shared arrays (all but W3 and b3)
-// copied for h = 0 and added for h > 0, so the sum runs in head order; W3's
-// column h and b3[h] take the head's own gradient
-__global__ void __launch_bounds__(256) head_accumulate(GradSegs g, int h, int M) {
-  const int a = blockIdx.y;
-  const int64_t n = g.n[a];
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
-    const float v = g.src[a][k];
-    if (a == 5)
-      g.dst[a][k * M + h] = v;  // W3 [H2][M]
-    else if (a == 6)
-      g.dst[a][h] = v;  // b3 [M]
-    else
-      g.dst[a][k] = h == 0 ? v : g.dst[a][k] + v;
-  }
+  if (t < HP2) w3h[(int64_t)h * HP2 + t] = w3[(int64_t)t * M + h];
+  if (t < B) dEh[(int64_t)h * B + t] = dE[(int64_t)t * M + h];
 }
 
 gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                            const double* ebar, const float* lambda, gmnn_param_grads* g, void* ws, size_t ws_bytes,
-                           float* dL_dpos, float* gpos, bool accumulate_pos, hipStream_t s);
+                           float* dL_dpos, float* gpos, int head, int heads, hipStream_t s);
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// parameter counts in gmnn_param_grads order, W3 and b3 for one head
-static void head_grad_sizes(const DevModel& m, int H1, int H2, int64_t n[9]) {
-  n[0] = (int64_t)m.n_species * m.n_species * kS * m.K;
-  n[1] = (int64_t)kF * H1;
-  n[2] = H1;
-  n[3] = (int64_t)H1 * H2;
-  n[4] = H2;
-  n[5] = H2;
-  n[6] = 1;
-  n[7] = m.n_species;
-  n[8] = m.n_species;
-}
-
-size_t heads_backward_extra_bytes(const DevModel& m, int H1, int H2, int n_structs) {
-  int64_t n[9];
-  head_grad_sizes(m, H1, H2, n);
-  size_t b = 0;
-  for (int k = 0; k < 9; ++k) b += align256(4 * (size_t)n[k]);
-  return b + align256(4 * (size_t)m.HP2) + align256(8 * (size_t)n_structs);
+size_t heads_backward_extra_bytes(const DevModel& m, int n_structs) {
+  return align256(4 * (size_t)m.HP2 * m.M) + align256(8 * (size_t)n_structs * m.M);
 }
 
 // one double backward per head (gmnn_backward with GMNN_BACKWARD_PER_HEAD):
 // head h sees the model with W3[:, h], b3[h] alone, dL/dE[:, h] and
-// dL/dF[h]; head_ws holds the head's gradients, its W3 column and its dL/dE
-// column.  The positions' gradient (dL_dpos, optional) is summed over the
-// heads in head order.
+// dL/dF[h]; head_ws holds the heads' W3 and dL/dE columns.  The gradients
+// (and the positions', optional) are summed over the heads in head order.
 gmnn_status train_backward_heads(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                                  int n_structs, const double* dE, const float* dF, gmnn_param_grads* g, void* ws,
                                  size_t train_bytes, char* head_ws, size_t head_bytes, float* dL_dpos, float* gpos,
                                  hipStream_t s) {
-  if (head_bytes < heads_backward_extra_bytes(m, H1, H2, n_structs)) return GMNN_ERR_WORKSPACE;
-  char* X = head_ws;
-  int64_t n[9];
-  head_grad_sizes(m, H1, H2, n);
-  float* tmp[9];
-  for (int k = 0; k < 9; ++k) {
-    tmp[k] = (float*)X;
-    X += align256(4 * (size_t)n[k]);
-  }
-  float* w3h = (float*)X;
-  X += align256(4 * (size_t)m.HP2);
-  double* dEh = (double*)X;
-  gmnn_param_grads hg = {tmp[0], tmp[1], tmp[2], tmp[3], tmp[4], tmp[5], tmp[6], tmp[7], tmp[8]};
-  GradSegs segs;
-  float* dst[9] = {g->beta, g->W1, g->b1, g->W2, g->b2, g->W3, g->b3, g->scale, g->shift};
-  int64_t nmax = 0;
-  for (int k = 0; k < 9; ++k) {
-    segs.src[k] = tmp[k];
-    segs.dst[k] = dst[k];
-    segs.n[k] = n[k];
-    nmax = n[k] > nmax ? n[k] : nmax;
-  }
+  if (head_bytes < heads_backward_extra_bytes(m, n_structs)) return GMNN_ERR_WORKSPACE;
   const int M = m.M;
+  float* w3h = (float*)head_ws;
+  double* dEh = (double*)(head_ws + align256(4 * (size_t)m.HP2 * M));
   const int64_t n3 = 3 * (int64_t)sys.n_atoms;
   const int nv = m.HP2 > n_structs ? m.HP2 : n_structs;
+  hipLaunchKernelGGL(head_views, dim3((nv + 255) / 256, M), dim3(256), 0, s, m.w3, m.HP2, M, dE, n_structs, w3h, dEh);
   for (int h = 0; h < M; ++h) {
-    hipLaunchKernelGGL(head_view, dim3((nv + 255) / 256), dim3(256), 0, s, m.w3, m.HP2, M, h, dE, n_structs, w3h,
-                       dEh);
     DevModel mh = m;
     mh.M = 1;
-    mh.w3 = w3h;
-    mh.w3bar = w3h;
+    mh.w3 = w3h + (int64_t)h * m.HP2;
+    mh.w3bar = mh.w3;
     mh.b3 = m.b3 + h;
-    const gmnn_status st =
-        train_backward(mh, sys, bf16, lanes16, H1, H2, dEh, dF + h * n3, &hg, ws, train_bytes, dL_dpos, gpos, h > 0, s);
+    const gmnn_status st = train_backward(mh, sys, bf16, lanes16, H1, H2, dEh + (int64_t)h * n_structs, dF + h * n3, g,
+                                          ws, train_bytes, dL_dpos, gpos, h, M, s);
     if (st != GMNN_OK) return st;
-    const int nb = (int)std::min<int64_t>((nmax + 255) / 256, 512);
-    hipLaunchKernelGGL(head_accumulate, dim3(nb, 9), dim3(256), 0, s, segs, h, M);
   }
   return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
 }

@@ -205,33 +205,6 @@ __device__ __forceinline__ void mma_ring(BRing<BF16, TPW, DEPTH>& r, const void*
   }
 }
 
-// BF16 product with the A tile kept in FP32 in LDS: the 8 values of each A
-// fragment are rounded to BF16 (nearest even) as they are loaded (the
-// training tile keeps its activations in FP32 for the parameter products).
-// The _ring form takes the ring already holding k-steps 0..PF-1 (filled ahead
-// with ring_fill), so its first fragments can arrive during earlier work.
-template <int TPW, int DEPTH>
-__device__ __forceinline__ void mma_bf16_a32_ring(BRing<true, TPW, DEPTH>& r, const float* __restrict__ A, int lda,
-                                                  int rb, const Weights& B, int K, int nb0, int nbs, int NB,
-                                                  floatx4 (&acc)[TPW]) {
-  constexpr int PF = DEPTH;
-  const int l = threadIdx.x & 63;
-  const int KB = K / 32;
-  const float* arow = A + (rb * 16 + (l & 15)) * lda + (l >> 4) * 8;
-  auto step = [&](int slot, int kb) {
-    const float4 lo = *(const float4*)(arow + kb * 32);
-    const float4 hi = *(const float4*)(arow + kb * 32 + 4);
-    bf16x8 a;
-    a[0] = (__bf16)lo.x; a[1] = (__bf16)lo.y; a[2] = (__bf16)lo.z; a[3] = (__bf16)lo.w;
-    a[4] = (__bf16)hi.x; a[5] = (__bf16)hi.y; a[6] = (__bf16)hi.z; a[7] = (__bf16)hi.w;
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      if (has_block(i, nb0, nbs, NB)) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
-    }
-  };
-  pipeline<PF>(KB, step, [&](int slot, int kb) { ring_load(r, slot, B, KB, kb, nb0, nbs, NB); });
-}
-
 // ---------------------------------------------------------------------------
 // Split-BF16 products (the network's forward products in BF16 mode).  Each
 // FP32 operand x is held as two bf16 parts, hi = bf16(x) and lo = bf16(x - hi)

@@ -10,15 +10,15 @@
 // the position perturbation lambda.  D is evaluated in forward (tangent)
 // mode and Phi differentiated in reverse mode:
 //   pair_tangent    Psidot_i = sum_p dPsi/dd_p . delta_p
-//   train_tile      per 8 atoms: invariants G and their tangent Gdot (in
-//                   dual numbers: the product rule on every contraction
-//                   family, exact since G is a polynomial); the network forward in
-//                   dual numbers with primal and tangent rows stacked into one
-//                   16-row MFMA tile; its reverse pass; the invariant
-//                   backward Psibar = J^T Gbar + (d/dPsi J Psidot)^T Gdotbar
-//                   (the backward map is quadratic in Psi, so the second
-//                   term is an exact central difference) and Psidotbar =
-//                   J^T Gdotbar.  Writes the rows the weight products need.
+//   train_features  invariants G and their tangent Gdot (in dual numbers: the
+//                   product rule on every contraction family, exact since G
+//                   is a polynomial), 6 atoms per block
+//   train_network   the network forward in dual numbers, a 16-row MFMA block
+//                   of primal rows next to one of tangent rows, and its
+//                   reverse pass; writes the rows the weight products need
+//   contract_back_dual  the invariant backward in dual numbers, one atom per
+//                   lane: Psidotbar = J^T Gdotbar and
+//                   Psibar = J^T Gbar + (d/dPsi J^T Gdotbar) Psidot
 //   pair_beta_grad  dPhi/dbeta per pair, reduced per (Z_i, Z_j) without
 //                   atomics on the result
 //   weight_grad     W1bar = [G;Gdot]^T [z1bar;z1dotbar],
@@ -28,21 +28,18 @@
 #include <algorithm>
 
 #include "common.h"
+#include "contract_lanes.h"
 #include "contraction.h"
-#include "mfma.h"
+#include "mfma_rows.h"
 #include "model.h"
 #include "pair_math.h"
 
 namespace gmnn {
 
-constexpr int kTrainThreads = 512;
+constexpr int kTrainThreads = 512;  // threads of a training network block
 constexpr int kTrainWaves = kTrainThreads / 64;
-constexpr int kTA = 8;  // atoms per training tile (16 MFMA rows: primal + tangent)
-// phase A of the invariant backward: each task's two output groups on two
-// threads when the tile has the threads (no result changes)
-constexpr int kTrainKSA = 2 * ((kTA * 30 + 63) / 64 * 64) <= kTrainThreads ? 2 : 1;
-// 8 atoms leave threads for both halves of every task of the invariants' first pass
-constexpr int kFwdSplit = 2 * ((kTA * 20 + 63) / 64 * 64) <= kTrainThreads ? 2 : 1;
+constexpr int kTfAtoms = 6;         // atoms and threads of a training invariant block
+constexpr int kTfThreads = 256;
 
 // directional derivative of every monomial at u along v
 __device__ inline void dmonomials(float x, float y, float z, float vx, float vy, float vz, float* d) {
@@ -125,341 +122,314 @@ __device__ inline void swish_d2(float z, float& s, float& d1, float& d2) {
   d2 = sg * (1.0f - sg) * (2.0f + z * (1.0f - 2.0f * sg));
 }
 
-// network products of the training tile: FP32 (three-part operands), or BF16
-// on the weights' high parts with the FP32 activation tile rounded on load:
-// one network product of the training tile (16 rows: primal + tangent) from
-// a ring filled ahead with the first k-steps of its weights
-template <bool BF16, int TPW, int DEPTH>
-__device__ __forceinline__ void train_mma(BRing<BF16, TPW, DEPTH>& ring, const float* A, int lda, const Weights& B,
-                                          int K, int nb0, int nbs, int NB, floatx4 (&acc)[TPW]) {
-  if constexpr (BF16) mma_bf16_a32_ring(ring, A, lda, 0, B, K, nb0, nbs, NB, acc);
-  else mma_ring(ring, A, lda, 0, B, K, nb0, nbs, NB, acc);
-}
-
-template <int HP>
-struct TrainLds {
-  static constexpr int TA = kTA;
-  static constexpr int LDG = kFP + 4;   // FP32 A tiles
-  static constexpr int LDH = HP + 4;
-  static constexpr int LDGB = kFP + 1;
-  static constexpr size_t al(size_t x) { return (x + 255) & ~size_t(255); }
-  static constexpr size_t mx(size_t a, size_t b) { return a > b ? a : b; }
-  static constexpr size_t tables = 0;
-  static constexpr size_t psi = al(sizeof(Tables));
-  static constexpr size_t psid = psi + al(4 * (size_t)TA * PS);
-  static constexpr size_t ptmp = psid + al(4 * (size_t)TA * PS);
-  static constexpr size_t inter = ptmp + al(4 * (size_t)TA * PS);
-  static constexpr size_t gt = inter + al(4 * (size_t)TA * IS);           // [16][LDG]: G rows 0-7, Gdot rows 8-15
-  static constexpr size_t gtmp = gt + al(4 * (size_t)16 * LDG);           // scratch (see gtmp_bytes)
-  // scratch: the tangent intermediates [8][ISF], later Gbar [16][LDGB]
-  static constexpr size_t gtmp_bytes = mx(4 * (size_t)TA * ISF, 4 * (size_t)16 * LDGB);
-  static constexpr size_t ht = gtmp + al(gtmp_bytes);                      // [16][LDH]: h1 / delta tiles
-  static constexpr size_t pba = ht + al(4 * (size_t)16 * LDH);            // Psibar accumulator [8][PS]
-  static constexpr size_t pbs = pba + al(4 * (size_t)TA * PS);            // scratch full gradient [8][PS]
-  static constexpr size_t ep = pbs + al(4 * (size_t)TA * PS);             // [waves][16 rows] partial sums (2 values)
-  static constexpr size_t rows = ep + al(4 * (size_t)kTrainWaves * 16 * 2);
-  static constexpr size_t bytes = rows + al(4 * 4 * (size_t)TA);          // scale, a, t, y-mean sums
+// ---------------------------------------------------------------------------
+// Invariants and their tangents.  G [N][kFP] (with PRIMAL) and Gd [N][kFP],
+// rows of the first weight product.  What bounds it: latency of the short
+// contraction tasks between block barriers, as in readout_features, so its
+// block size (three blocks per CU at 49 KB of LDS); the sums are those of the
+// earlier 8-atom training tile, term by term, which keeps the BF16 network's
+// operand roundings where they were.
+static constexpr size_t tf_al(size_t x) { return (x + 255) & ~size_t(255); }
+struct TrainFeatLds {
+  static constexpr size_t psi = tf_al(sizeof(Tables));
+  static constexpr size_t psid = psi + tf_al(4 * (size_t)kTfAtoms * PS);
+  static constexpr size_t inter = psid + tf_al(4 * (size_t)kTfAtoms * PS);
+  static constexpr size_t interd = inter + tf_al(4 * (size_t)kTfAtoms * ISF);
+  static constexpr size_t g = interd + tf_al(4 * (size_t)kTfAtoms * ISF);
+  static constexpr size_t gd = g + tf_al(4 * (size_t)kTfAtoms * kFP);
+  static constexpr size_t bytes = gd + tf_al(4 * (size_t)kTfAtoms * kFP);
 };
 
-// weight-product rows: row k = 16 * tile + r, r < 8 primal atom rows, r >= 8 tangent rows
-template <int HP, bool BF16>
-__global__ void __launch_bounds__(kTrainThreads)
-    train_tile(DevModel m, DevSystem sys, const float* __restrict__ psi, const float* __restrict__ psidot,
-               const double* __restrict__ ebar, float* __restrict__ psibar, float* __restrict__ psidotbar,
-               float* __restrict__ X1, float* __restrict__ Y1, float* __restrict__ X2, float* __restrict__ Y2,
-               float* __restrict__ w3g, float* __restrict__ qsig) {
-  using L = TrainLds<HP>;
-  using Sh = NetShape<16, HP, kTrainWaves>;
-  constexpr int TA = kTA;
-  constexpr int TPW = Sh::TPW, TPW_G = Sh::TPW_G, NBH = Sh::NBH, NBG = Sh::NBG, WPR = Sh::WPR;
+template <bool PRIMAL>
+__global__ void __launch_bounds__(kTfThreads) train_features(int n_atoms, const float* __restrict__ psi,
+                                                             const float* __restrict__ psid, float* __restrict__ G,
+                                                             float* __restrict__ Gd) {
+  using L = TrainFeatLds;
+  constexpr int TA = kTfAtoms, NT = kTfThreads, NP = kS * kPacked;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  Tables& tb = *(Tables*)(lds + L::tables);
+  Tables& tb = *(Tables*)lds;
   float* sPsi = (float*)(lds + L::psi);
   float* sPd = (float*)(lds + L::psid);
-  float* sPt = (float*)(lds + L::ptmp);
   float* sI = (float*)(lds + L::inter);
-  float* sGT = (float*)(lds + L::gt);
-  float* sGtmp = (float*)(lds + L::gtmp);
-  float* sGb = (float*)(lds + L::gtmp);
-  float* sH = (float*)(lds + L::ht);
-  float* sPbA = (float*)(lds + L::pba);
-  float* sPbS = (float*)(lds + L::pbs);
-  float* sEp = (float*)(lds + L::ep);
+  float* sId = (float*)(lds + L::interd);
+  float* sG = (float*)(lds + L::g);
+  float* sGd = (float*)(lds + L::gd);
+  const int tid = threadIdx.x;
+  const int row0 = xcd_block(blockIdx.x, gridDim.x) * TA;
+  const int n_rows = min(TA, n_atoms - row0);
+  // packed moments and tangents are contiguous runs: every load issued at
+  // once, then expanded into the full tensors
+  constexpr int NU = (TA * NP + NT - 1) / NT;
+  float v[NU], vd[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int t = tid + u * NT;
+    const bool ok = t < n_rows * NP;
+    v[u] = ok ? psi[(int64_t)row0 * NP + t] : 0.0f;
+    vd[u] = ok ? psid[(int64_t)row0 * NP + t] : 0.0f;
+  }
+  load_tables(&tb);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int t = tid + u * NT;
+    if (t < TA * NP) {
+      const int a = t / NP, e = t % NP;
+      const int s = e / kPacked, c = e % kPacked;
+      const int n = tb.packed_mult[c];
+      for (int q = 0; q < n; ++q) {
+        sPsi[a * PS + s * kFull + tb.packed_full[c][q]] = v[u];
+        sPd[a * PS + s * kFull + tb.packed_full[c][q]] = vd[u];
+      }
+    }
+  }
+  __syncthreads();
+  constexpr int KSF = 2 * ((TA * 20 + 63) / 64 * 64) <= NT ? 2 : 1;
+  contract_forward_a<TA, NT, false, PRIMAL, ISF, KSF>(sPsi, sI, sG, kFP, tb);
+  contract_forward_a_dual<TA, NT, ISF, KSF>(sPsi, sPd, sId, sGd, kFP);
+  __syncthreads();
+  if (PRIMAL) contract_forward_b<TA, NT, false, ISF>(sPsi, sI, sG, kFP, tb);
+  contract_forward_b_dual<TA, NT, ISF, ISF>(sPsi, sPd, sI, sId, sGd, kFP, tb);
+  __syncthreads();
+  const int n4 = n_rows * kFP / 4;
+  for (int t = tid; t < n4; t += NT) {
+    if (PRIMAL) ((float4*)(G + (int64_t)row0 * kFP))[t] = ((const float4*)sG)[t];
+    ((float4*)(Gd + (int64_t)row0 * kFP))[t] = ((const float4*)sGd)[t];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The network in dual numbers on tiles of 16 AB atoms: row block 2 q holds the
+// primal rows of atoms 16 q .. 16 q + 15, row block 2 q + 1 their tangent
+// rows, so a lane's accumulators hold both values of the same atom and unit
+// (products transposed as in readout_network: four consecutive units of one
+// atom per lane).  Rows of the weight products (X1, X2 and Y1, Y2: [2 N], the
+// primal rows first) are read and written as 16-byte runs.  BF16: operands
+// rounded once as they are stored; FP32: three parts (mfma.h).
+//   X1 = [G; Gdot] in; X2 = [h1; h1dot], Y2 = [z2bar; z2dotbar],
+//   Y1 = [z1bar; z1dotbar] out; Gbar, Gdbar out (dg_index)
+template <int HP, bool BF16, int AB>
+struct TrainNetLds {
+  static constexpr int TM = 32 * AB, NP = BF16 ? 1 : 3;
+  static constexpr int G = kFP + 8, H = HP + 8;  // row strides (bf16)
+  static constexpr size_t al(size_t x) { return (x + 255) & ~size_t(255); }
+  static constexpr size_t part_g = (size_t)TM * G, part_h = (size_t)TM * H;
+  static constexpr size_t rows = 0;                                        // scale, a
+  static constexpr size_t ep = rows + al(4 * 2 * 16 * (size_t)AB);         // [waves][TM] partial sums
+  static constexpr size_t a = ep + al(4 * (size_t)kTrainWaves * TM);
+  static constexpr size_t bytes = a + al(2 * NP * (part_g > part_h ? part_g : part_h));
+};
+
+template <int HP, bool BF16, int AB>
+__global__ void __launch_bounds__(kTrainThreads)
+    train_network(DevModel m, DevSystem sys, const double* __restrict__ ebar, const float* __restrict__ X1,
+                  float* __restrict__ Y1, float* __restrict__ X2, float* __restrict__ Y2, float* __restrict__ w3g,
+                  float* __restrict__ qsig, float* __restrict__ Gbar, float* __restrict__ Gdbar) {
+  using L = TrainNetLds<HP, BF16, AB>;
+  constexpr int NP = L::NP, MB = 2 * AB, NW = kTrainWaves;
+  constexpr int NBH = HP / 16, NBG = kFP / 16;
+  constexpr int TPW = (NBH + NW - 1) / NW, TPW_G = (NBG + NW - 1) / NW;
+  constexpr int PG = (int)L::part_g, PH = (int)L::part_h;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
   float* sScale = (float*)(lds + L::rows);
-  float* sA = sScale + TA;
-  float* sT = sA + TA;
+  float* sA = sScale + 16 * AB;
+  float* sEp = (float*)(lds + L::ep);
+  __bf16* sT = (__bf16*)(lds + L::a);
   const int tid = threadIdx.x;
   const int w = tid >> 6, l = tid & 63;
-  const int row0 = xcd_block(blockIdx.x, gridDim.x) * TA;
-  const int n_rows = min(TA, sys.n_atoms - row0);
-  const int64_t k0 = (int64_t)blockIdx.x * 16;  // first weight-product row of this tile
+  const int N = sys.n_atoms;
+  const int row0 = xcd_block(blockIdx.x, gridDim.x) * 16 * AB;
+  const int n_rows = min(16 * AB, N - row0);
+  // a lane's accumulator entries j = 0..3: unit uq + j of the column block,
+  // atom ar of the row block
+  const int ar = l & 15, uq = 4 * (l >> 4);
+  RowsRing<NP, TPW> ring;
+  RowsRing<NP, TPW_G> ring_g;
 
-  load_tables(&tb);
-  for (int a = tid; a < TA; a += kTrainThreads) {
-    float sc = 0.0f, aa = 0.0f;
-    if (a < n_rows) {
-      sc = m.scale[sys.species[row0 + a]];
-      aa = (float)ebar[sys.atom_struct[row0 + a]];
+  {
+    constexpr int C4 = kFP / 4;
+    constexpr int NU = L::TM * C4 / kTrainThreads;
+    static_assert(NU * kTrainThreads == L::TM * C4, "whole rounds of loads");
+    floatx4 v[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = tid + u * kTrainThreads;
+      const int row = t / C4, a = (row / 32) * 16 + row % 16;
+      v[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (a < n_rows) v[u] = ((const floatx4*)(X1 + ((int64_t)((row / 16) & 1) * N + row0 + a) * kFP))[t % C4];
     }
-    sScale[a] = sc;
-    sA[a] = aa;
+    rows_pre<NP, TPW>(ring, m.w1, kFP / 32, w, NW, NBH);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = tid + u * kTrainThreads;
+      st4<NP>(sT, PG, (t / C4) * L::G + (t % C4) * 4, v[u]);
+    }
+    for (int a = tid; a < 16 * AB; a += kTrainThreads) {
+      sScale[a] = a < n_rows ? m.scale[sys.species[row0 + a]] : 0.0f;
+      sA[a] = a < n_rows ? (float)ebar[sys.atom_struct[row0 + a]] : 0.0f;
+    }
+  }
+  lds_barrier();
+
+  // the two rows of atom `a` (in the tile) and unit col of a [2 N][HP] array
+  auto put = [&](float* X, int a, int col, floatx4 p, floatx4 t) {
+    if (a < n_rows) {
+      *(floatx4*)(X + (int64_t)(row0 + a) * HP + col) = p;
+      *(floatx4*)(X + (int64_t)(N + row0 + a) * HP + col) = t;
+    }
+  };
+  // the tile's operands of the next product, once every wave has read this one's
+  auto stage = [&](const floatx4 (&acc)[MB][TPW]) {
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      if (!has_block(i, w, NW, NBH)) continue;
+#pragma unroll
+      for (int r = 0; r < MB; ++r) st4<NP>(sT, PH, (r * 16 + ar) * L::H + (w + i * NW) * 16 + uq, acc[r][i]);
+    }
+    lds_barrier();
+  };
+
+  // ---- forward: z1, h1 and their tangents -------------------------------------
+  floatx4 s1d[AB][TPW], s1dd[AB][TPW], z1dot[AB][TPW];
+  {
+    floatx4 acc[MB][TPW];
+    zero_rows(acc);
+    mma_rows<NP>(ring, sT, PG, L::G, m.w1, kFP / 32, w, NW, NBH, acc);
+    rows_pre<NP, TPW>(ring, m.w2, HP / 32, w, NW, NBH);
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      if (!has_block(i, w, NW, NBH)) continue;
+      const int col = (w + i * NW) * 16 + uq;
+      const floatx4 bias = *(const floatx4*)(m.b1 + col);
+#pragma unroll
+      for (int q = 0; q < AB; ++q) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float zd = acc[2 * q + 1][i][j];
+          float s, d1, d2;
+          swish_d2(acc[2 * q][i][j] + bias[j], s, d1, d2);
+          s1d[q][i][j] = d1;
+          s1dd[q][i][j] = d2;
+          z1dot[q][i][j] = zd;
+          acc[2 * q][i][j] = s;
+          acc[2 * q + 1][i][j] = d1 * zd;
+        }
+        put(X2, q * 16 + ar, col, acc[2 * q][i], acc[2 * q + 1][i]);
+      }
+    }
+    stage(acc);
+  }
+  // ---- z2, h2, their tangents, and the adjoints z2bar, z2dotbar ----------------
+  {
+    floatx4 acc[MB][TPW];
+    zero_rows(acc);
+    mma_rows<NP>(ring, sT, PH, L::H, m.w2, HP / 32, w, NW, NBH, acc);
+    rows_pre<NP, TPW>(ring, m.w2t, HP / 32, w, NW, NBH);
+    float part[MB][4];  // sums over this wave's units of h2 . w3bar and h2dot . w3bar
+#pragma unroll
+    for (int r = 0; r < MB; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) part[r][j] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      if (!has_block(i, w, NW, NBH)) continue;
+      const int col = (w + i * NW) * 16 + uq;
+      const floatx4 bias = *(const floatx4*)(m.b2 + col);
+      const floatx4 wbv = *(const floatx4*)(m.w3bar + col);
+#pragma unroll
+      for (int q = 0; q < AB; ++q) {
+        const int a = q * 16 + ar;
+        const float sg = sScale[a], aa = sA[a];
+        floatx4 gw;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float wb = wbv[j], zd = acc[2 * q + 1][i][j];
+          float h2, d1, dd;
+          swish_d2(acc[2 * q][i][j] + bias[j], h2, d1, dd);
+          const float h2d = d1 * zd;
+          const float hbar = aa * sg * wb;   // dPhi/dh2
+          const float hdbar = -sg * wb;      // dPhi/dh2dot
+          part[2 * q][j] += h2 * wb;
+          part[2 * q + 1][j] += h2d * wb;
+          gw[j] = (aa * h2 - h2d) * sg / (float)m.M;
+          acc[2 * q][i][j] = hbar * d1 + hdbar * dd * zd;
+          acc[2 * q + 1][i][j] = hdbar * d1;
+        }
+        if (a < n_rows) *(floatx4*)(w3g + (int64_t)(row0 + a) * HP + col) = gw;
+        put(Y2, a, col, acc[2 * q][i], acc[2 * q + 1][i]);
+      }
+    }
+    // over the 16 units of a block: bits 3 and 2 across the lane groups, 1
+    // and 0 inside the lane
+#pragma unroll
+    for (int r = 0; r < MB; ++r) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        part[r][j] += __shfl_xor(part[r][j], 32);
+        part[r][j] += __shfl_xor(part[r][j], 16);
+      }
+      const float v = (part[r][0] + part[r][2]) + (part[r][1] + part[r][3]);
+      if (l < 16) sEp[w * L::TM + r * 16 + ar] = v;
+    }
+    stage(acc);
+  }
+  // scale gradient per atom: a ybar_mean - ydot_mean, with y_mean = h2 . w3bar + mean b3
+  if (tid < n_rows) {
+    const int r = tid / 16 * 32 + tid % 16;
+    float yp = 0.0f, yt = 0.0f, b3m = 0.0f;
+    for (int hm = 0; hm < m.M; ++hm) b3m += m.b3[hm];
+    b3m /= (float)m.M;
+    for (int ww = 0; ww < NW; ++ww) {
+      yp += sEp[ww * L::TM + r];
+      yt += sEp[ww * L::TM + r + 16];
+    }
+    qsig[row0 + tid] = sA[tid] * (yp + b3m) - yt;
+  }
+  // ---- reverse ------------------------------------------------------------------
+  {
+    floatx4 acc[MB][TPW];
+    zero_rows(acc);
+    mma_rows<NP>(ring, sT, PH, L::H, m.w2t, HP / 32, w, NW, NBH, acc);
+    rows_pre<NP, TPW_G>(ring_g, m.w1t, HP / 32, w, NW, NBG);
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      if (!has_block(i, w, NW, NBH)) continue;
+#pragma unroll
+      for (int q = 0; q < AB; ++q) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float hbar = acc[2 * q][i][j], hdbar = acc[2 * q + 1][i][j];
+          acc[2 * q][i][j] = hbar * s1d[q][i][j] + hdbar * s1dd[q][i][j] * z1dot[q][i][j];
+          acc[2 * q + 1][i][j] = hdbar * s1d[q][i][j];
+        }
+        put(Y1, q * 16 + ar, (w + i * NW) * 16 + uq, acc[2 * q][i], acc[2 * q + 1][i]);
+      }
+    }
+    stage(acc);
   }
   {
-    // the tile's packed moments and tangents are contiguous runs: every load
-    // issued at once, then expanded into the full tensors
-    constexpr int NP = kS * kPacked;
-    constexpr int NU = (TA * NP + kTrainThreads - 1) / kTrainThreads;
-    float v[NU], vd[NU];
+    floatx4 acc[MB][TPW_G];
+    zero_rows(acc);
+    mma_rows<NP, MB, TPW_G, true>(ring_g, sT, PH, L::H, m.w1t, HP / 32, w, NW, NBG, acc);
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int t = tid + u * kTrainThreads;
-      const bool ok = t < n_rows * NP;
-      v[u] = ok ? psi[(int64_t)row0 * NP + t] : 0.0f;
-      vd[u] = ok ? psidot[(int64_t)row0 * NP + t] : 0.0f;
-    }
-    __syncthreads();  // the tables are in LDS
+    for (int i = 0; i < TPW_G; ++i) {
+      if (!has_block(i, w, NW, NBG)) continue;
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int t = tid + u * kTrainThreads;
-      if (t < TA * NP) {
-        const int a = t / NP, e = t % NP;
-        const int s = e / kPacked, c = e % kPacked;
-        const int n = tb.packed_mult[c];
-        for (int q = 0; q < n; ++q) {
-          sPsi[a * PS + s * kFull + tb.packed_full[c][q]] = v[u];
-          sPd[a * PS + s * kFull + tb.packed_full[c][q]] = vd[u];
+      for (int r = 0; r < MB; ++r) {
+        const int a = r / 2 * 16 + uq;  // a lane's four atoms (of one feature)
+        if (a >= n_rows) continue;
+        float* o = (r & 1 ? Gdbar : Gbar) + dg_index(N, row0 + a, (w + i * NW) * 16 + ar);
+        if (N - (row0 + a) / kDgRun * kDgRun >= kDgRun) {
+          *(floatx4*)o = acc[r][i];  // a whole run: its rows are 16-byte aligned
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (a + j < n_rows) o[j] = acc[r][i][j];
         }
       }
     }
   }
-  __syncthreads();
-  // per-atom step t = |Psi| / |Psidot| for the exact polynomial differences
-  if (w < TA) {
-    float n0 = 0.0f, n1 = 0.0f;
-    for (int e = l; e < kS * kFull; e += 64) {
-      n0 += sPsi[w * PS + e] * sPsi[w * PS + e];
-      n1 += sPd[w * PS + e] * sPd[w * PS + e];
-    }
-    n0 = wave_sum(n0);
-    n1 = wave_sum(n1);
-    if (l == 0) sT[w] = (n1 > 0.0f && n0 > 0.0f) ? sqrtf(n0 / n1) : 1.0f;
-  }
-  __syncthreads();
-
-  // ---- invariants G (rows 0-7) and Gdot (rows 8-15) ---------------------------
-  contract_forward_a<TA, kTrainThreads, false, true, IS, kFwdSplit>(sPsi, sI, sGT, L::LDG, tb);
-  __syncthreads();
-  contract_forward_b<TA, kTrainThreads, false>(sPsi, sI, sGT, L::LDG, tb);
-  __syncthreads();
-  // Gdot = dG/dPsi . Psidot in dual numbers (exact: G is a polynomial in
-  // Psi); the tangent intermediates use the scratch region
-  contract_forward_a_dual<TA, kTrainThreads, ISF, kFwdSplit>(sPsi, sPd, sGtmp, sGT + 8 * L::LDG, L::LDG);
-  __syncthreads();
-  contract_forward_b_dual<TA, kTrainThreads, ISF>(sPsi, sPd, sI, sGtmp, sGT + 8 * L::LDG, L::LDG, tb);
-  __syncthreads();
-  // the first weight fragments of the network start loading now; each
-  // product then fills the ring of the next one as soon as its own
-  // fragments are consumed, ahead of its epilogue and barrier
-  BRing<BF16, TPW> ring;
-  ring_fill(ring, m.w1, kFP, w, WPR, NBH);
-  // weight-product rows X1 = [G; Gdot]
-  for (int t = tid; t < 16 * kFP; t += kTrainThreads) {
-    const int r = t / kFP, f = t % kFP;
-    X1[(k0 + r) * kFP + f] = ((r & 7) < n_rows) ? sGT[r * L::LDG + f] : 0.0f;
-  }
-
-  // ---- network forward in dual numbers ---------------------------------------------
-  // the wave's output fragments: rows 4 (l>>4) + j; lanes l and l^32 hold the
-  // primal (row < 8) and tangent (row + 8) value of the same column
-  const bool prim = l < 32;
-  const int cw = w;  // one 16-row block: waves split the columns
-  floatx4 s1d[TPW], s1dd[TPW], z1dot[TPW];
-  {
-    floatx4 acc[TPW];
-    zero_acc(acc);
-    train_mma(ring, sGT, L::LDG, m.w1, kFP, cw, WPR, NBH, acc);
-    ring_fill(ring, m.w2, HP, cw, WPR, NBH);
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = cw + i * WPR;
-      const int col = nb * 16 + (l & 15);
-      const float bias = nb < NBH ? m.b1[col] : 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float zv = acc[i][j] + (prim ? bias : 0.0f);
-        const float other = lane_xor32(zv);
-        const float z1 = prim ? zv : other, zd = prim ? other : zv;
-        float s, d1, d2;
-        swish_d2(z1, s, d1, d2);
-        s1d[i][j] = d1;
-        s1dd[i][j] = d2;
-        z1dot[i][j] = zd;
-        const int row = 4 * (l >> 4) + j;
-        if (nb < NBH) sH[row * L::LDH + col] = prim ? s : d1 * zd;
-      }
-    }
-  }
-  __syncthreads();
-  for (int t = tid; t < 16 * HP; t += kTrainThreads) {
-    const int r = t / HP, c = t % HP;
-    X2[(k0 + r) * HP + c] = ((r & 7) < n_rows) ? sH[r * L::LDH + c] : 0.0f;
-  }
-  {
-    floatx4 acc[TPW];
-    zero_acc(acc);
-    train_mma(ring, sH, L::LDH, m.w2, HP, cw, WPR, NBH, acc);
-    ring_fill(ring, m.w2t, HP, cw, WPR, NBH);
-    float ypart[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // primal lanes: h2 . w3bar, tangent lanes: h2dot . w3bar
-    floatx4 d2out[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = cw + i * WPR;
-      const int col = nb * 16 + (l & 15);
-      const bool ok = nb < NBH;
-      const float bias = ok ? m.b2[col] : 0.0f;
-      const float wb = ok ? m.w3bar[col] : 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = 4 * (l >> 4) + j;
-        const int a = row & 7;
-        const float zv = acc[i][j] + (prim ? bias : 0.0f);
-        const float other = lane_xor32(zv);
-        const float z2 = prim ? zv : other, zd = prim ? other : zv;
-        float h2, d1, dd;
-        swish_d2(z2, h2, d1, dd);
-        const float h2d = d1 * zd;
-        const float sg = sScale[a];
-        const float hbar = sA[a] * sg * wb;       // dPhi/dh2
-        const float hdbar = -sg * wb;             // dPhi/dh2dot
-        // primal row: z2bar = hbar s' + hdbar s'' z2dot; tangent row: z2dotbar = hdbar s'
-        d2out[i][j] = prim ? (hbar * d1 + hdbar * dd * zd) : (hdbar * d1);
-        ypart[j] += (prim ? h2 : h2d) * wb;
-        if (ok && prim && a < n_rows) w3g[(int64_t)(row0 + a) * HP + col] = (sA[a] * h2 - h2d) * sg / (float)m.M;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float v = ypart[j];
-      v = row16_rot_sum(v);  // lane 0 of the row: the xor-butterfly sum
-      if ((l & 15) == 0) sEp[w * 16 + 4 * (l >> 4) + j] = v;
-    }
-    __syncthreads();  // everyone has read h1 (sH) for the product above
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = cw + i * WPR;
-      if (nb >= NBH) continue;
-      const int col = nb * 16 + (l & 15);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sH[(4 * (l >> 4) + j) * L::LDH + col] = d2out[i][j];
-    }
-  }
-  __syncthreads();
-  // scale gradient per atom: a ybar_mean - ydot_mean, with y_mean = h2 . w3bar + mean b3
-  if (tid < TA) {
-    float yp = 0.0f, yt = 0.0f, b3m = 0.0f;
-    for (int hm = 0; hm < m.M; ++hm) b3m += m.b3[hm];
-    b3m /= (float)m.M;
-    for (int ww = 0; ww < kTrainWaves; ++ww) {
-      yp += sEp[ww * 16 + tid];
-      yt += sEp[ww * 16 + 8 + tid];
-    }
-    if (tid < n_rows) qsig[row0 + tid] = sA[tid] * (yp + b3m) - yt;
-  }
-  for (int t = tid; t < 16 * HP; t += kTrainThreads) {
-    const int r = t / HP, c = t % HP;
-    Y2[(k0 + r) * HP + c] = ((r & 7) < n_rows) ? sH[r * L::LDH + c] : 0.0f;
-  }
-  // ---- network reverse ------------------------------------------------------------
-  BRing<BF16, TPW_G> ring_g;
-  {
-    floatx4 acc[TPW];
-    zero_acc(acc);
-    train_mma(ring, sH, L::LDH, m.w2t, HP, cw, WPR, NBH, acc);
-    ring_fill(ring_g, m.w1t, HP, cw, WPR, NBG);
-    __syncthreads();  // all reads of [z2bar; z2dotbar] done before the tile is overwritten
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int nb = cw + i * WPR;
-      const int col = nb * 16 + (l & 15);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float hv = acc[i][j];                // primal lanes: h1bar, tangent lanes: h1dotbar
-        const float other = lane_xor32(hv);
-        const float hbar = prim ? hv : other, hdbar = prim ? other : hv;
-        const float out = prim ? (hbar * s1d[i][j] + hdbar * s1dd[i][j] * z1dot[i][j]) : (hdbar * s1d[i][j]);
-        if (nb < NBH) sH[(4 * (l >> 4) + j) * L::LDH + col] = out;
-      }
-    }
-  }
-  __syncthreads();
-  for (int t = tid; t < 16 * HP; t += kTrainThreads) {
-    const int r = t / HP, c = t % HP;
-    Y1[(k0 + r) * HP + c] = ((r & 7) < n_rows) ? sH[r * L::LDH + c] : 0.0f;
-  }
-  {
-    floatx4 acc[TPW_G];
-    zero_acc(acc);
-    train_mma(ring_g, sH, L::LDH, m.w1t, HP, cw, WPR, NBG, acc);
-#pragma unroll
-    for (int i = 0; i < TPW_G; ++i) {
-      const int nb = cw + i * WPR;
-      if (nb >= NBG) continue;
-      const int col = nb * 16 + (l & 15);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sGb[(4 * (l >> 4) + j) * L::LDGB + col] = acc[i][j];  // rows 0-7 Gbar, 8-15 Gdotbar
-    }
-  }
-  __syncthreads();
-
-  // ---- invariant backward ---------------------------------------------------------
-  const float* Gbar = sGb;
-  const float* Gdbar = sGb + 8 * L::LDGB;
-  // 8 atoms leave threads for both halves of every task of the invariant
-  // backward; the second halves go to the G tile, free from here on
-  constexpr int KS = (TA * 29 * 2 <= kTrainThreads) ? 2 : 1;
-  static_assert(KS == 1 || 2 * TA * PS <= 16 * L::LDG, "both second halves fit the G tile");
-  float* sPbS2 = KS == 2 ? sGT : nullptr;
-  float* sPbA2 = KS == 2 ? sGT + TA * PS : nullptr;
-  // Psidotbar = B(Psi; Gdotbar)
-  contract_forward_a<TA, kTrainThreads, false, false, IS, kFwdSplit>(sPsi, sI, nullptr, 0, tb);  // intermediates of Psi
-  __syncthreads();
-  contract_backward_a<TA, kTrainThreads, kTrainKSA>(sPsi, Gdbar, L::LDGB, sI, tb);
-  __syncthreads();
-  contract_backward_b<TA, kTrainThreads, KS>(sPsi, Gdbar, L::LDGB, sI, sPbS, tb, sPbS2);
-  __syncthreads();
-  auto to_psidotbar = [&](int a, int e, float v) {
-    if (a < n_rows) psidotbar[(int64_t)(row0 + a) * (kS * kPacked) + e] = v;
-  };
-  fold_packed<TA, kTrainThreads, decltype(to_psidotbar), KS == 2>(sPbS, tb, to_psidotbar, sPbS2);
-  // Psibar = B(Psi; Gbar) + [B(Psi + t Psidot; Gdotbar) - B(Psi - t Psidot; Gdotbar)] / (2t)
-  contract_backward_a<TA, kTrainThreads, kTrainKSA>(sPsi, Gbar, L::LDGB, sI, tb);
-  __syncthreads();
-  contract_backward_b<TA, kTrainThreads, KS>(sPsi, Gbar, L::LDGB, sI, sPbA, tb, sPbA2);
-  __syncthreads();
-  for (int ev = 0; ev < 2; ++ev) {
-    const float sgn = ev == 0 ? 1.0f : -1.0f;
-    for (int t = tid; t < TA * kS * kFull; t += kTrainThreads) {
-      const int a = t % TA, e = t / TA;
-      sPt[a * PS + e] = sPsi[a * PS + e] + sgn * sT[a] * sPd[a * PS + e];
-    }
-    __syncthreads();
-    contract_forward_a<TA, kTrainThreads, false, false, IS, kFwdSplit>(sPt, sI, nullptr, 0, tb);  // intermediates of Psi +- t Psidot
-    __syncthreads();
-    contract_backward_a<TA, kTrainThreads, kTrainKSA>(sPt, Gdbar, L::LDGB, sI, tb);
-    __syncthreads();
-    contract_backward_b<TA, kTrainThreads, KS>(sPt, Gdbar, L::LDGB, sI, sPbS, tb, sPbS2);
-    __syncthreads();
-    for (int t = tid; t < TA * kS * kFull; t += kTrainThreads) {
-      const int a = t % TA, e = t / TA;
-      const float d = KS == 2 ? sPbS[a * PS + e] + sPbS2[a * PS + e] : sPbS[a * PS + e];
-      sPbA[a * PS + e] += sgn * d / (2.0f * sT[a]);
-    }
-    __syncthreads();
-  }
-  auto to_psibar = [&](int a, int e, float v) {
-    if (a < n_rows) psibar[(int64_t)(row0 + a) * (kS * kPacked) + e] = v;
-  };
-  fold_packed<TA, kTrainThreads, decltype(to_psibar), KS == 2>(sPbA, tb, to_psibar, sPbA2);
 }
 
 // ---------------------------------------------------------------------------
@@ -578,16 +548,6 @@ __global__ void __launch_bounds__(kBetaMaxThreads) pair_beta_grad(DevModel m, De
 // same gradient evaluated in dual numbers (value, derivative along
 // delta_p), which needs R_s'' besides R_s and R_s'.  The positions' gradient
 // then gathers these over the reverse index like the forces.
-struct Dual {
-  float v, t;
-};
-__device__ inline Dual operator+(Dual a, Dual b) { return {a.v + b.v, a.t + b.t}; }
-__device__ inline Dual operator-(Dual a, Dual b) { return {a.v - b.v, a.t - b.t}; }
-__device__ inline Dual operator*(Dual a, Dual b) { return {a.v * b.v, a.v * b.t + a.t * b.v}; }
-__device__ inline Dual operator*(float a, Dual b) { return {a * b.v, a * b.t}; }
-__device__ inline Dual operator*(Dual a, float b) { return {a.v * b, a.t * b}; }
-__device__ inline Dual& operator+=(Dual& a, Dual b) { a.v += b.v; a.t += b.t; return a; }
-
 // R_s, dR_s/dr and d^2R_s/dr^2 (the basis and cutoff of radial<true>):
 //   Gaussians    g_k'' = (4 gamma^2 (r - mu_k)^2 - 2 gamma) g_k
 //   Bessel-like  d^2/dr^2 sinc(k x) = -(k pi / r_c)^2 sinc(k x) - 2 (cos(k x) - sinc(k x)) / r^2
@@ -970,36 +930,23 @@ __device__ inline float sum_chunks(const float* __restrict__ partial, int nchunk
   return v;
 }
 
-// out[i] = sum_c partial[c][i]
-__global__ void sum_partials(const float* __restrict__ partial, int nchunks, int64_t n, float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  out[i] = sum_chunks(partial, nchunks, n, i);
-}
-
-// the same sums of a padded [.][ld] gradient (n = padded size), written
-// unpadded into the caller's [rows][cols] array
-__global__ void sum_partials_unpad(const float* __restrict__ partial, int nchunks, int64_t n, int ld, int rows,
-                                   int cols, float* __restrict__ dst) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)rows * cols) return;
-  const int r = (int)(t / cols), c = (int)(t % cols);
-  dst[t] = sum_chunks(partial, nchunks, n, (int64_t)r * ld + c);
-}
-
-// column sums, stage 1: partial[chunk][c] = sum of Y[k][c] over the rows k
-// of the chunk (with primal_only, the rows with (k & 15) < 8: the primal
-// halves of the dual-number tiles).  Block = 64 columns x 4 row lanes; lane
-// r takes rows r, r + 4, ... of the chunk; the four lane sums are added in
-// lane order.  Grid (ceil(ncols / 64), chunks).
+// Sums over atoms, stage 1, in one launch: the bias gradients (columns of the
+// primal rows of Y1 and Y2), the W3 gradient (columns of w3g), and per species
+// the sums of qsig and of the energies' weights.
+//   blocks [0, 3 nx ny): array b / (nx ny), 64 columns x one chunk of rows;
+//     4 row lanes take rows r, r + 4, ... of the chunk, added in lane order:
+//     part[array][chunk][column]
+//   blocks beyond: species_partials' chunk of 256 atoms
 constexpr int kColChunks = 128;  // at most this many row chunks
-__global__ void __launch_bounds__(256) column_partials(const float* __restrict__ Y, int ld, int64_t nrows,
-                                                       int64_t rows_per_chunk, int ncols, bool primal_only,
-                                                       float* __restrict__ partial) {
-  __shared__ float red[4][64];
+struct ColumnSums {
+  const float* src[3];
+  int ncols[3];
+};
+__device__ inline void column_partials(const float* __restrict__ Y, int ld, int64_t nrows, int64_t rows_per_chunk,
+                                       int ncols, int bx, int chunk, float* __restrict__ partial, float (*red)[64]) {
   const int cl = threadIdx.x & 63, r = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
-  const int64_t k0 = (int64_t)blockIdx.y * rows_per_chunk;
+  const int c = bx * 64 + cl;
+  const int64_t k0 = (int64_t)chunk * rows_per_chunk;
   const int64_t k1 = min(nrows, k0 + rows_per_chunk);
   float v = 0.0f;
   if (c < ncols) {
@@ -1007,32 +954,26 @@ __global__ void __launch_bounds__(256) column_partials(const float* __restrict__
     for (; k + 28 < k1; k += 32) {
       float x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int64_t kk = k + 4 * u;
-        x[u] = (!primal_only || (kk & 15) < 8) ? Y[kk * ld + c] : 0.0f;
-      }
+      for (int u = 0; u < 8; ++u) x[u] = Y[(k + 4 * u) * ld + c];
 #pragma unroll
       for (int u = 0; u < 8; ++u) v += x[u];
     }
-    for (; k < k1; k += 4)
-      if (!primal_only || (k & 15) < 8) v += Y[k * ld + c];
+    for (; k < k1; k += 4) v += Y[k * ld + c];
   }
   red[r][cl] = v;
   __syncthreads();
-  if (r == 0 && c < ncols)
-    partial[(int64_t)blockIdx.y * ncols + c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+  if (r == 0 && c < ncols) partial[(int64_t)chunk * ncols + c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
 }
 
-// per-species sums, stage 1: block b takes atoms [b*256, b*256+256) and
-// writes, in FP64, sp[b][z][0] = sum qsig_i and sp[b][z][1] = sum ebar_b(i)
-// over its atoms of species z, and sp[b][nsp][0] = sum ebar_b(i) sigma_z(i)
+// per-species sums: chunk b takes atoms [b*256, b*256+256) and writes, in
+// FP64, sp[b][z][0] = sum qsig_i and sp[b][z][1] = sum ebar_b(i) over its
+// atoms of species z, and sp[b][nsp][0] = sum ebar_b(i) sigma_z(i)
 // (fixed-shape tree sums: the result does not depend on scheduling)
 constexpr int kSpeciesChunk = 256;
-__global__ void __launch_bounds__(kSpeciesChunk)
-    species_partials(DevModel m, DevSystem sys, const double* __restrict__ ebar, const float* __restrict__ qsig,
-                     double* __restrict__ sp) {
-  __shared__ double red[kSpeciesChunk / 64][kMaxSpecies + 1][2];
-  const int i = blockIdx.x * kSpeciesChunk + threadIdx.x;
+__device__ inline void species_partials(const DevModel& m, const DevSystem& sys, const double* __restrict__ ebar,
+                                        const float* __restrict__ qsig, int b, double* __restrict__ sp,
+                                        double (*red)[kMaxSpecies + 1][2]) {
+  const int i = b * kSpeciesChunk + threadIdx.x;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   int z = -1;
   double q = 0.0, e = 0.0;
@@ -1043,11 +984,11 @@ __global__ void __launch_bounds__(kSpeciesChunk)
   }
   const int nsp = m.n_species;
   for (int t = 0; t < nsp; ++t) {
-    const double a = wave_sum(z == t ? q : 0.0);
-    const double b = wave_sum(z == t ? e : 0.0);
+    const double x = wave_sum(z == t ? q : 0.0);
+    const double y = wave_sum(z == t ? e : 0.0);
     if (l == 0) {
-      red[w][t][0] = a;
-      red[w][t][1] = b;
+      red[w][t][0] = x;
+      red[w][t][1] = y;
     }
   }
   const double c = wave_sum(z >= 0 ? e * (double)m.scale[z] : 0.0);
@@ -1057,85 +998,119 @@ __global__ void __launch_bounds__(kSpeciesChunk)
     const int t = threadIdx.x >> 1, k = threadIdx.x & 1;
     double v = 0.0;
     for (int ww = 0; ww < kSpeciesChunk / 64; ++ww) v += (t < nsp || k == 0) ? red[ww][t][k] : 0.0;
-    sp[((int64_t)blockIdx.x * (kMaxSpecies + 1) + t) * 2 + k] = v;
+    sp[((int64_t)b * (kMaxSpecies + 1) + t) * 2 + k] = v;
   }
 }
 
-// stage 2: scale / shift / b3 gradients from the block partials, in block order
-__global__ void species_finish(DevModel m, const double* __restrict__ sp, int nblocks, float* __restrict__ gscale,
-                               float* __restrict__ gshift, float* __restrict__ gb3) {
-  const int t = threadIdx.x;
-  const int nsp = m.n_species;
+__global__ void __launch_bounds__(kSpeciesChunk)
+    train_partials(DevModel m, DevSystem sys, const double* __restrict__ ebar, const float* __restrict__ qsig,
+                   ColumnSums cols, int64_t rows_per_chunk, int nx, int ny, float* __restrict__ part,
+                   int64_t part_stride, double* __restrict__ sp) {
+  __shared__ double smem[kSpeciesChunk / 64][kMaxSpecies + 1][2];
+  static_assert(sizeof(smem) >= sizeof(float) * 4 * 64, "the column sums' four rows fit");
+  const int b = blockIdx.x;
+  if (b < 3 * nx * ny) {
+    const int k = b / (nx * ny), t = b % (nx * ny);
+    column_partials(cols.src[k], m.HP1, sys.n_atoms, rows_per_chunk, cols.ncols[k], t % nx, t / nx,
+                    part + k * part_stride, (float(*)[64])smem);
+  } else {
+    species_partials(m, sys, ebar, qsig, b - 3 * nx * ny, sp, smem);
+  }
+}
+
+// Stage 2, in one launch: every gradient from its partials, added in chunk
+// order, into the caller's arrays (unpadded).  Per head of a shallow ensemble
+// (head >= 0) the shared arrays are summed over the heads in head order and
+// W3 and b3 take the head's column; otherwise every head's column of W3 and
+// b3 equals the mean's gradient.
+struct GradSums {
+  const float *part1, *part2, *cpart, *bpart;
+  int64_t cstride;  // between the three column-sum arrays in cpart
+  const double* sp;
+  int kch, cch, bch, sp_blocks;
+  int HP, H1, H2, heads, head;  // heads: columns of W3
+};
+__global__ void __launch_bounds__(256) train_sums(DevModel m, GradSums g, gmnn_param_grads out) {
+  const int nsp = m.n_species, nslots = nsp * nsp * kS * kMaxBasis;
+  const bool add = g.head > 0;
+  auto store = [&](float* dst, int64_t i, float v) { dst[i] = add ? dst[i] + v : v; };
+  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t n1 = (int64_t)kF * g.H1, n2 = (int64_t)g.H1 * g.H2;
+  if (t < n1) {
+    store(out.W1, t, sum_chunks(g.part1, g.kch, (int64_t)kFP * g.HP, t / g.H1 * g.HP + t % g.H1));
+    return;
+  }
+  t -= n1;
+  if (t < n2) {
+    store(out.W2, t, sum_chunks(g.part2, g.kch, (int64_t)g.HP * g.HP, t / g.H2 * g.HP + t % g.H2));
+    return;
+  }
+  t -= n2;
+  if (t < g.H1) {
+    store(out.b1, t, sum_chunks(g.cpart, g.cch, g.H1, t));
+    return;
+  }
+  t -= g.H1;
+  if (t < g.H2) {
+    store(out.b2, t, sum_chunks(g.cpart + g.cstride, g.cch, g.H2, t));
+    return;
+  }
+  t -= g.H2;
+  if (t < g.H2) {
+    const float v = sum_chunks(g.cpart + 2 * g.cstride, g.cch, g.H2, t);
+    if (g.head >= 0) out.W3[t * g.heads + g.head] = v;
+    else
+      for (int h = 0; h < g.heads; ++h) out.W3[t * g.heads + h] = v;
+    return;
+  }
+  t -= g.H2;
+  if (t < (int64_t)nsp * nsp * kS * m.K) {
+    store(out.beta, t, sum_chunks(g.bpart, g.bch, nslots, t / m.K * kMaxBasis + t % m.K));
+    return;
+  }
+  t -= (int64_t)nsp * nsp * kS * m.K;
   if (t > nsp) return;
-  // block partials added in block order; the loads of 8 blocks are issued
-  // before their adds so they overlap
+  // scale / shift / b3 from the species sums, added in block order; the loads
+  // of 8 blocks are issued before their adds so they overlap
   constexpr int kBatch = 8;
   double s1 = 0.0, s2 = 0.0;
-  for (int b0 = 0; b0 < nblocks; b0 += kBatch) {
+  for (int b0 = 0; b0 < g.sp_blocks; b0 += kBatch) {
     double x[kBatch], y[kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
-      const int64_t o = ((int64_t)std::min(b0 + j, nblocks - 1) * (kMaxSpecies + 1) + t) * 2;
-      x[j] = sp[o];
-      y[j] = sp[o + 1];
+      const int64_t o = ((int64_t)std::min(b0 + j, g.sp_blocks - 1) * (kMaxSpecies + 1) + t) * 2;
+      x[j] = g.sp[o];
+      y[j] = g.sp[o + 1];
     }
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
-      if (b0 + j < nblocks) {
+      if (b0 + j < g.sp_blocks) {
         s1 += x[j];
         s2 += y[j];
       }
     }
   }
   if (t < nsp) {
-    gscale[t] = (float)s1;
-    gshift[t] = (float)s2;
+    store(out.scale, t, (float)s1);
+    store(out.shift, t, (float)s2);
+  } else if (g.head >= 0) {
+    out.b3[g.head] = (float)s1;
   } else {
     // dPhi/db3_m = sum_i a_i sigma_i / M (the same for every head)
-    for (int hm = 0; hm < m.M; ++hm) gb3[hm] = (float)(s1 / m.M);
+    for (int h = 0; h < g.heads; ++h) out.b3[h] = (float)(s1 / g.heads);
   }
 }
 
-// W3 gradient: every head column equals the column sum of w3g
-__global__ void w3_broadcast(const float* __restrict__ w3sum, int H2, int M, float* __restrict__ gw3) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H2) return;
-  for (int hm = 0; hm < M; ++hm) gw3[(int64_t)h * M + hm] = w3sum[h];
-}
-
-// beta gradient: sum of block partials in block order
-__global__ void beta_unpack(const float* __restrict__ summed, int nsp, int K, float* __restrict__ gbeta) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = nsp * nsp * kS * K;
-  if (t >= n) return;
-  const int k = t % K, rest = t / K;
-  gbeta[t] = summed[rest * kMaxBasis + k];
-}
-
 // ---------------------------------------------------------------------------
-template <int HP, bool BF16>
-static gmnn_status launch_train_tile_t(const DevModel& m, const DevSystem& sys, const float* psi, const float* psidot,
-                                       const double* ebar, float* psibar, float* psidotbar, float* X1, float* Y1,
-                                       float* X2, float* Y2, float* w3g, float* qsig, hipStream_t s) {
-  using L = TrainLds<HP>;
-  if (L::bytes > 160 * 1024) return GMNN_ERR_UNSUPPORTED;
-  auto k = train_tile<HP, BF16>;
-  const gmnn_status sa = ensure_lds_limit((const void*)k, L::bytes);
-  if (sa != GMNN_OK) return sa;
-  const int grid = (sys.n_atoms + kTA - 1) / kTA;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(kTrainThreads), L::bytes, s, m, sys, psi, psidot, ebar, psibar, psidotbar,
-                     X1, Y1, X2, Y2, w3g, qsig);
-  return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
-}
-
 struct TrainLayout {
-  size_t psi, psidot, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, part1, part2, bpart, bsum;
-  size_t cpart, w3sum, spart, bytes;
-  int ccK, ccN;        // row chunks of the column sums over K rows / over N atoms
-  int64_t rcK, rcN;    // rows per chunk of those sums
+  size_t psi, psidot, psibar, psidotbar, X1, Y1, X2, Y2, gbar, gdbar, w3g, qsig, part1, part2, bpart;
+  size_t cpart, spart, bytes;
+  int64_t cstride;     // between the column-sum arrays in cpart
+  int ccN;             // row chunks of the column sums
+  int64_t rcN;         // rows per chunk
   int sp_blocks;       // blocks of the per-species sums
-  int64_t K;           // weight-product rows
-  int kchunks;          // split-K chunks the partial buffers hold (the larger count)
+  int64_t K;           // weight-product rows: primal, then tangent
+  int kchunks;         // split-K chunks the partial buffers hold (the larger count)
   int beta_blocks;
 };
 
@@ -1148,8 +1123,7 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
     return o;
   };
   const size_t N = (size_t)n_atoms;
-  const int64_t tiles = (n_atoms + kTA - 1) / kTA;
-  L.K = tiles * 16;
+  L.K = 2 * (int64_t)N;
   L.kchunks = (int)((L.K + kWgRowsF32 - 1) / kWgRowsF32);
   L.beta_blocks = 256;
   L.psi = take(4 * N * 100);
@@ -1160,19 +1134,18 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   L.Y1 = take(4 * (size_t)L.K * HP);
   L.X2 = take(4 * (size_t)L.K * HP);
   L.Y2 = take(4 * (size_t)L.K * HP);
+  L.gbar = take(4 * N * kFP);
+  L.gdbar = take(4 * N * kFP);
   L.w3g = take(4 * N * HP);
   L.qsig = take(4 * N);
   L.part1 = take(4 * (size_t)L.kchunks * kFP * HP);
   L.part2 = take(4 * (size_t)L.kchunks * HP * HP);
   const size_t nslots = (size_t)nsp * nsp * kS * kMaxBasis;
   L.bpart = take(4 * (size_t)L.beta_blocks * nslots);
-  L.bsum = take(4 * nslots);
-  L.rcK = L.K > 0 ? (L.K + kColChunks - 1) / kColChunks : 1;
   L.rcN = N > 0 ? ((int64_t)N + kColChunks - 1) / kColChunks : 1;
-  L.ccK = (int)((L.K + L.rcK - 1) / L.rcK);
   L.ccN = (int)(((int64_t)N + L.rcN - 1) / L.rcN);
-  L.cpart = take(4 * (size_t)HP * (size_t)(L.ccK > L.ccN ? L.ccK : L.ccN));
-  L.w3sum = take(4 * (size_t)HP);
+  L.cstride = (int64_t)HP * L.ccN;
+  L.cpart = take(4 * 3 * (size_t)L.cstride);
   L.sp_blocks = (int)((N + kSpeciesChunk - 1) / kSpeciesChunk);
   L.spart = take(8 * 2 * (size_t)(kMaxSpecies + 1) * (L.sp_blocks > 0 ? L.sp_blocks : 1));
   L.bytes = off;
@@ -1183,15 +1156,52 @@ template <int LPA>
 __global__ void pair_moments(DevModel m, DevSystem sys, float* psi, int* counters, int n_counters);
 
 bool train_supported(const DevModel& m) {
-  return m.n_species <= kMaxSpecies && TrainLds<512>::bytes <= 160 * 1024 &&
-         (m.HP1 == 64 || m.HP1 == 128 || m.HP1 == 256 || m.HP1 == 512);
+  return m.n_species <= kMaxSpecies && (m.HP1 == 64 || m.HP1 == 128 || m.HP1 == 256 || m.HP1 == 512);
 }
 
 size_t train_workspace_bytes(int n_atoms, int HP, int nsp) { return train_layout(n_atoms, HP, nsp).bytes; }
 
+struct TrainNetArgs {
+  const double* ebar;
+  const float* X1;
+  float *Y1, *X2, *Y2, *w3g, *qsig, *Gbar, *Gdbar;
+};
+template <int HP, bool BF16, int AB>
+static gmnn_status launch_train_network_t(const DevModel& m, const DevSystem& sys, const TrainNetArgs& t,
+                                          hipStream_t s) {
+  using L = TrainNetLds<HP, BF16, AB>;
+  static_assert(L::bytes <= 160 * 1024, "the tile fits the LDS");
+  auto k = train_network<HP, BF16, AB>;
+  const gmnn_status st = ensure_lds_limit((const void*)k, L::bytes);
+  if (st != GMNN_OK) return st;
+  hipLaunchKernelGGL(k, dim3((sys.n_atoms + 16 * AB - 1) / (16 * AB)), dim3(kTrainThreads), L::bytes, s, m, sys,
+                     t.ebar, t.X1, t.Y1, t.X2, t.Y2, t.w3g, t.qsig, t.Gbar, t.Gdbar);
+  return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
+}
+static gmnn_status launch_train_network(const DevModel& m, const DevSystem& sys, bool bf16, const TrainNetArgs& t,
+                                        hipStream_t s) {
+  // 32-atom tiles (half the weight traffic) once 16-atom ones would need a
+  // second round of the 256 compute units, where registers and LDS allow
+  const bool two = sys.n_atoms > 16 * 256;
+#define CASE(HP, AB2)                                                                            \
+  if (m.HP1 == HP) {                                                                             \
+    if (AB2 > 1 && two)                                                                          \
+      return bf16 ? launch_train_network_t<HP, true, AB2>(m, sys, t, s)                          \
+                  : launch_train_network_t<HP, false, AB2>(m, sys, t, s);                        \
+    return bf16 ? launch_train_network_t<HP, true, 1>(m, sys, t, s)                              \
+                : launch_train_network_t<HP, false, 1>(m, sys, t, s);                            \
+  }
+  CASE(64, 1) CASE(128, 1) CASE(256, 2) CASE(512, 1)
+#undef CASE
+  return GMNN_ERR_UNSUPPORTED;
+}
+
+// head < 0: the head-mean gradient.  head >= 0: head `head` of `heads` (m is
+// its one-head view): shared gradients summed in head order, W3 and b3 by
+// column; the moments and invariants of the first head serve the others.
 gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                            const double* ebar, const float* lambda, gmnn_param_grads* g, void* ws, size_t ws_bytes,
-                           float* dL_dpos, float* gpos, bool accumulate_pos, hipStream_t s) {
+                           float* dL_dpos, float* gpos, int head, int heads, hipStream_t s) {
   const int HP = m.HP1;
   const int nsp = m.n_species;
   const TrainLayout L = train_layout(sys.n_atoms, HP, nsp);
@@ -1202,116 +1212,89 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
   float* psibar = (float*)(W + L.psibar);
   float* psidotbar = (float*)(W + L.psidotbar);
   float *X1 = (float*)(W + L.X1), *Y1 = (float*)(W + L.Y1), *X2 = (float*)(W + L.X2), *Y2 = (float*)(W + L.Y2);
+  float *gbar = (float*)(W + L.gbar), *gdbar = (float*)(W + L.gdbar);
   float* w3g = (float*)(W + L.w3g);
   float* qsig = (float*)(W + L.qsig);
   float* part1 = (float*)(W + L.part1);
   float* part2 = (float*)(W + L.part2);
   float* bpart = (float*)(W + L.bpart);
-  float* bsum = (float*)(W + L.bsum);
+  float* cpart = (float*)(W + L.cpart);
+  double* spart = (double*)(W + L.spart);
   const int N = sys.n_atoms;
   const int nslots = nsp * nsp * kS * kMaxBasis;
   const size_t beta_lds = sizeof(float) * (size_t)nslots;
   const int lpa = (N < 8192 && !lanes16) ? 64 : 16;
   const int nb = (N + kPairBlock / lpa - 1) / (kPairBlock / lpa);
+  const bool first = head <= 0;
   gmnn_status st = GMNN_OK;
   if (N > 0) {
     if (lpa == 64) {
-      hipLaunchKernelGGL(pair_moments<64>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, psi, (int*)nullptr, 0);
+      if (first)
+        hipLaunchKernelGGL(pair_moments<64>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, psi, (int*)nullptr, 0);
       hipLaunchKernelGGL(pair_tangent<64>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, lambda, psidot);
     } else {
-      hipLaunchKernelGGL(pair_moments<16>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, psi, (int*)nullptr, 0);
+      if (first)
+        hipLaunchKernelGGL(pair_moments<16>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, psi, (int*)nullptr, 0);
       hipLaunchKernelGGL(pair_tangent<16>, dim3(nb), dim3(kPairBlock), beta_lds, s, m, sys, lambda, psidot);
     }
-    switch (HP) {
-      case 64:
-        st = bf16 ? launch_train_tile_t<64, true>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s)
-                  : launch_train_tile_t<64, false>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s);
-        break;
-      case 128:
-        st = bf16 ? launch_train_tile_t<128, true>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s)
-                  : launch_train_tile_t<128, false>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s);
-        break;
-      case 256:
-        st = bf16 ? launch_train_tile_t<256, true>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s)
-                  : launch_train_tile_t<256, false>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s);
-        break;
-      case 512:
-        st = bf16 ? launch_train_tile_t<512, true>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s)
-                  : launch_train_tile_t<512, false>(m, sys, psi, psidot, ebar, psibar, psidotbar, X1, Y1, X2, Y2, w3g, qsig, s);
-        break;
-      default: return GMNN_ERR_UNSUPPORTED;
-    }
+    auto kf = first ? train_features<true> : train_features<false>;
+    st = ensure_lds_limit((const void*)kf, TrainFeatLds::bytes);
+    if (st != GMNN_OK) return st;
+    hipLaunchKernelGGL(kf, dim3((N + kTfAtoms - 1) / kTfAtoms), dim3(kTfThreads), TrainFeatLds::bytes, s, N, psi,
+                       psidot, X1, X1 + (int64_t)N * kFP);
+    st = launch_train_network(m, sys, bf16, TrainNetArgs{ebar, X1, Y1, X2, Y2, w3g, qsig, gbar, gdbar}, s);
+    if (st == GMNN_OK) st = launch_contract_back_dual(N, psi, psidot, gdbar, gbar, psidotbar, psibar, s);
     if (st != GMNN_OK) return st;
   }
   if (dL_dpos && N > 0) {
     // the positions' gradient from the same adjoints as the beta gradient
     const int nbp = (N + kPairBlock / kPosLanes - 1) / (kPairBlock / kPosLanes);
     auto kp = m.basis == GMNN_BASIS_BESSEL ? pair_pos_grad<GMNN_BASIS_BESSEL> : pair_pos_grad<GMNN_BASIS_GAUSSIAN>;
-    const gmnn_status sp = ensure_lds_limit((const void*)kp, beta_lds);
-    if (sp != GMNN_OK) return sp;
+    st = ensure_lds_limit((const void*)kp, beta_lds);
+    if (st != GMNN_OK) return st;
     hipLaunchKernelGGL(kp, dim3(nbp), dim3(kPairBlock), beta_lds, s, m, sys, lambda, psibar, psidotbar, gpos);
-    hipLaunchKernelGGL(pos_gather, dim3(nbp), dim3(kPairBlock), 0, s, sys, gpos, dL_dpos, accumulate_pos ? 1 : 0);
+    hipLaunchKernelGGL(pos_gather, dim3(nbp), dim3(kPairBlock), 0, s, sys, gpos, dL_dpos, first ? 0 : 1);
   }
   // waves per block: the beta table plus one gradient copy per wave in 160 KB
   const int beta_waves = (int)std::min<size_t>(kBetaMaxThreads / 64, std::max<size_t>(1, 160 * 1024 / beta_lds - 1));
   {
     auto kb = m.basis == GMNN_BASIS_BESSEL ? pair_beta_grad<GMNN_BASIS_BESSEL> : pair_beta_grad<GMNN_BASIS_GAUSSIAN>;
-    const gmnn_status sa = ensure_lds_limit((const void*)kb, beta_lds * (1 + beta_waves));
-    if (sa != GMNN_OK) return sa;
+    st = ensure_lds_limit((const void*)kb, beta_lds * (1 + beta_waves));
+    if (st != GMNN_OK) return st;
     hipLaunchKernelGGL(kb, dim3(L.beta_blocks), dim3(64 * beta_waves), beta_lds * (1 + beta_waves), s, m, sys, lambda,
                        psibar, psidotbar, bpart);
   }
-  // weight products, split over chunks of rows, partials summed in chunk order
+  // weight products, split over chunks of rows, partials summed in chunk order:
+  // two parts per operand on the BF16 path, three on the FP32 path; widths
+  // that are multiples of the staged kernel's block tile take it
   const bool staged = HP % kWgBlk == 0;
   const int64_t wg_rows = (staged && !bf16) ? kWgRowsF32 : kWgRows;
   const int kch = (int)((L.K + wg_rows - 1) / wg_rows);
-  {
-    if (kch > 0) {
-      // two parts per operand on the BF16 path, three on the FP32 path; widths
-      // that are multiples of the staged kernel's block tile take it
-      auto product = [&](const float* X, int ldx, const float* Y, float* part) {
-        if (staged)
-          hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
-                             dim3((ldx / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K,
-                             wg_rows, part);
-        else
-          hipLaunchKernelGGL(bf16 ? weight_grad<2> : weight_grad<3>, dim3(((ldx / 64) * (HP / 64) + 3) / 4, kch),
-                             dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K, wg_rows, part);
-      };
-      product(X1, kFP, Y1, part1);
-      product(X2, HP, Y2, part2);
-    }
-    const int64_t n1 = (int64_t)kFP * HP, n2 = (int64_t)HP * HP;
-    // [kFP][HP] and [HP][HP] partials summed straight into the caller's [F][H1] and [H1][H2]
-    hipLaunchKernelGGL(sum_partials_unpad, dim3((kF * H1 + 255) / 256), dim3(256), 0, s, part1, kch, n1, HP,
-                       kF, H1, g->W1);
-    hipLaunchKernelGGL(sum_partials_unpad, dim3((H1 * H2 + 255) / 256), dim3(256), 0, s, part2, kch, n2, HP,
-                       H1, H2, g->W2);
+  if (kch > 0) {
+    auto product = [&](const float* X, int ldx, const float* Y, float* part) {
+      if (staged)
+        hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
+                           dim3((ldx / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K,
+                           wg_rows, part);
+      else
+        hipLaunchKernelGGL(bf16 ? weight_grad<2> : weight_grad<3>, dim3(((ldx / 64) * (HP / 64) + 3) / 4, kch),
+                           dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K, wg_rows, part);
+    };
+    product(X1, kFP, Y1, part1);
+    product(X2, HP, Y2, part2);
   }
-  // bias, W3, scale/shift gradients: two-stage sums with chunk partials added in order
-  float* cpart = (float*)(W + L.cpart);
-  float* w3sum = (float*)(W + L.w3sum);
-  double* spart = (double*)(W + L.spart);
+  // bias, W3, scale/shift partials, then every gradient from its partials
   // (with no atoms there are no chunks: the sums of zero partials are zero)
-  if (N > 0)
-    hipLaunchKernelGGL(column_partials, dim3((H1 + 63) / 64, L.ccK), dim3(256), 0, s, Y1, HP, L.K, L.rcK, H1, true,
-                       cpart);
-  hipLaunchKernelGGL(sum_partials, dim3((H1 + 255) / 256), dim3(256), 0, s, cpart, L.ccK, (int64_t)H1, g->b1);
-  if (N > 0)
-    hipLaunchKernelGGL(column_partials, dim3((H2 + 63) / 64, L.ccK), dim3(256), 0, s, Y2, HP, L.K, L.rcK, H2, true,
-                       cpart);
-  hipLaunchKernelGGL(sum_partials, dim3((H2 + 255) / 256), dim3(256), 0, s, cpart, L.ccK, (int64_t)H2, g->b2);
   if (N > 0) {
-    hipLaunchKernelGGL(column_partials, dim3((H2 + 63) / 64, L.ccN), dim3(256), 0, s, w3g, HP, (int64_t)N, L.rcN, H2,
-                       false, cpart);
-    hipLaunchKernelGGL(species_partials, dim3(L.sp_blocks), dim3(kSpeciesChunk), 0, s, m, sys, ebar, qsig, spart);
+    const int nx = (std::max(H1, H2) + 63) / 64;
+    hipLaunchKernelGGL(train_partials, dim3(3 * nx * L.ccN + L.sp_blocks), dim3(kSpeciesChunk), 0, s, m, sys, ebar,
+                       qsig, ColumnSums{{Y1, Y2, w3g}, {H1, H2, H2}}, L.rcN, nx, L.ccN, cpart, L.cstride, spart);
   }
-  hipLaunchKernelGGL(sum_partials, dim3((H2 + 255) / 256), dim3(256), 0, s, cpart, L.ccN, (int64_t)H2, w3sum);
-  hipLaunchKernelGGL(w3_broadcast, dim3((H2 + 255) / 256), dim3(256), 0, s, w3sum, H2, m.M, g->W3);
-  hipLaunchKernelGGL(species_finish, dim3(1), dim3(64), 0, s, m, spart, L.sp_blocks, g->scale, g->shift, g->b3);
-  hipLaunchKernelGGL(sum_partials, dim3((nslots + 255) / 256), dim3(256), 0, s, bpart, L.beta_blocks,
-                     (int64_t)nslots, bsum);
-  hipLaunchKernelGGL(beta_unpack, dim3((nsp * nsp * kS * m.K + 255) / 256), dim3(256), 0, s, bsum, nsp, m.K, g->beta);
+  const GradSums sums{part1, part2, cpart, bpart, L.cstride, spart, kch, L.ccN, L.beta_blocks, L.sp_blocks,
+                      HP, H1, H2, heads, head};
+  const int64_t total = (int64_t)kF * H1 + (int64_t)H1 * H2 + H1 + 2 * (int64_t)H2 +
+                        (int64_t)nsp * nsp * kS * m.K + nsp + 1;
+  hipLaunchKernelGGL(train_sums, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, m, sums, *g);
   return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
 }
 
