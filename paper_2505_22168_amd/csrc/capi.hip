@@ -903,7 +903,8 @@ gmnn_status gmnn_last_layer_features(const gmnn_model* m, const gmnn_system* sys
                        s);
     if (st != GMNN_OK) return st;
   }
-  hipLaunchKernelGGL(ll_features, dim3(sys->n_structs), dim3(256), 0, s, dm, ds, m->hidden2, h2, phi);
+  // one thread per column of a structure's features
+  hipLaunchKernelGGL(ll_features, dim3(sys->n_structs), dim3(round_up(m->hidden2 + 1, 64)), 0, s, dm, ds, m->hidden2, h2, phi);
   if (hipGetLastError() != hipSuccess) return GMNN_ERR_HIP;
   if ((flags & GMNN_SYNC) && hipStreamSynchronize(s) != hipSuccess) return GMNN_ERR_HIP;
   return GMNN_OK;
