@@ -33,6 +33,8 @@ gmnn_status launch_tile(bool fused, bool perhead, int tile_atoms, const DevModel
 bool tile_fused_supported(int n_species, int hp, bool bf16, bool perhead);
 gmnn_status launch_stream(const DevModel& m, const DevSystem& sys, bool bf16, const float* psi, void* G, float* dG,
                           float* atomic_e, float* psibar, hipStream_t s, hipEvent_t* ev, int phases);
+gmnn_status launch_network_heads(const DevModel& m, const DevSystem& sys, bool bf16, const float* dsw, int head0,
+                                 int n_heads, float* dG, hipStream_t s);
 size_t stream_lds_bytes(int hp, bool bf16, int n_heads);
 size_t stream_g_bytes(int n_atoms, bool bf16);
 size_t stream_dg_bytes(int n_atoms);
@@ -249,6 +251,7 @@ static DevModel dev_model(const gmnn_model* m) {
   d.head_w = nullptr;
   d.fwd_only = 0;
   d.h2_out = nullptr;
+  d.dsw_out = nullptr;
   return d;
 }
 
@@ -332,6 +335,35 @@ static EfLayout ef_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   L.head_w = take(4 * (size_t)packed_layout(m->hidden1, m->hidden2, m->n_heads).HP2 * sys->n_structs);
   L.bytes = off;
   return L;
+}
+
+// Scratch of the streamed per-head backwards inside an evaluation's
+// workspace: swish' [2][N][HP] in the per-pair gradients' region, and dE/dG of
+// `group` heads in the rest of it, or, where that is larger, in the G and
+// dE/dG regions (adjacent, two heads).  Groups of at most kHeadGroupBytes keep
+// dE/dG between its two kernels inside the 256 MB last-level cache.  False if
+// the list is too short to leave the room: the readout tile runs the heads
+// one after the other then.
+struct HeadScratch {
+  float* dsw = nullptr;
+  float* dG = nullptr;
+  int group = 0;
+};
+constexpr size_t kHeadGroupBytes = (size_t)192 << 20;
+static bool head_scratch(const gmnn_model* m, const gmnn_neighbors* nl, const EfLayout& L, char* W, int N, int nh,
+                         HeadScratch& hs) {
+  if (N == 0) return false;
+  const size_t HP = (size_t)packed_layout(m->hidden1, m->hidden2, m->n_heads).HP1;
+  const size_t pairs = 12 * (size_t)nl->capacity * nh, one = 4 * (size_t)kFP * N;
+  const size_t dsw = (2 * 4 * HP * N + 255) & ~size_t(255);
+  if (dsw > pairs) return false;
+  const size_t rest = (pairs - dsw) / one;
+  hs.dsw = (float*)(W + L.gpair);
+  hs.dG = rest > 2 ? (float*)(W + L.gpair + dsw) : (float*)(W + L.g);
+  // whole blocks of four heads, at least one where there is room
+  const int most = (int)std::min<size_t>(std::max<size_t>(rest, 2), std::max<size_t>(kHeadGroupBytes / one, 4));
+  hs.group = std::min(nh, most >= 4 ? most / 4 * 4 : most);
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -575,6 +607,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
     if (ev) hipEventRecord(ev[k], s);
   };
   const bool var = (flags & GMNN_WANT_FORCE_VAR) != 0;
+  const int nh = var ? m->n_heads : 1;
   Plan P;
   gmnn_plan split_plan{GMNN_SCHEDULE_SPLIT, 0, GMNN_READOUT_AUTO, 0};
   if (udd) {
@@ -593,13 +626,17 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   const bool fused = P.fused;
   const int ta = launch_tile_atoms(P.ta, bf16, N);
   const bool stream_readout = P.stream || (!fused && !var && tall_tiles(m, N));
+  // one backward per head on the streamed kernels: swish' of both layers and
+  // dE/dG of a group of heads pass through memory that is free until the pair
+  // backward (the per-pair gradients' region) or after the forward (G, dE/dG)
+  HeadScratch hs;
+  const bool stream_heads = !fused && var && head_scratch(m, nl, L, W, N, nh, hs);
   const int lpa = P.lpa;
   // the fused schedule sums each structure in one block from the tiles'
   // records; the split one from per-atom values in chunks of kReduceChunk
   const int nchunk = fused ? 1 : reduce_chunks(sys);
   const int nb_gather = (N + kPairThreads / lpa - 1) / (kPairThreads / lpa);
   const int64_t gstride = nl->capacity;
-  const int nh = var ? m->n_heads : 1;
   if (N > 0) {
     if (fused) {
       mark(0);
@@ -624,7 +661,8 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
         // structure; then the head weights c_m and the weighted W3 vectors
         DevModel da = dm;
         da.fwd_only = 1;
-        if (stream_readout)
+        if (stream_heads) da.dsw_out = hs.dsw;
+        if (stream_readout || stream_heads)
           st = launch_stream(da, ds, bf16, psi, W + L.g, (float*)(W + L.dg), atomic_e, psibar, s, nullptr, 3);
         else
           st = launch_tile(false, var, 16, da, ds, bf16, psi, atomic_e, psibar, nullptr, nullptr, gstride, nullptr, s);
@@ -649,7 +687,22 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
         // the pair counters of the chunked sums were used by pass 1's
         // reduction, which leaves them cleared
       }
-      if (stream_readout) {
+      if (stream_heads) {
+        mark(2);
+        if (!udd) {  // (the bias's first pass was this forward)
+          DevModel da = dm;
+          da.fwd_only = 1;
+          da.dsw_out = hs.dsw;
+          st = launch_stream(da, ds, bf16, psi, W + L.g, nullptr, atomic_e, nullptr, s, nullptr, 3);
+        }
+        for (int h = 0; h < nh && st == GMNN_OK; h += hs.group) {
+          const int n = std::min(hs.group, nh - h);
+          st = launch_network_heads(dm, ds, bf16, hs.dsw, h, n, hs.dG, s);
+          if (st == GMNN_OK)
+            st = launch_contract_back(N, n, psi, hs.dG, psibar + (int64_t)h * N * kS * kPacked, s);
+        }
+        for (int k = 3; k < 8; ++k) mark(k);
+      } else if (stream_readout) {
         st = launch_stream(db, ds, bf16, psi, W + L.g, (float*)(W + L.dg), atomic_e, psibar, s, ev ? ev + 2 : nullptr,
                            phases);
       } else {

@@ -85,6 +85,8 @@ struct DevModel {
   const float* head_w;
   int fwd_only;         // readout kernels stop after the energies (no backward)
   float* h2_out;        // [N][HP2] second hidden layer's activations, written when set
+  float* dsw_out;       // streamed network, when set: swish'(z1) [N][HP1], then
+                        // sigma swish'(z2) [N][HP2] (the per-head backwards start from them)
 };
 
 // System view shared by the energy kernels.

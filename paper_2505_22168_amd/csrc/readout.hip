@@ -149,7 +149,8 @@ struct NetLds {
   }
 };
 
-template <int HP, bool BF16>
+// DSW: the forward of per-head backwards (energies and swish', no backward)
+template <int HP, bool BF16, bool DSW>
 __global__ void __launch_bounds__(kRoThreads)
     readout_network(DevModel m, DevSystem sys, const void* __restrict__ G, float* __restrict__ atomic_e,
                     float* __restrict__ dG) {
@@ -287,6 +288,11 @@ __global__ void __launch_bounds__(kRoThreads)
           d[j] = dj;
         }
         if (m.h2_out && row < n_rows) *(floatx4*)(m.h2_out + (int64_t)(row0 + row) * HP + col) = acc[r][i];
+        if (DSW && row < n_rows) {
+          float* o = m.dsw_out + (int64_t)(row0 + row) * HP + col;
+          *(floatx4*)o = dsw1[r][i];
+          *(floatx4*)(o + (int64_t)sys.n_atoms * HP) = d * sScale[row];
+        }
         const floatx4 wr = m.head_w ? *(const floatx4*)(m.head_w + (int64_t)sStruct[row] * HP + col) : wb;
         st4<NBK>(sB, PH, row * L::H + col, d * sScale[row] * wr);
       }
@@ -342,7 +348,7 @@ __global__ void __launch_bounds__(kRoThreads)
     }
   }
   // forward-only pass (the energies an uncertainty bias needs first)
-  if (m.fwd_only) return;
+  if (DSW || m.fwd_only) return;
 
   // delta1 = swish'(z1) (delta2 W2^T) -> region A (h1 is dead)
   {
@@ -391,6 +397,135 @@ __global__ void __launch_bounds__(kRoThreads)
 }
 
 // ---------------------------------------------------------------------------
+// The network's backward for several heads (Section 2.2: the heads share
+// everything but W3): rows are (head, atom), row block r the 16 atoms of the
+// tile under head h0 + r, so swish' of both layers is loaded once for all
+// heads and every weight fragment feeds HB row blocks.
+//   delta2 = sigma swish'(z2) W3[:, h], delta1 = swish'(z1) (delta2 W2^T),
+//   dE/dG = delta1 W1^T -> dG [head][...] (dg_index)
+// What bounds it: the latency of the weights from L2 and of W3's column, at
+// two blocks a CU (28,160 atoms, 2x256 BF16: 89 us for four heads, four times
+// for 16).  With its forward (97 us) and the invariant backward (4 x 68 us)
+// it replaces the readout tile, which ran the heads of an atom one after the
+// other, the invariant backward between them (1313 us).
+template <int HP, bool BF16>
+struct HeadsLds {
+  static constexpr int NP = BF16 ? 1 : 3;
+  static constexpr int HB = !BF16 && HP >= 512 ? 2 : 4;  // heads per block
+  static constexpr int H = HP + 8;
+  static constexpr size_t part = (size_t)16 * HB * H;
+  static constexpr size_t bytes = 2 * NP * part;
+};
+
+template <int HP, bool BF16>
+__global__ void __launch_bounds__(kRoThreads)
+    network_heads(DevModel m, int n_atoms, const float* __restrict__ dsw, int head0, int n_heads,
+                  float* __restrict__ dG) {
+  using L = HeadsLds<HP, BF16>;
+  constexpr int NP = L::NP, MB = L::HB, NW = kRoWaves;
+  constexpr int NBH = HP / 16, NBG = kFP / 16;
+  constexpr int TPW = (NBH + NW - 1) / NW, TPW_G = (NBG + NW - 1) / NW;
+  constexpr int PH = (int)L::part;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __bf16* sT = (__bf16*)lds;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int row0 = xcd_block(blockIdx.x, gridDim.x) * 16;
+  const int n_rows = min(16, n_atoms - row0);
+  const int hb = blockIdx.y * MB, nh = min(MB, n_heads - hb);  // heads of this block, from head0 + hb
+  const int ar = l & 15, uq = 4 * (l >> 4);
+  RowsRing<NP, TPW> ring;
+  RowsRing<NP, TPW_G> ring_g;
+  rows_pre<NP, TPW>(ring, m.w2t, HP / 32, w, NW, NBH);
+  floatx4 dsw1[TPW];
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) {
+    if (!has_block(i, w, NW, NBH)) continue;
+    const int col = (w + i * NW) * 16 + uq;
+    floatx4 d2 = {0.0f, 0.0f, 0.0f, 0.0f};
+    dsw1[i] = d2;
+    if (ar < n_rows) {
+      const float* p = dsw + (int64_t)(row0 + ar) * HP + col;
+      dsw1[i] = *(const floatx4*)p;
+      d2 = *(const floatx4*)(p + (int64_t)n_atoms * HP);
+    }
+#pragma unroll
+    for (int r = 0; r < MB; ++r) {
+      floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (r < nh)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = d2[j] * m.w3[(col + j) * m.M + head0 + hb + r];
+      st4<NP>(sT, PH, (r * 16 + ar) * L::H + col, v);
+    }
+  }
+  lds_barrier();
+  {
+    floatx4 acc[MB][TPW];
+    zero_rows(acc);
+    mma_rows<NP>(ring, sT, PH, L::H, m.w2t, HP / 32, w, NW, NBH, acc);
+    rows_pre<NP, TPW_G>(ring_g, m.w1t, HP / 32, w, NW, NBG);
+    lds_barrier();  // every wave is done with delta2, which delta1 replaces
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+      if (!has_block(i, w, NW, NBH)) continue;
+#pragma unroll
+      for (int r = 0; r < MB; ++r)
+        st4<NP>(sT, PH, (r * 16 + ar) * L::H + (w + i * NW) * 16 + uq, acc[r][i] * dsw1[i]);
+    }
+  }
+  lds_barrier();
+  {
+    floatx4 acc[MB][TPW_G];
+    zero_rows(acc);
+    mma_rows<NP, MB, TPW_G, true>(ring_g, sT, PH, L::H, m.w1t, HP / 32, w, NW, NBG, acc);
+    const bool whole = n_atoms - row0 / kDgRun * kDgRun >= kDgRun;  // a whole run: 16-byte aligned rows
+#pragma unroll
+    for (int i = 0; i < TPW_G; ++i) {
+      if (!has_block(i, w, NW, NBG)) continue;
+      if (uq >= n_rows) continue;
+      const int64_t o = dg_index(n_atoms, row0 + uq, (w + i * NW) * 16 + ar);
+#pragma unroll
+      for (int r = 0; r < MB; ++r) {
+        if (r >= nh) continue;
+        float* p = dG + (int64_t)(hb + r) * n_atoms * kFP + o;
+        if (whole) {
+          *(floatx4*)p = acc[r][i];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (uq + j < n_rows) p[j] = acc[r][i][j];
+        }
+      }
+    }
+  }
+}
+
+template <int HP, bool BF16>
+static gmnn_status launch_heads_t(const DevModel& m, const DevSystem& sys, const float* dsw, int head0, int n_heads,
+                                  float* dG, hipStream_t s) {
+  using L = HeadsLds<HP, BF16>;
+  static_assert(L::bytes <= 160 * 1024, "the tile fits the LDS");
+  const gmnn_status st = ensure_lds_limit((const void*)network_heads<HP, BF16>, L::bytes);
+  if (st != GMNN_OK) return st;
+  hipLaunchKernelGGL((network_heads<HP, BF16>), dim3((sys.n_atoms + 15) / 16, (n_heads + L::HB - 1) / L::HB),
+                     dim3(kRoThreads), L::bytes, s, m, sys.n_atoms, dsw, head0, n_heads, dG);
+  return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
+}
+
+// dE/dG of heads head0 .. head0 + n_heads - 1 (n_heads arrays, one after the
+// other), from the forward's swish' values (DevModel::dsw_out)
+gmnn_status launch_network_heads(const DevModel& m, const DevSystem& sys, bool bf16, const float* dsw, int head0,
+                                 int n_heads, float* dG, hipStream_t s) {
+  if (sys.n_atoms == 0 || n_heads == 0) return GMNN_OK;
+#define CASE(HP)                                                                     \
+  if (m.HP1 == HP)                                                                   \
+    return bf16 ? launch_heads_t<HP, true>(m, sys, dsw, head0, n_heads, dG, s)       \
+                : launch_heads_t<HP, false>(m, sys, dsw, head0, n_heads, dG, s);
+  CASE(64) CASE(128) CASE(256) CASE(512)
+#undef CASE
+  return GMNN_ERR_UNSUPPORTED;
+}
+
+// ---------------------------------------------------------------------------
 constexpr size_t kLdsMax = 160 * 1024;
 
 // phases: bit 0 invariants, bit 1 network, bit 2 invariant backward
@@ -403,7 +538,8 @@ static gmnn_status launch_stream_t(const DevModel& m, const DevSystem& sys, cons
   using NL = NetLds<HP, BF16>;
   if (NL::bytes(m.M) > kLdsMax) return GMNN_ERR_UNSUPPORTED;
   gmnn_status st = ensure_lds_limit((const void*)readout_features<BF16>, FeatLds<BF16>::bytes);
-  if (st == GMNN_OK) st = ensure_lds_limit((const void*)readout_network<HP, BF16>, NL::bytes(m.M));
+  auto network = m.dsw_out ? readout_network<HP, BF16, true> : readout_network<HP, BF16, false>;
+  if (st == GMNN_OK) st = ensure_lds_limit((const void*)network, NL::bytes(m.M));
   if (st != GMNN_OK) return st;
   const int N = sys.n_atoms;
   const int g16 = (N + kRoAtoms - 1) / kRoAtoms;
@@ -414,7 +550,7 @@ static gmnn_status launch_stream_t(const DevModel& m, const DevSystem& sys, cons
   mark(1);
   mark(2);
   if (phases & 2)
-    hipLaunchKernelGGL((readout_network<HP, BF16>), dim3(gn), dim3(kRoThreads), NL::bytes(m.M), s, m, sys,
+    hipLaunchKernelGGL(network, dim3(gn), dim3(kRoThreads), NL::bytes(m.M), s, m, sys,
                        (const void*)G, atomic_e, dG);
   mark(3);
   mark(4);
