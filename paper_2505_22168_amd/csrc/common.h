@@ -94,6 +94,19 @@ __device__ inline void split3(float v, __bf16& h, __bf16& m, __bf16& l) {
   l = (__bf16)(r - (float)m);
 }
 
+// split3 of two values at once: the parts come out packed, and one conversion
+// makes both parts of a pair (three conversions instead of nine)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ inline void split3_pair(float a, float b, bf16x2& h, bf16x2& m, bf16x2& l) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  asm("" : "+v"(a));  // as in split_low
+  asm("" : "+v"(b));
+  h = __builtin_convertvector((f32x2{a, b}), bf16x2);
+  const float ra = a - (float)h[0], rb = b - (float)h[1];
+  m = __builtin_convertvector((f32x2{ra, rb}), bf16x2);
+  l = __builtin_convertvector((f32x2{ra - (float)m[0], rb - (float)m[1]}), bf16x2);
+}
+
 // ---------------------------------------------------------------------------
 // wave-level helpers
 // ---------------------------------------------------------------------------

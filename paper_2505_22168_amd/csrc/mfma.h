@@ -44,22 +44,27 @@ struct Split3 {
 __device__ __forceinline__ Split3 split3x8(floatx4 a, floatx4 b) {
   Split3 s;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    __bf16 h, m, l;
-    split3(e < 4 ? a[e & 3] : b[e & 3], h, m, l);
-    s.h[e] = h;
-    s.m[e] = m;
-    s.l[e] = l;
+  for (int e = 0; e < 8; e += 2) {
+    const floatx4 v = e < 4 ? a : b;
+    bf16x2 h, m, l;
+    split3_pair(v[e & 3], v[(e & 3) + 1], h, m, l);
+    s.h[e] = h[0]; s.h[e + 1] = h[1];
+    s.m[e] = m[0]; s.m[e + 1] = m[1];
+    s.l[e] = l[0]; s.l[e + 1] = l[1];
   }
   return s;
 }
 
-// one k-step of N FP32 products, sum[n] += x(n) y(n), smallest part products
-// first from zero, then added to the sum in FP32 (rounded to nearest: the
-// MFMA's own accumulation of a long sum was measured to bias it towards zero
-// by up to 1e-6).  The N chains are interleaved: an MFMA waits for the one
-// before it in its own chain.  SWAP: y is the MFMA's A operand (the order of
-// the part products stays, so both orientations agree bit for bit).
+// one k-step of N FP32 products, t[n] = x(n) y(n): the five smaller part
+// products, smallest first from zero, and the largest from zero, added in FP32.
+// An MFMA aligns the sum it adds to with its products and drops what falls
+// below (towards minus infinity), so a long sum kept in it drifts: by 1e-6 of
+// a force over a whole product, and still by 2e-9 of the terms, which doubles
+// the error of a solid's stress, where only the largest part of a step adds
+// to the smaller ones' sum; apart, by less than 5e-11.  The N chains are
+// interleaved: an MFMA waits for the one before it in its own chain.  SWAP: y
+// is the MFMA's A operand (the order of the part products stays, so both
+// orientations agree bit for bit).
 template <bool SWAP = false, int N, typename X, typename Y>
 __device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
 #define GMNN_PART(PX, PY, FROM)                                                                           \
@@ -71,8 +76,11 @@ __device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
   GMNN_PART(m, m, t[n]);
   GMNN_PART(m, h, t[n]);
   GMNN_PART(h, m, t[n]);
-  GMNN_PART(h, h, t[n]);
 #undef GMNN_PART
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+    t[n] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(SWAP ? y(n).h : x(n).h, SWAP ? x(n).h : y(n).h,
+                                                    (floatx4{0.0f, 0.0f, 0.0f, 0.0f}), 0, 0, 0);
 }
 template <bool SWAP = false, int N, typename X, typename Y>
 __device__ __forceinline__ void mma_six(floatx4 (&sum)[N], X x, Y y) {

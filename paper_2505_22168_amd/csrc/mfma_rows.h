@@ -125,15 +125,18 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 template <int NP>
 __device__ __forceinline__ void st4(__bf16* base, int part, int idx, floatx4 v) {
   bf16x4 o[3];
+  if constexpr (NP == 3) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if constexpr (NP == 3) {
-      __bf16 h, m, l;
-      split3(v[j], h, m, l);
-      o[0][j] = h;
-      o[1][j] = m;
-      o[2][j] = l;
-    } else {
+    for (int j = 0; j < 4; j += 2) {
+      bf16x2 h, m, l;
+      split3_pair(v[j], v[j + 1], h, m, l);
+      o[0][j] = h[0]; o[0][j + 1] = h[1];
+      o[1][j] = m[0]; o[1][j + 1] = m[1];
+      o[2][j] = l[0]; o[2][j + 1] = l[1];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
       o[0][j] = (__bf16)v[j];
       if constexpr (NP == 2) o[1][j] = (__bf16)split_low(v[j], o[0][j]);
     }
