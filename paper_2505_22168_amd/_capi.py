@@ -32,6 +32,7 @@ GMNN_WANT_FORCE_VAR = 4
 GMNN_SYNC = 8
 GMNN_BACKWARD_LANES16 = 16
 GMNN_BACKWARD_PER_HEAD = 32
+GMNN_HEADS_TILE = 64
 GMNN_LOSS_MSE, GMNN_LOSS_NLL, GMNN_LOSS_CRPS = 0, 1, 2
 GMNN_GROUP_EMBEDDING, GMNN_GROUP_NN, GMNN_GROUP_SCALE, GMNN_GROUP_SHIFT = 0, 1, 2, 3
 GMNN_LR_CONSTANT, GMNN_LR_LINEAR, GMNN_LR_COSINE = 0, 1, 2

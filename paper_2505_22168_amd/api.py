@@ -674,6 +674,10 @@ class EnsembleTrainer:
         self.energy_ref = torch.as_tensor(energy_ref, dtype=torch.float64, device=dev).contiguous()
         self.forces_ref = torch.as_tensor(forces_ref, dtype=torch.float32, device=dev).reshape(-1, 3).contiguous()
         self.ev = EnergyForces(model, system, nl, precision=precision, stress=False, force_var=True, plan=plan)
+        if precision == "bf16":
+            # Adam's first steps turn a last-bit change of the forces into 5e-4 of the next gradients
+            # (the BF16 operands of the double backward round to the other side)
+            self.ev.flags |= A.GMNN_HEADS_TILE
         self.grads = {k: torch.empty_like(v) for k, v in model.tensors.items()}
         lib = A.load()
         mc, sc, nc = model.c(), system.c(), nl.c()

@@ -21,11 +21,13 @@ template <int LPA>
 __global__ void pair_backward(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* virial);
 __global__ void pair_backward_heads(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* virial, int nh,
                                     int64_t gstride, const float* head_c);
-template <int LPA, bool VAR>
+__global__ void pair_backward_rows(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* own,
+                                   float* virial, int nh, const float* head_c);
+template <int LPA, int VAR>
 __global__ void finish(int M, DevSystem sys, const float* gpair, const float* atomic_e, const float* virial,
-                       int want_stress, int nb_gather, int64_t gstride, int nchunk, double* partial, int* counters,
-                       float* forces, float* force_var, double* energy, double* energy_var, double* energy_mean,
-                       double* stress, const double* tile_part, int tile_atoms, const float* head_c,
+                       int want_stress, int nb_gather, int64_t gstride, const float* own, int nchunk, double* partial,
+                       int* counters, float* forces, float* force_var, double* energy, double* energy_var,
+                       double* energy_mean, double* stress, const double* tile_part, int tile_atoms, const float* head_c,
                        float* forces_heads);
 gmnn_status launch_tile(bool fused, bool perhead, int tile_atoms, const DevModel& m, const DevSystem& sys, bool bf16,
                         const float* psi, float* atomic_e, float* psibar, float* gpair, float* virial,
@@ -306,7 +308,7 @@ static DevSystem dev_system(const gmnn_system* s, const gmnn_neighbors* nl) {
 }
 
 struct EfLayout {
-  size_t psi = 0, psibar = 0, atomic_e = 0, gpair = 0, virial = 0, g = 0, dg = 0, partial = 0, counters = 0,
+  size_t psi = 0, psibar = 0, atomic_e = 0, gpair = 0, own = 0, virial = 0, g = 0, dg = 0, partial = 0, counters = 0,
          tilerec = 0, head_c = 0, head_w = 0, bytes = 0;
 };
 
@@ -324,6 +326,7 @@ static EfLayout ef_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   L.psibar = take(4 * N * kS * kPacked * nh);
   L.atomic_e = take(4 * N * (size_t)m->n_heads);
   L.gpair = take(12 * (size_t)nl->capacity * nh);
+  L.own = (flags & GMNN_WANT_FORCE_VAR) ? take(12 * N * nh) : 0;  // the rows' sums of gpair, [N][nh][3]
   L.virial = take(4 * 9 * N);
   L.g = take(stream_g_bytes((int)N, (flags & GMNN_PREC_BF16) != 0));
   L.dg = take(stream_dg_bytes((int)N));
@@ -592,6 +595,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   float* psibar = (float*)(W + L.psibar);
   float* atomic_e = out->atomic_energy ? out->atomic_energy : (float*)(W + L.atomic_e);
   float* gpair = (float*)(W + L.gpair);
+  float* own = (flags & GMNN_WANT_FORCE_VAR) ? (float*)(W + L.own) : nullptr;
   float* virial = (float*)(W + L.virial);
   double* partial = (double*)(W + L.partial);
   int* counters = (int*)(W + L.counters);
@@ -626,11 +630,25 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   const bool fused = P.fused;
   const int ta = launch_tile_atoms(P.ta, bf16, N);
   const bool stream_readout = P.stream || (!fused && !var && tall_tiles(m, N));
-  // one backward per head on the streamed kernels: swish' of both layers and
-  // dE/dG of a group of heads pass through memory that is free until the pair
-  // backward (the per-pair gradients' region) or after the forward (G, dE/dG)
+  // One backward per head.  Readout: the tile runs an atom's heads one after
+  // the other, the streamed kernels several at a time, with swish' of both
+  // layers and dE/dG of a group of heads in memory that is free until the pair
+  // backward (the per-pair gradients' region) or after the forward (G, dE/dG).
+  // Streaming wins from kManyHeads heads on at any size (2x128 BF16, 8 heads:
+  // 87.6 against 125 us at 64 atoms, 264 against 318 at 8192), and below that
+  // once the tile needs a second round of the compute units (4 heads: 191
+  // against 207 us at 8192 atoms, but 134 against 113 at 4096); three heads
+  // and less in FP32 stay on the tile (2x256, 3 heads: 267 against 237 us).
+  // Pair backward: the matrix form has 16 rows whatever the heads, the lane
+  // form's time grows with them; they meet at kManyHeads (28,160 atoms, 2x128
+  // BF16, evaluation: 6 heads 767 against 634 us, 8 heads 796 against 800, 16
+  // heads 1127 against 1451).
+  constexpr int kManyHeads = 8;
+  const bool heads_free = !fused && var && !(flags & GMNN_HEADS_TILE);
+  const bool rows = heads_free && nh >= kManyHeads;
   HeadScratch hs;
-  const bool stream_heads = !fused && var && head_scratch(m, nl, L, W, N, nh, hs);
+  const bool stream_heads = heads_free && (rows || (N > 16 * kComputeUnits && (bf16 || nh >= 4))) &&
+                            head_scratch(m, nl, L, W, N, nh, hs);
   const int lpa = P.lpa;
   // the fused schedule sums each structure in one block from the tiles'
   // records; the split one from per-atom values in chunks of kReduceChunk
@@ -670,10 +688,10 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
         const dim3 rgrid(sys->n_structs * nchunk);
 #define FINISH_REDUCE(VAR)                                                                                      \
   hipLaunchKernelGGL((finish<64, VAR>), rgrid, dim3(kPairThreads), 0, s, m->n_heads, ds, gpair, atomic_e, virial,  \
-                     0, 0, gstride, nchunk, partial, counters, out->forces, out->force_var, out->energy,           \
+                     0, 0, gstride, nullptr, nchunk, partial, counters, out->forces, out->force_var, out->energy,  \
                      out->energy_var, out->energy_mean, out->stress, nullptr, 0, nullptr, nullptr)
-        if (var) FINISH_REDUCE(true);
-        else FINISH_REDUCE(false);
+        if (var) FINISH_REDUCE(kGatherHeads);
+        else FINISH_REDUCE(0);
 #undef FINISH_REDUCE
         hipLaunchKernelGGL(udd_weights, dim3((sys->n_structs + 63) / 64), dim3(64), 0, s, sys->n_structs, m->n_heads,
                            sys->atom_ptr, out->energy, (double)udd->A, (double)udd->B, head_c, udd->bias_energy);
@@ -718,13 +736,17 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
 #define PAIR_BACKWARD(LPA)                                                                                 \
   hipLaunchKernelGGL(pair_backward<LPA>, dim3(nb_gather), dim3(kPairThreads), beta_lds, s, dm, ds, psibar, gpair, \
                      virial)
-      if (nh > 1) {
+      if (nh > 1 && !rows) {
         // one backward per head: every pair's geometry serves all heads
         const size_t lds = beta_lds + sizeof(float) * kHeadsAtoms * (size_t)nh * kS * kPacked;
         st = ensure_lds_limit((const void*)pair_backward_heads, lds);
         if (st != GMNN_OK) return st;
         hipLaunchKernelGGL(pair_backward_heads, dim3((N + kHeadsAtoms - 1) / kHeadsAtoms), dim3(kPairThreads), lds,
                            s, dm, ds, psibar, gpair, virial, nh, gstride, udd ? head_c : nullptr);
+      } else if (rows) {
+        const size_t lds = sizeof(float) * kHeadsAtoms * (size_t)m->n_species * kS * kMaxBasis;
+        hipLaunchKernelGGL(pair_backward_rows, dim3((N + kHeadsAtoms - 1) / kHeadsAtoms), dim3(kPairThreads), lds,
+                           s, dm, ds, psibar, gpair, own, virial, nh, udd ? head_c : nullptr);
       } else if (lpa == 64) PAIR_BACKWARD(64);
       else if (lpa == 32) PAIR_BACKWARD(32);
       else if (lpa == 16) PAIR_BACKWARD(16);
@@ -735,26 +757,22 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   }
   mark(10);
   const int want_stress = (flags & GMNN_WANT_STRESS) ? 1 : 0;
-  const int nbg = N > 0 ? nb_gather : 0;
+  const int nbg = N == 0 ? 0 : rows ? (N + kHeadsAtoms - 1) / kHeadsAtoms : nb_gather;
   const dim3 fgrid(nbg + sys->n_structs * nchunk);
 #define FINISH(LPA, VAR)                                                                                       \
   hipLaunchKernelGGL((finish<LPA, VAR>), fgrid, dim3(kPairThreads), 0, s, m->n_heads, ds, gpair, atomic_e, virial, \
-                     want_stress, nbg, gstride, nchunk, partial, counters, out->forces, out->force_var, out->energy, \
-                     out->energy_var, out->energy_mean, out->stress, fused ? tilerec : nullptr, fused ? ta : 0, \
-                     (udd && var) ? head_c : nullptr, var ? out->forces_heads : nullptr)
-  if (lpa == 64) {
-    if (var) FINISH(64, true);
-    else FINISH(64, false);
-  } else if (lpa == 32) {
-    if (var) FINISH(32, true);
-    else FINISH(32, false);
-  } else if (lpa == 16) {
-    if (var) FINISH(16, true);
-    else FINISH(16, false);
-  } else {
-    if (var) FINISH(8, true);
-    else FINISH(8, false);
-  }
+                     want_stress, nbg, gstride, own, nchunk, partial, counters, out->forces, out->force_var,        \
+                     out->energy, out->energy_var, out->energy_mean, out->stress, fused ? tilerec : nullptr,        \
+                     fused ? ta : 0, (udd && var) ? head_c : nullptr, var ? out->forces_heads : nullptr)
+  if (rows) FINISH(64, kGatherRecords);
+  else if (lpa == 64 && var) FINISH(64, kGatherHeads);
+  else if (lpa == 64) FINISH(64, 0);
+  else if (lpa == 32 && var) FINISH(32, kGatherHeads);
+  else if (lpa == 32) FINISH(32, 0);
+  else if (lpa == 16 && var) FINISH(16, kGatherHeads);
+  else if (lpa == 16) FINISH(16, 0);
+  else if (var) FINISH(8, kGatherHeads);
+  else FINISH(8, 0);
 #undef FINISH
   mark(11);
   if (hipGetLastError() != hipSuccess) return GMNN_ERR_HIP;

@@ -9,7 +9,9 @@
 namespace gmnn {
 
 constexpr int kPairBlock = 256;  // threads per block of the pair kernels
-constexpr int kHeadsAtoms = kPairBlock / 64;  // atoms per block of the per-head pair backward
+constexpr int kHeadsAtoms = kPairBlock / 64;  // atoms per block of the per-head pair backwards
+// gradients the gather (finish) reads: one head's, one set per head, one record per pair
+constexpr int kGatherHeads = 1, kGatherRecords = 2;
 
 // --- DPP lane exchanges inside rows of 16 lanes ----------------------------
 __device__ inline float dpp_mirror(float v) {  // lane 15 - l

@@ -23,6 +23,7 @@
 // per lane group in LDS (the list's skin pairs do not occupy lanes).
 #include "common.h"
 #include "model.h"
+#include "mfma.h"
 #include "pair_math.h"
 
 namespace gmnn {
@@ -138,11 +139,279 @@ __global__ void __launch_bounds__(kPairBlock) pair_backward_heads(DevModel m, De
 }
 
 // ---------------------------------------------------------------------------
+// One backward per head: a pair's gradients under all heads are one matrix
+// product.  dE^h/dd_p is linear in pb^h = dE_i^h/dPsi_i (pair_gradient):
+//   radial part  A^h = sum_{s,t} pb^h[s][t] dR_s mono_t(u)            (K = 100)
+//   grad Q^h, c  G^h = sum_{s,m} f pb^h[s][t(c, m)] R_s mono_m(u)     (K = 50)
+// over the ten monomials m of degree <= 2, d mono_t / dx_c = f mono_m.  Rows
+// are the heads (up to 16), columns 16 pairs of the atom: the atom's
+// coefficients stay in registers as MFMA operands, the pairs' products
+// dR_s mono_t and R_s mono_m are formed in the lanes that hold their column,
+// both in three exact BF16 parts (six products a step, as the network's FP32
+// products).  Quarter uq of a wave holds five of the twenty monomials (its
+// first two or three of degree <= 2), so K is 4 * (25 of 32) and 4 * (15 of
+// 16) and no lane forms another's products.
+// A wave takes an atom: its pairs inside r_c are queued (ring_append), up to
+// 64 at a time get their radial functions one pair per lane, and run as
+// blocks of 16 columns.  Gradients go out head-interleaved, gpair[p][h][3]
+// (192 contiguous bytes a pair at 16 heads), and their sum over the row to
+// own[i][h][3], so the gather reads the reverse pairs only.
+// What bounds it: the VALU work of forming and splitting the pairs' products
+// and, once an atom, its coefficients, at two waves a SIMD (28,160 atoms, 16
+// heads: 259 us against 471 us one pair per lane; the gather 102 against 180).
+// head_c (may be null): per-structure head weights [B][kMaxHeads] of the
+// virial (an uncertainty bias); null: the mean over heads
+struct RowsWave {
+  static constexpr int kPbStride = kS * kPacked + 1;  // odd: the 16 heads of a column read fall in 16 banks
+  union {
+    struct {
+      float4 ring[kRingBatches * 64];
+      float4 batch[4][64];
+    };
+    float pb[kMaxHeads * kPbStride];  // until the operands are formed
+  };
+};
+
+// v[uq] of four compile-time values
+template <typename T>
+__device__ __forceinline__ T of_quarter(int uq, T a, T b, T c, T d) {
+  return uq < 2 ? (uq ? b : a) : (uq == 2 ? c : d);
+}
+
+// an operand fragment of the first `n` <= 8 values, zeros after them
+template <int n, typename F>
+__device__ __forceinline__ Split3 split3_of(F value) {
+  Split3 s;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    bf16x2 h = {}, m = {}, l = {};
+    if (e < n) split3_pair(value(e), e + 1 < n ? value(e + 1) : 0.0f, h, m, l);
+    s.h[e] = h[0]; s.h[e + 1] = h[1];
+    s.m[e] = m[0]; s.m[e + 1] = m[1];
+    s.l[e] = l[0]; s.l[e + 1] = l[1];
+  }
+  return s;
+}
+
+__global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu(2)))
+    pair_backward_rows(DevModel m, DevSystem sys, const float* __restrict__ psibar, float* __restrict__ gpair,
+                        float* __restrict__ own, float* __restrict__ virial, int nh,
+                        const float* __restrict__ head_c) {
+  extern __shared__ float s_beta[];
+  __shared__ RowsWave s_wave[kHeadsAtoms];
+  constexpr int NP = kS * kPacked;
+  const int w = threadIdx.x >> 6, q = threadIdx.x & 63;
+  const int col = q & 15, uq = q >> 4;
+  const int i = xcd_block(blockIdx.x, gridDim.x) * kHeadsAtoms + w;
+  const bool live = i < sys.n_atoms;
+  RowsWave& S = s_wave[w];
+  if (!live) return;
+  // every load of the atom is issued before the first use: the coefficients
+  // (nh runs of 100), its context, the first pairs' indices, beta
+  constexpr int kLoads = (kMaxHeads * NP / 4 + 63) / 64;
+  float4 ld[kLoads];
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+    const int t = min(q + 64 * u, nh * (NP / 4) - 1);
+    ld[u] = *(const float4*)(psibar + ((int64_t)(t / (NP / 4)) * sys.n_atoms + i) * NP + 4 * (t % (NP / 4)));
+  }
+  AtomCtx c;
+  load_atom(sys, i, c);
+  const CandIdx first = cand_index(sys, c, c.p0 + q);
+  // beta of the atom's species with every neighbour species, [zj][s][kMaxBasis]
+  const int nbz = m.n_species * kS * kMaxBasis;
+  float* bzi = s_beta + w * nbz;
+  const float* beta = m.beta + (int64_t)c.zsp * m.n_species * kS * m.K;
+#pragma unroll 4
+  for (int t = q; t < nbz; t += 64) {
+    const int k = t % kMaxBasis;
+    bzi[t] = k < m.K ? beta[t / kMaxBasis * m.K + k] : 0.0f;
+  }
+  Cand cur = cand_fetch(sys, c, c.p0 + q, first);
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+    const int t = q + 64 * u;
+    float* o = S.pb + t / (NP / 4) * RowsWave::kPbStride + 4 * (t % (NP / 4));
+    if (t < nh * (NP / 4)) {
+      o[0] = ld[u].x; o[1] = ld[u].y; o[2] = ld[u].z; o[3] = ld[u].w;
+    } else if (t < kMaxHeads * (NP / 4)) {
+      o[0] = o[1] = o[2] = o[3] = 0.0f;  // rows past the heads
+    }
+  }
+  wave_lds_sync();
+  CandIdx nxt = cand_index(sys, c, c.p0 + 64 + q);
+
+  // the atom's operands: row col = head, monomials of quarter uq
+  Split3 A[4], Q[3][2];
+  {
+    const float* pb = S.pb + col * RowsWave::kPbStride;
+    const int t[5] = {of_quarter(uq, 0, 3, 6, 8), of_quarter(uq, 1, 4, 7, 9), of_quarter(uq, 2, 5, 14, 17),
+                      of_quarter(uq, 10, 12, 15, 18), of_quarter(uq, 11, 13, 16, 19)};
+    auto a = [&](int k) { return pb[k / 5 * kPacked + t[k % 5]]; };
+#pragma unroll
+    for (int ks = 0; ks < 3; ++ks) A[ks] = split3_of<8>([&](int e) { return a(8 * ks + e); });
+    A[3] = split3_of<1>([&](int) { return a(24); });
+    // t(c, m) and f for m = 0 .. 9: 1, x y z, xx xy xz yy yz zz (f = 0: the
+    // third monomial of two quarters is of degree 3)
+    const int td[3][3] = {{of_quarter(uq, 1, 6, 12, 14), of_quarter(uq, 4, 10, 13, 15), of_quarter(uq, 5, 11, 0, 0)},
+                          {of_quarter(uq, 2, 8, 14, 17), of_quarter(uq, 5, 11, 16, 18), of_quarter(uq, 7, 13, 0, 0)},
+                          {of_quarter(uq, 3, 9, 15, 18), of_quarter(uq, 6, 12, 17, 19), of_quarter(uq, 8, 14, 0, 0)}};
+    const float fd[3][3] = {{of_quarter(uq, 1.0f, 1.0f, 2.0f, 1.0f), of_quarter(uq, 2.0f, 3.0f, 1.0f, 1.0f),
+                             of_quarter(uq, 1.0f, 2.0f, 0.0f, 0.0f)},
+                            {of_quarter(uq, 1.0f, 1.0f, 1.0f, 2.0f), of_quarter(uq, 1.0f, 1.0f, 3.0f, 1.0f),
+                             of_quarter(uq, 2.0f, 2.0f, 0.0f, 0.0f)},
+                            {of_quarter(uq, 1.0f, 2.0f, 2.0f, 2.0f), of_quarter(uq, 1.0f, 1.0f, 1.0f, 3.0f),
+                             of_quarter(uq, 1.0f, 1.0f, 0.0f, 0.0f)}};
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      auto v = [&](int k) { return fd[x][k % 3] * pb[k / 3 * kPacked + td[x][k % 3]]; };
+      Q[x][0] = split3_of<8>(v);
+      Q[x][1] = split3_of<7>([&](int e) { return v(8 + e); });
+    }
+  }
+  wave_lds_sync();  // the ring takes the coefficients' place
+  float hw[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    hw[j] = 4 * uq + j >= nh ? 0.0f : head_c ? head_c[(int64_t)sys.atom_struct[i] * kMaxHeads + 4 * uq + j] : 1.0f;
+  const bool quads = (nh & 3) == 0;
+  float vir[9], sum[12];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) vir[k] = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) sum[k] = 0.0f;
+
+  int head = 0, tail = 0;
+  auto run_batch = [&]() {
+    const int take = min(tail - head, 64);
+    if (q < take) {
+      const float4 e = S.ring[(head + q) & (kRingBatches * 64 - 1)];
+      const int tag = __float_as_int(e.w);
+      const float r2 = e.x * e.x + e.y * e.y + e.z * e.z;
+      float r, ir;
+      length_of(r2, r, ir);
+      Radial rad;
+      radial<true>(m, bzi + (tag & ((1 << kRingTagBits) - 1)) * kS * kMaxBasis, r, rad);
+      S.batch[0][q] = make_float4(rad.R[0], rad.R[1], rad.R[2], rad.R[3]);
+      S.batch[1][q] = make_float4(rad.R[4], rad.dR[0], rad.dR[1], rad.dR[2]);
+      S.batch[2][q] = make_float4(rad.dR[3], rad.dR[4], ir, r);
+      S.batch[3][q] = make_float4(e.x * ir, e.y * ir, e.z * ir, __int_as_float(tag >> kRingTagBits));
+    }
+    head += take;
+    wave_lds_sync();
+#pragma unroll 1
+    for (int c0 = 0; c0 < take; c0 += 16) {
+      const float4 b0 = S.batch[0][c0 + col], b1 = S.batch[1][c0 + col], b2 = S.batch[2][c0 + col],
+                   b3 = S.batch[3][c0 + col];
+      const float R[kS] = {b0.x, b0.y, b0.z, b0.w, b1.x}, dR[kS] = {b1.y, b1.z, b1.w, b2.x, b2.y};
+      const float x = b3.x, y = b3.y, z = b3.z, ir = b2.z, r = b2.w;
+      // this quarter's monomials: {1, x, y, xxx, xxy}, {z, xx, xy, xxz, xyy},
+      // {xz, yy, xyz, xzz, yyy}, {yz, zz, yyz, yzz, zzz}
+      float mo[20];
+      monomials(x, y, z, mo);
+      float mq[5];
+      mq[0] = of_quarter(uq, mo[0], mo[3], mo[6], mo[8]);
+      mq[1] = of_quarter(uq, mo[1], mo[4], mo[7], mo[9]);
+      mq[2] = of_quarter(uq, mo[2], mo[5], mo[14], mo[17]);
+      mq[3] = of_quarter(uq, mo[10], mo[12], mo[15], mo[18]);
+      mq[4] = of_quarter(uq, mo[11], mo[13], mo[16], mo[19]);
+      floatx4 ta[4], g[3], radial_part;
+      {
+        auto v = [&](int k) { return dR[k / 5] * mq[k % 5]; };
+        Split3 B[4];
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks) B[ks] = split3_of<8>([&](int e) { return v(8 * ks + e); });
+        B[3] = split3_of<1>([&](int) { return v(24); });
+        six_products(ta, [&](int n) -> const Split3& { return A[n]; }, [&](int n) -> const Split3& { return B[n]; });
+      }
+      radial_part = (ta[0] + ta[1]) + (ta[2] + ta[3]);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) g[a] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        auto v = [&](int e) { return R[(8 * ks + e) / 3] * mq[(8 * ks + e) % 3]; };
+        const Split3 B = ks ? split3_of<7>(v) : split3_of<8>(v);
+        mma_six(g, [&](int n) -> const Split3& { return Q[n][ks]; }, [&](int) -> const Split3& { return B; });
+      }
+      // column col = pair c0 + col, rows = heads 4 uq + j
+      const bool in = c0 + col < take;
+      float out[12];
+      float vx = 0.0f, vy = 0.0f, vz = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float gu = g[0][j] * x + g[1][j] * y + g[2][j] * z;
+        out[3 * j] = radial_part[j] * x + (g[0][j] - gu * x) * ir;
+        out[3 * j + 1] = radial_part[j] * y + (g[1][j] - gu * y) * ir;
+        out[3 * j + 2] = radial_part[j] * z + (g[2][j] - gu * z) * ir;
+        vx += hw[j] * out[3 * j];
+        vy += hw[j] * out[3 * j + 1];
+        vz += hw[j] * out[3 * j + 2];
+      }
+      if (in) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) sum[k] += out[k];
+        const float dx = x * r, dy = y * r, dz = z * r;
+        vir[0] += vx * dx; vir[1] += vx * dy; vir[2] += vx * dz;
+        vir[3] += vy * dx; vir[4] += vy * dy; vir[5] += vy * dz;
+        vir[6] += vz * dx; vir[7] += vz * dy; vir[8] += vz * dz;
+        float* o = gpair + ((c.p0 + __float_as_int(b3.w)) * nh + 4 * uq) * 3;
+        if (quads) {
+          if (4 * uq < nh)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+              *(float4*)(o + 4 * k) = make_float4(out[4 * k], out[4 * k + 1], out[4 * k + 2], out[4 * k + 3]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 12; ++k)
+            if (4 * uq + k / 3 < nh) o[k] = out[k];
+        }
+      }
+    }
+    wave_lds_sync();
+  };
+#pragma unroll 1
+  for (int64_t pc = c.p0; pc < c.p1; pc += 64) {
+    const Cand cd = cur;
+    cur = cand_fetch(sys, c, pc + 64 + q, nxt);
+    nxt = cand_index(sys, c, pc + 128 + q);
+    bool rejected;
+    ring_append<64>(m, sys, c, q, pc, cd, S.ring, tail, rejected);
+    if (rejected) {
+      float* o = gpair + (pc + q) * nh * 3;
+      if (quads)
+        for (int k = 0; k < 3 * nh; k += 4) *(float4*)(o + k) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      else
+        for (int k = 0; k < 3 * nh; ++k) o[k] = 0.0f;
+    }
+    // full batches; after the row's last chunk the rest too
+    while (tail - head >= 64 || (pc + 64 >= c.p1 && tail > head)) run_batch();
+  }
+#pragma unroll
+  for (int k = 0; k < 12; ++k) sum[k] = row16_sum(sum[k]);
+  if (col == 0) {
+    float* o = own + ((int64_t)i * nh + 4 * uq) * 3;
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      if (4 * uq + k / 3 < nh) o[k] = sum[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) vir[k] = atom_sum<64>(vir[k]);
+  if (q == 0) {
+    const float inv = head_c ? 1.0f : 1.0f / (float)nh;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) virial[(int64_t)i * 9 + k] = vir[k] * inv;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // blocks [0, B*nchunk): FP64 sums per structure, fixed order (first in the
 // grid, so they start at once and overlap the gather);
-// the last nb_gather blocks: force gather, LPA lanes per atom; with VAR, gpair
-// holds one gradient set per head ([M][gstride][3]) and the kernel writes the
-// mean force and the per-atom force variance (1/M) sum_m |F^m - Fbar|^2
+// the last nb_gather blocks: force gather, LPA lanes per atom.  With VAR, gpair
+// holds the gradients of all heads and the kernel writes the mean force and
+// the per-atom force variance (1/M) sum_m |F^m - Fbar|^2: kGatherHeads, one set
+// per head ([M][gstride][3]); kGatherRecords, one record per pair ([P][M][3],
+// a wave per atom), with the rows' sums sum_{q in row k} g_q in own
+// ([N][M][3]), so that only the reverse pairs are read
 // float4 q of x (elements 4q .. 4q+3) with the elements outside [e0, e1)
 // read as zero; the float4 that ends past the array (end elements), or any
 // float4 of an array that is not 16-byte aligned, is read element by element
@@ -300,11 +569,12 @@ __device__ inline void structure_sums_tiled(int M, int want_stress, int64_t a0, 
   }
 }
 
-template <int LPA, bool VAR>
+template <int LPA, int VAR>
 __global__ void __launch_bounds__(kPairBlock) finish(int M, DevSystem sys, const float* __restrict__ gpair,
                                                      const float* __restrict__ atomic_e,
                                                      const float* __restrict__ virial, int want_stress, int nb_gather,
-                                                     int64_t gstride, int nchunk, double* __restrict__ partial,
+                                                     int64_t gstride, const float* __restrict__ own, int nchunk,
+                                                     double* __restrict__ partial,
                                                      int* __restrict__ counters, float* __restrict__ forces,
                                                      float* __restrict__ force_var, double* __restrict__ energy,
                                                      double* __restrict__ energy_var,
@@ -358,31 +628,86 @@ __global__ void __launch_bounds__(kPairBlock) finish(int M, DevSystem sys, const
       }
     } else {
       float f[kMaxHeads][3];
+      float mean[3] = {0.0f, 0.0f, 0.0f};
+      __shared__ float s_f[kPairBlock / 64][3 * kMaxHeads];
+      float* tot = s_f[threadIdx.x >> 6];  // records: the wave's force elements
+      const int E = 3 * M;
+      if constexpr (VAR == kGatherRecords) {
+        // lane (g, e) of the atom's wave takes element vector e (V floats) of
+        // the pair records, pairs g, g + G, ...; a record is read whole by
+        // adjacent lanes
+        __shared__ float4 s_sum[kPairBlock / 64][64];
+        float4* part = s_sum[threadIdx.x >> 6];
+        const bool quads = (M & 3) == 0;
+        const int Q = quads ? E / 4 : E, G = 64 / Q;
+        const int g = q / Q, e = q % Q;
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (live && g < G) {
+          const int64_t p1 = sys.row_ptr[i + 1];
+          int64_t p = sys.row_ptr[i] + g;
+          constexpr int U = 4;  // records in flight per lane
+          for (; p < p1; p += U * G) {
+            int64_t rp[U];
 #pragma unroll
-      for (int h = 0; h < kMaxHeads; ++h) f[h][0] = f[h][1] = f[h][2] = 0.0f;
-      if (live) {
-        const int64_t p0 = sys.row_ptr[i], p1 = sys.row_ptr[i + 1];
-        for (int64_t p = p0 + q; p < p1; p += LPA) {
-          const int64_t rp = sys.rev[p];
+            for (int u = 0; u < U; ++u) rp[u] = p + u * G < p1 ? (int64_t)sys.rev[p + u * G] : -1;
+            float4 x[U];
 #pragma unroll
-          for (int h = 0; h < kMaxHeads; ++h) {
-            if (h < M) {
-              const float* g = gpair + (int64_t)h * gstride * 3;
-              f[h][0] += g[3 * p] - g[3 * rp];
-              f[h][1] += g[3 * p + 1] - g[3 * rp + 1];
-              f[h][2] += g[3 * p + 2] - g[3 * rp + 2];
+            for (int u = 0; u < U; ++u) {
+              x[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+              if (rp[u] >= 0) {
+                if (quads) x[u] = ((const float4*)(gpair + rp[u] * E))[e];
+                else x[u].x = gpair[rp[u] * E + e];
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              a.x += x[u].x; a.y += x[u].y; a.z += x[u].z; a.w += x[u].w;
             }
           }
         }
-      }
-      float mean[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int h = 0; h < kMaxHeads; ++h)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          f[h][k] = atom_sum<LPA>(f[h][k]);
-          if (h < M) mean[k] += f[h][k];
+        part[q] = a;
+        wave_lds_sync();
+        if (live && q < E) {
+          const int V = quads ? 4 : 1;
+          const float* flat = (const float*)part;
+          float x = 0.0f;
+          for (int k = 0; k < G; ++k) x += flat[4 * (k * Q + q / V) + q % V];
+          tot[q] = own[(int64_t)i * E + q] - x;
         }
+        wave_lds_sync();
+#pragma unroll
+        for (int h = 0; h < kMaxHeads; ++h)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            f[h][k] = h < M ? tot[3 * h + k] : 0.0f;
+            if (h < M) mean[k] += f[h][k];
+          }
+      } else {
+#pragma unroll
+        for (int h = 0; h < kMaxHeads; ++h) f[h][0] = f[h][1] = f[h][2] = 0.0f;
+        if (live) {
+          const int64_t p0 = sys.row_ptr[i], p1 = sys.row_ptr[i + 1];
+          for (int64_t p = p0 + q; p < p1; p += LPA) {
+            const int64_t rp = sys.rev[p];
+#pragma unroll
+            for (int h = 0; h < kMaxHeads; ++h) {
+              if (h < M) {
+                const float* g = gpair + (int64_t)h * gstride * 3;
+                f[h][0] += g[3 * p] - g[3 * rp];
+                f[h][1] += g[3 * p + 1] - g[3 * rp + 1];
+                f[h][2] += g[3 * p + 2] - g[3 * rp + 2];
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < kMaxHeads; ++h)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            f[h][k] = atom_sum<LPA>(f[h][k]);
+            if (h < M) mean[k] += f[h][k];
+          }
+      }
       const float invM = 1.0f / (float)M;
 #pragma unroll
       for (int k = 0; k < 3; ++k) mean[k] *= invM;
@@ -404,12 +729,14 @@ __global__ void __launch_bounds__(kPairBlock) finish(int M, DevSystem sys, const
 #pragma unroll
             for (int k = 0; k < 3; ++k) fo[k] += c[h] * f[h][k];
       }
+      if (VAR == kGatherRecords && live && forces_heads && q < E)
+        forces_heads[((int64_t)(q / 3) * sys.n_atoms + i) * 3 + q % 3] = tot[q];
       if (live && q == 0) {
         forces[3 * (int64_t)i] = fo[0];
         forces[3 * (int64_t)i + 1] = fo[1];
         forces[3 * (int64_t)i + 2] = fo[2];
         force_var[i] = var * invM;
-        if (forces_heads) {
+        if (VAR == kGatherHeads && forces_heads) {
 #pragma unroll
           for (int h = 0; h < kMaxHeads; ++h)
             if (h < M)
@@ -496,9 +823,10 @@ template __global__ void pair_backward<32>(DevModel, DevSystem, const float*, fl
 template __global__ void pair_backward<64>(DevModel, DevSystem, const float*, float*, float*);
 #define FIN(LPA, VAR)                                                                                         \
   template __global__ void finish<LPA, VAR>(int, DevSystem, const float*, const float*, const float*, int, int, \
-                                            int64_t, int, double*, int*, float*, float*, double*, double*, double*, \
+                                            int64_t, const float*, int, double*, int*, float*, float*, double*, double*, double*, \
                                             double*, const double*, int, const float*, float*);
-FIN(8, false) FIN(16, false) FIN(32, false) FIN(64, false) FIN(8, true) FIN(16, true) FIN(32, true) FIN(64, true)
+FIN(8, 0) FIN(16, 0) FIN(32, 0) FIN(64, 0)
+FIN(8, kGatherHeads) FIN(16, kGatherHeads) FIN(32, kGatherHeads) FIN(64, kGatherHeads) FIN(64, kGatherRecords)
 #undef FIN
 
 }  // namespace gmnn
