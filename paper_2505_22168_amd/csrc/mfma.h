@@ -82,6 +82,23 @@ __device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
     t[n] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(SWAP ? y(n).h : x(n).h, SWAP ? x(n).h : y(n).h,
                                                     (floatx4{0.0f, 0.0f, 0.0f, 0.0f}), 0, 0, 0);
 }
+// ... with the largest added inside the MFMA (one register set, no extra adds):
+// for callers that negate x in every other k-step and subtract those products,
+// so that what is dropped towards minus infinity cancels (2e-9 of the terms a
+// step, alternating)
+template <int N, typename X, typename Y>
+__device__ __forceinline__ void six_products_alternating(floatx4 (&t)[N], X x, Y y) {
+#define GMNN_PART(PX, PY, FROM)         \
+  _Pragma("unroll") for (int n = 0; n < N; ++n) \
+      t[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x(n).PX, y(n).PY, FROM, 0, 0, 0)
+  GMNN_PART(l, h, (floatx4{0.0f, 0.0f, 0.0f, 0.0f}));
+  GMNN_PART(h, l, t[n]);
+  GMNN_PART(m, m, t[n]);
+  GMNN_PART(m, h, t[n]);
+  GMNN_PART(h, m, t[n]);
+  GMNN_PART(h, h, t[n]);
+#undef GMNN_PART
+}
 template <bool SWAP = false, int N, typename X, typename Y>
 __device__ __forceinline__ void mma_six(floatx4 (&sum)[N], X x, Y y) {
   floatx4 t[N];

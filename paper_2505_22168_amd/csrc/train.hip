@@ -41,6 +41,20 @@ constexpr int kTrainWaves = kTrainThreads / 64;
 constexpr int kTfAtoms = 6;         // atoms and threads of a training invariant block
 constexpr int kTfThreads = 256;
 
+// Rows of the weight products (X1, Y1, X2, Y2): 16 per group of 8 atoms, its
+// primal rows and its tangent rows, groups in the order in which blocks of one
+// group each would be dispatched (xcd_block's inverse); rows of absent atoms
+// are zero.  The order is that of the sums over atoms, which BF16 training
+// keeps bit for bit (see train_contract).
+constexpr int kRowAtoms = 8;
+__device__ __forceinline__ int group_rows(int n_atoms, int group) {
+  const int nb = (n_atoms + kRowAtoms - 1) / kRowAtoms, q = nb / kXcds, r = nb % kXcds;
+  const int long_runs = r * (q + 1);  // groups of the first r runs, q + 1 each
+  const int x = group < long_runs ? group / (q + 1) : r + (group - long_runs) / q;
+  const int k = group < long_runs ? group % (q + 1) : (group - long_runs) % q;
+  return 16 * (k * kXcds + x);
+}
+
 // directional derivative of every monomial at u along v
 __device__ inline void dmonomials(float x, float y, float z, float vx, float vy, float vz, float* d) {
   d[0] = 0.0f;
@@ -123,8 +137,8 @@ __device__ inline void swish_d2(float z, float& s, float& d1, float& d2) {
 }
 
 // ---------------------------------------------------------------------------
-// Invariants and their tangents.  G [N][kFP] (with PRIMAL) and Gd [N][kFP],
-// rows of the first weight product.  What bounds it: latency of the short
+// Invariants (with PRIMAL) and their tangents into X1, the rows of the first
+// weight product.  What bounds it: latency of the short
 // contraction tasks between block barriers, as in readout_features, so its
 // block size (three blocks per CU at 49 KB of LDS); the sums are those of the
 // earlier 8-atom training tile, term by term, which keeps the BF16 network's
@@ -142,8 +156,8 @@ struct TrainFeatLds {
 
 template <bool PRIMAL>
 __global__ void __launch_bounds__(kTfThreads) train_features(int n_atoms, const float* __restrict__ psi,
-                                                             const float* __restrict__ psid, float* __restrict__ G,
-                                                             float* __restrict__ Gd) {
+                                                             const float* __restrict__ psid,
+                                                             float* __restrict__ X1) {
   using L = TrainFeatLds;
   constexpr int TA = kTfAtoms, NT = kTfThreads, NP = kS * kPacked;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -191,10 +205,15 @@ __global__ void __launch_bounds__(kTfThreads) train_features(int n_atoms, const 
   if (PRIMAL) contract_forward_b<TA, NT, false, ISF>(sPsi, sI, sG, kFP, tb);
   contract_forward_b_dual<TA, NT, ISF, ISF>(sPsi, sPd, sI, sId, sGd, kFP, tb);
   __syncthreads();
-  const int n4 = n_rows * kFP / 4;
-  for (int t = tid; t < n4; t += NT) {
-    if (PRIMAL) ((float4*)(G + (int64_t)row0 * kFP))[t] = ((const float4*)sG)[t];
-    ((float4*)(Gd + (int64_t)row0 * kFP))[t] = ((const float4*)sGd)[t];
+  // the block of the last atom also clears the rows of its group's absent atoms
+  const int n_out = row0 + n_rows < n_atoms ? n_rows : (n_atoms + kRowAtoms - 1) / kRowAtoms * kRowAtoms - row0;
+  constexpr int C4 = kFP / 4;
+  for (int t = tid; t < n_out * C4; t += NT) {
+    const int a = t / C4, i = row0 + a;
+    float4* o = (float4*)(X1 + (int64_t)(group_rows(n_atoms, i / kRowAtoms) + i % kRowAtoms) * kFP) + t % C4;
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (PRIMAL) o[0] = a < n_rows ? ((const float4*)sG)[t] : zero;
+    o[kRowAtoms * C4] = a < n_rows ? ((const float4*)sGd)[t] : zero;
   }
 }
 
@@ -203,8 +222,8 @@ __global__ void __launch_bounds__(kTfThreads) train_features(int n_atoms, const 
 // primal rows of atoms 16 q .. 16 q + 15, row block 2 q + 1 their tangent
 // rows, so a lane's accumulators hold both values of the same atom and unit
 // (products transposed as in readout_network: four consecutive units of one
-// atom per lane).  Rows of the weight products (X1, X2 and Y1, Y2: [2 N], the
-// primal rows first) are read and written as 16-byte runs.  BF16: operands
+// atom per lane).  Rows of the weight products (X1, X2 and Y1, Y2) are read
+// and written as 16-byte runs.  BF16: operands
 // rounded once as they are stored; FP32: three parts (mfma.h).
 //   X1 = [G; Gdot] in; X2 = [h1; h1dot], Y2 = [z2bar; z2dotbar],
 //   Y1 = [z1bar; z1dotbar] out; Gbar, Gdbar out (dg_index)
@@ -245,6 +264,19 @@ __global__ void __launch_bounds__(kTrainThreads)
   const int ar = l & 15, uq = 4 * (l >> 4);
   RowsRing<NP, TPW> ring;
   RowsRing<NP, TPW_G> ring_g;
+  // primal weight-product row of atom a of the tile; its tangent row is kRowAtoms on
+  auto group_at = [&](int k) {
+    const int g = row0 / kRowAtoms + k;
+    return g * kRowAtoms < N ? group_rows(N, g) : 0;
+  };
+  const int r0 = group_at(0), d1 = group_at(1) - r0;
+  const int d2 = AB > 1 ? group_at(2) - d1 - r0 : 0, d3 = AB > 1 ? group_at(3) - d2 - d1 - r0 : 0;
+  auto prow = [&](int a) {
+    int r = r0 + a % kRowAtoms + (a >= kRowAtoms ? d1 : 0);
+    if (AB > 1) r += (a >= 2 * kRowAtoms ? d2 : 0) + (a >= 3 * kRowAtoms ? d3 : 0);
+    return (int64_t)r;
+  };
+  const int n_out = min(16 * AB, (N + kRowAtoms - 1) / kRowAtoms * kRowAtoms - row0);  // with the absent atoms' rows
 
   {
     constexpr int C4 = kFP / 4;
@@ -256,7 +288,7 @@ __global__ void __launch_bounds__(kTrainThreads)
       const int t = tid + u * kTrainThreads;
       const int row = t / C4, a = (row / 32) * 16 + row % 16;
       v[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      if (a < n_rows) v[u] = ((const floatx4*)(X1 + ((int64_t)((row / 16) & 1) * N + row0 + a) * kFP))[t % C4];
+      if (a < n_rows) v[u] = ((const floatx4*)(X1 + (prow(a) + ((row / 16) & 1) * kRowAtoms) * kFP))[t % C4];
     }
     rows_pre<NP, TPW>(ring, m.w1, kFP / 32, w, NW, NBH);
 #pragma unroll
@@ -271,11 +303,13 @@ __global__ void __launch_bounds__(kTrainThreads)
   }
   lds_barrier();
 
-  // the two rows of atom `a` (in the tile) and unit col of a [2 N][HP] array
+  // the two rows of atom `a` (in the tile) and unit col of a weight-product array
   auto put = [&](float* X, int a, int col, floatx4 p, floatx4 t) {
-    if (a < n_rows) {
-      *(floatx4*)(X + (int64_t)(row0 + a) * HP + col) = p;
-      *(floatx4*)(X + (int64_t)(N + row0 + a) * HP + col) = t;
+    if (a < n_out) {
+      const floatx4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      float* o = X + prow(a) * HP + col;
+      *(floatx4*)o = a < n_rows ? p : zero;
+      *(floatx4*)(o + kRowAtoms * HP) = a < n_rows ? t : zero;
     }
   };
   // the tile's operands of the next product, once every wave has read this one's
@@ -353,7 +387,7 @@ __global__ void __launch_bounds__(kTrainThreads)
           part[2 * q][j] += h2 * wb;
           part[2 * q + 1][j] += h2d * wb;
           gw[j] = (aa * h2 - h2d) * sg / (float)m.M;
-          acc[2 * q][i][j] = hbar * d1 + hdbar * dd * zd;
+          acc[2 * q][i][j] = __builtin_fmaf(hdbar * dd, zd, hbar * d1);
           acc[2 * q + 1][i][j] = hdbar * d1;
         }
         if (a < n_rows) *(floatx4*)(w3g + (int64_t)(row0 + a) * HP + col) = gw;
@@ -430,6 +464,117 @@ __global__ void __launch_bounds__(kTrainThreads)
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The invariant backward of the BF16 per-head double backward, 8 atoms a block:
+//   Psidotbar = B(Psi; Gdbar),
+//   Psibar = B(Psi; Gbar) + [B(Psi + t Psidot; Gdbar) - B(Psi - t Psidot; Gdbar)] / (2 t)
+// (exact for B's cubic polynomials, t = |Psi| / |Psidot|).  The one-atom-per-
+// lane dual form (contract_lanes) is faster (11,200 atoms: 23 against 320 us) and serves every
+// other case, but rounds differently in the last bit: an ensemble's training
+// loop in BF16 turns that into 5e-4 of its second step's gradients, by Adam's
+// sign-like first step and the operand roundings that it moves, so this path
+// keeps its sums.
+struct TrainContractLds {
+  static constexpr int TA = kRowAtoms, LDGB = kFP + 1;
+  static constexpr size_t psi = tf_al(sizeof(Tables));
+  static constexpr size_t psid = psi + tf_al(4 * (size_t)TA * PS);
+  static constexpr size_t ptmp = psid + tf_al(4 * (size_t)TA * PS);
+  static constexpr size_t inter = ptmp + tf_al(4 * (size_t)TA * PS);
+  static constexpr size_t gb = inter + tf_al(4 * (size_t)TA * IS);     // [16][LDGB]: Gbar, Gdbar
+  static constexpr size_t pba = gb + tf_al(4 * (size_t)16 * LDGB);     // Psibar accumulator, two halves
+  static constexpr size_t pbs = pba + tf_al(4 * 2 * (size_t)TA * PS);  // one backward's gradient, two halves
+  static constexpr size_t step = pbs + tf_al(4 * 2 * (size_t)TA * PS);
+  static constexpr size_t bytes = step + tf_al(4 * (size_t)TA);
+};
+__global__ void __launch_bounds__(kTrainThreads)
+    train_contract(int n_atoms, const float* __restrict__ psi, const float* __restrict__ psidot,
+                   const float* __restrict__ gbar, const float* __restrict__ gdbar, float* __restrict__ psibar,
+                   float* __restrict__ psidotbar) {
+  using L = TrainContractLds;
+  constexpr int TA = L::TA, NT = kTrainThreads, NP = kS * kPacked;
+  constexpr int KSA = 2 * ((TA * 30 + 63) / 64 * 64) <= NT ? 2 : 1, KSF = 2 * ((TA * 20 + 63) / 64 * 64) <= NT ? 2 : 1;
+  static_assert(TA * 29 * 2 <= NT && TA <= kTrainWaves, "threads for both halves of every task");
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  Tables& tb = *(Tables*)lds;
+  float* sPsi = (float*)(lds + L::psi);
+  float* sPd = (float*)(lds + L::psid);
+  float* sPt = (float*)(lds + L::ptmp);
+  float* sI = (float*)(lds + L::inter);
+  float* sGb = (float*)(lds + L::gb);
+  float* sPbA = (float*)(lds + L::pba);
+  float* sPbA2 = sPbA + TA * PS;
+  float* sPbS = (float*)(lds + L::pbs);
+  float* sPbS2 = sPbS + TA * PS;
+  float* sT = (float*)(lds + L::step);
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int row0 = xcd_block(blockIdx.x, gridDim.x) * TA;
+  const int n_rows = min(TA, n_atoms - row0);
+  load_tables(&tb);
+  for (int t = tid; t < 16 * kFP; t += NT) {
+    const int a = t % TA, f = t / TA % kFP, h = t / (TA * kFP);
+    sGb[(h * TA + a) * L::LDGB + f] = a < n_rows ? (h ? gdbar : gbar)[dg_index(n_atoms, row0 + a, f)] : 0.0f;
+  }
+  __syncthreads();
+  for (int t = tid; t < TA * NP; t += NT) {
+    const int a = t / NP, e = t % NP, s = e / kPacked, c = e % kPacked;
+    const bool ok = a < n_rows;
+    const float v = ok ? psi[(int64_t)row0 * NP + t] : 0.0f, vd = ok ? psidot[(int64_t)row0 * NP + t] : 0.0f;
+    for (int q = 0; q < tb.packed_mult[c]; ++q) {
+      sPsi[a * PS + s * kFull + tb.packed_full[c][q]] = v;
+      sPd[a * PS + s * kFull + tb.packed_full[c][q]] = vd;
+    }
+  }
+  __syncthreads();
+  if (w < TA) {
+    float n0 = 0.0f, n1 = 0.0f;
+    for (int e = l; e < kS * kFull; e += 64) {
+      n0 += sPsi[w * PS + e] * sPsi[w * PS + e];
+      n1 += sPd[w * PS + e] * sPd[w * PS + e];
+    }
+    n0 = wave_sum(n0);
+    n1 = wave_sum(n1);
+    if (l == 0) sT[w] = (n1 > 0.0f && n0 > 0.0f) ? sqrtf(n0 / n1) : 1.0f;
+  }
+  const float* Gbar = sGb;
+  const float* Gdbar = sGb + TA * L::LDGB;
+  // B(P; G) into pb and its second halves; with_inter: the intermediates of P first
+  auto backward = [&](const float* P, const float* G, float* pb, float* pb2, bool with_inter) {
+    if (with_inter) {
+      contract_forward_a<TA, NT, false, false, IS, KSF>(P, sI, nullptr, 0, tb);
+      __syncthreads();
+    }
+    contract_backward_a<TA, NT, KSA>(P, G, L::LDGB, sI, tb);
+    __syncthreads();
+    contract_backward_b<TA, NT, 2>(P, G, L::LDGB, sI, pb, tb, pb2);
+    __syncthreads();
+  };
+  backward(sPsi, Gdbar, sPbS, sPbS2, true);
+  auto to_psidotbar = [&](int a, int e, float v) {
+    if (a < n_rows) psidotbar[(int64_t)(row0 + a) * NP + e] = v;
+  };
+  fold_packed<TA, NT, decltype(to_psidotbar), true>(sPbS, tb, to_psidotbar, sPbS2);
+  backward(sPsi, Gbar, sPbA, sPbA2, false);
+  for (int ev = 0; ev < 2; ++ev) {
+    const float sgn = ev == 0 ? 1.0f : -1.0f;
+    for (int t = tid; t < TA * kS * kFull; t += NT) {
+      const int a = t % TA, e = t / TA;
+      sPt[a * PS + e] = sPsi[a * PS + e] + sgn * sT[a] * sPd[a * PS + e];
+    }
+    __syncthreads();
+    backward(sPt, Gdbar, sPbS, sPbS2, true);
+    for (int t = tid; t < TA * kS * kFull; t += NT) {
+      const int a = t % TA, e = t / TA;
+      const float d = sPbS[a * PS + e] + sPbS2[a * PS + e];
+      sPbA[a * PS + e] += sgn * d / (2.0f * sT[a]);
+    }
+    __syncthreads();
+  }
+  auto to_psibar = [&](int a, int e, float v) {
+    if (a < n_rows) psibar[(int64_t)(row0 + a) * NP + e] = v;
+  };
+  fold_packed<TA, NT, decltype(to_psibar), true>(sPbA, tb, to_psibar, sPbA2);
 }
 
 // ---------------------------------------------------------------------------
@@ -746,13 +891,20 @@ __global__ void __launch_bounds__(kPairBlock) pos_gather(DevSystem sys, const fl
 constexpr int kWgRows = 1024;    // rows per split-K chunk
 constexpr int kWgRowsF32 = 512;  // rows per chunk of the FP32 network's products (twice the blocks)
 
-// acc[c] += the NP-part products of one A fragment with four B fragments
+// acc[c] += the NP-part products of one A fragment with four B fragments; NP =
+// 3: A carries the k-step's sign (step_sign), which the sum takes out again
 template <int NP>
-__device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&b)[4][NP], floatx4 (&acc)[4]) {
+__device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&b)[4][NP], float sign,
+                                          floatx4 (&acc)[4]) {
   if constexpr (NP == 3) {
     const Split3 x{a[0], a[1], a[2]};
-    mma_six(acc, [&](int) -> const Split3& { return x; },
-            [&](int c) { return Split3{b[c][0], b[c][1], b[c][2]}; });
+    floatx4 t[4];
+    six_products_alternating(t, [&](int) -> const Split3& { return x; },
+                             [&](int c) { return Split3{b[c][0], b[c][1], b[c][2]}; });
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[c][j] = __builtin_fmaf(sign, t[c][j], acc[c][j]);
   } else {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -762,25 +914,55 @@ __device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&
     }
   }
 }
-// the NP parts of a loaded value into element e of the fragments
 template <int NP>
-__device__ __forceinline__ void put_parts(float v, bf16x8 (&o)[NP], int e) {
-  const __bf16 h = (__bf16)v;
-  const float r = v - (float)h;
-  const __bf16 m = (__bf16)r;
-  o[0][e] = h;
-  o[1][e] = m;
-  if constexpr (NP == 3) o[2][e] = (__bf16)(r - (float)m);
+__device__ __forceinline__ float step_sign(int64_t k) {
+  return NP == 3 && (k & 32) ? -1.0f : 1.0f;
+}
+// the NP parts of eight loaded values as fragments
+template <int NP>
+__device__ __forceinline__ void put_parts(const float (&v)[8], float sign, bf16x8 (&o)[NP]) {
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    bf16x2 p[3];
+    if constexpr (NP == 3) {
+      split3_pair(sign * v[e], sign * v[e + 1], p[0], p[1], p[2]);
+    } else {
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        p[0][d] = (__bf16)v[e + d];
+        p[1][d] = (__bf16)(v[e + d] - (float)p[0][d]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      o[q][e] = p[q][0];
+      o[q][e + 1] = p[q][1];
+    }
+  }
 }
 
+// Both layers' products in one launch: M x HP with M = kFP, then M = HP, so
+// that one's last blocks fill up with the other's.
+struct WeightProducts {
+  const float *A[2], *B[2];  // [K][M], [K][HP]
+  float* partial[2];
+  int HP;
+  int64_t K, kchunk;
+};
+
 template <int NP>
-__global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, int ldA, const float* __restrict__ B,
-                                                   int ldB, int Mdim, int Ndim, int64_t K, int64_t kchunk,
-                                                   float* __restrict__ partial) {
+__global__ void __launch_bounds__(256) weight_grad(WeightProducts g) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int tiles_n = Ndim / 64;
-  const int tile = blockIdx.x * 4 + w;
+  const int Ndim = g.HP, tiles_n = Ndim / 64, tiles1 = kFP / 64 * tiles_n;
+  int tile = blockIdx.x * 4 + w;
+  const bool second = tile >= tiles1;
+  if (second) tile -= tiles1;
+  const int Mdim = second ? g.HP : kFP;
   if (tile >= (Mdim / 64) * tiles_n) return;
+  const float *A = g.A[second], *B = g.B[second];
+  float* partial = g.partial[second];
+  const int ldA = Mdim, ldB = Ndim;
+  const int64_t K = g.K, kchunk = g.kchunk;
   const int m0 = (tile / tiles_n) * 64, n0 = (tile % tiles_n) * 64;
   const int64_t kb = (int64_t)blockIdx.y * kchunk;
   const int64_t ke = min(K, kb + kchunk);
@@ -804,17 +986,15 @@ __global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, 
         b[r][e] = ok ? bp[kk * ldB + r * 16] : 0.0f;
       }
     }
+    const float sign = step_sign<NP>(k - kb);
     bf16x8 bs[4][NP];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) put_parts<NP>(b[c][e], bs[c], e);
+    for (int c = 0; c < 4; ++c) put_parts<NP>(b[c], 1.0f, bs[c]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       bf16x8 as[NP];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) put_parts<NP>(a[r][e], as, e);
-      mma_parts<NP>(as, bs, acc[r]);
+      put_parts<NP>(a[r], sign, as);
+      mma_parts<NP>(as, bs, sign, acc[r]);
     }
   }
 #pragma unroll
@@ -837,14 +1017,19 @@ __global__ void __launch_bounds__(256) weight_grad(const float* __restrict__ A, 
 constexpr int kWgBlk = 128;  // block tile edge
 constexpr int kWgLdk = 40;   // LDS row stride in bf16 (32 k + 8 pad)
 template <int NP>
-__global__ void __launch_bounds__(256) weight_grad_staged(const float* __restrict__ A, int ldA,
-                                                          const float* __restrict__ B, int ldB, int Mdim, int Ndim,
-                                                          int64_t K, int64_t kchunk, float* __restrict__ partial) {
+__global__ void __launch_bounds__(256) weight_grad_staged(WeightProducts g) {
   // [A parts, B parts][column][k]
   __shared__ __attribute__((aligned(16))) __bf16 sm[2 * NP][kWgBlk * kWgLdk];
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-  const int tiles_n = Ndim / kWgBlk;
-  const int mb = (blockIdx.x / tiles_n) * kWgBlk, nb = (blockIdx.x % tiles_n) * kWgBlk;
+  const int Ndim = g.HP, tiles_n = Ndim / kWgBlk, tiles1 = kFP / kWgBlk * tiles_n;
+  const bool second = (int)blockIdx.x >= tiles1;
+  const int tile = blockIdx.x - (second ? tiles1 : 0);
+  const int Mdim = second ? g.HP : kFP;
+  const float *A = g.A[second], *B = g.B[second];
+  float* partial = g.partial[second];
+  const int ldA = Mdim, ldB = Ndim;
+  const int64_t K = g.K, kchunk = g.kchunk;
+  const int mb = (tile / tiles_n) * kWgBlk, nb = (tile % tiles_n) * kWgBlk;
   const int m0 = (w >> 1) * 64, n0 = (w & 1) * 64;  // the wave's block inside the block tile
   const int64_t kb = (int64_t)blockIdx.y * kchunk;
   const int64_t ke = min(K, kb + kchunk);
@@ -857,27 +1042,25 @@ __global__ void __launch_bounds__(256) weight_grad_staged(const float* __restric
   const int col = tid & (kWgBlk - 1), h = tid >> 7;
   const float* ap = A + mb + col;
   const float* bp = B + nb + col;
-  float ra[16], rb[16];
+  float ra[2][8], rb[2][8];
   auto fetch = [&](int64_t k) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int64_t kk = k + 16 * h + e;
       const bool ok = kk < ke;
-      ra[e] = ok ? ap[kk * ldA] : 0.0f;
-      rb[e] = ok ? bp[kk * ldB] : 0.0f;
+      ra[e / 8][e % 8] = ok ? ap[kk * ldA] : 0.0f;
+      rb[e / 8][e % 8] = ok ? bp[kk * ldB] : 0.0f;
     }
   };
   if (kb < ke) fetch(kb);
   for (int64_t k = kb; k < ke; k += 32) {
+    const float sign = step_sign<NP>(k - kb);
     __syncthreads();  // the previous step's fragment reads are done
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       bf16x8 a[NP], b[NP];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        put_parts<NP>(ra[8 * half + e], a, e);
-        put_parts<NP>(rb[8 * half + e], b, e);
-      }
+      put_parts<NP>(ra[half], sign, a);
+      put_parts<NP>(rb[half], 1.0f, b);
       const int o = col * kWgLdk + 16 * h + 8 * half;
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
@@ -901,7 +1084,7 @@ __global__ void __launch_bounds__(256) weight_grad_staged(const float* __restric
       bf16x8 a[NP];
 #pragma unroll
       for (int q = 0; q < NP; ++q) a[q] = *(const bf16x8*)&sm[q][o];
-      mma_parts<NP>(a, b, acc[r]);
+      mma_parts<NP>(a, b, sign, acc[r]);
     }
   }
 #pragma unroll
@@ -933,17 +1116,21 @@ __device__ inline float sum_chunks(const float* __restrict__ partial, int nchunk
 // Sums over atoms, stage 1, in one launch: the bias gradients (columns of the
 // primal rows of Y1 and Y2), the W3 gradient (columns of w3g), and per species
 // the sums of qsig and of the energies' weights.
-//   blocks [0, 3 nx ny): array b / (nx ny), 64 columns x one chunk of rows;
-//     4 row lanes take rows r, r + 4, ... of the chunk, added in lane order:
+//   blocks [0, 3 nx ny): array b / (nx ny), 64 columns x one chunk of rows
+//     (primal: of the weight products' rows, those with (k & 15) < 8); 4 row
+//     lanes take rows r, r + 4, ... of the chunk, added in lane order:
 //     part[array][chunk][column]
 //   blocks beyond: species_partials' chunk of 256 atoms
 constexpr int kColChunks = 128;  // at most this many row chunks
 struct ColumnSums {
   const float* src[3];
-  int ncols[3];
+  int ncols[3], chunks[3];
+  bool primal[3];
+  int64_t nrows[3], rows_per_chunk[3];
 };
 __device__ inline void column_partials(const float* __restrict__ Y, int ld, int64_t nrows, int64_t rows_per_chunk,
-                                       int ncols, int bx, int chunk, float* __restrict__ partial, float (*red)[64]) {
+                                       bool primal, int ncols, int bx, int chunk, float* __restrict__ partial,
+                                       float (*red)[64]) {
   const int cl = threadIdx.x & 63, r = threadIdx.x >> 6;
   const int c = bx * 64 + cl;
   const int64_t k0 = (int64_t)chunk * rows_per_chunk;
@@ -954,11 +1141,15 @@ __device__ inline void column_partials(const float* __restrict__ Y, int ld, int6
     for (; k + 28 < k1; k += 32) {
       float x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = Y[(k + 4 * u) * ld + c];
+      for (int u = 0; u < 8; ++u) {
+        const int64_t kk = k + 4 * u;
+        x[u] = !primal || (kk & 15) < kRowAtoms ? Y[kk * ld + c] : 0.0f;
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) v += x[u];
     }
-    for (; k < k1; k += 4) v += Y[k * ld + c];
+    for (; k < k1; k += 4)
+      if (!primal || (k & 15) < kRowAtoms) v += Y[k * ld + c];
   }
   red[r][cl] = v;
   __syncthreads();
@@ -1004,15 +1195,16 @@ __device__ inline void species_partials(const DevModel& m, const DevSystem& sys,
 
 __global__ void __launch_bounds__(kSpeciesChunk)
     train_partials(DevModel m, DevSystem sys, const double* __restrict__ ebar, const float* __restrict__ qsig,
-                   ColumnSums cols, int64_t rows_per_chunk, int nx, int ny, float* __restrict__ part,
-                   int64_t part_stride, double* __restrict__ sp) {
+                   ColumnSums cols, int nx, int ny, float* __restrict__ part, int64_t part_stride,
+                   double* __restrict__ sp) {
   __shared__ double smem[kSpeciesChunk / 64][kMaxSpecies + 1][2];
   static_assert(sizeof(smem) >= sizeof(float) * 4 * 64, "the column sums' four rows fit");
   const int b = blockIdx.x;
   if (b < 3 * nx * ny) {
     const int k = b / (nx * ny), t = b % (nx * ny);
-    column_partials(cols.src[k], m.HP1, sys.n_atoms, rows_per_chunk, cols.ncols[k], t % nx, t / nx,
-                    part + k * part_stride, (float(*)[64])smem);
+    if (t / nx >= cols.chunks[k]) return;
+    column_partials(cols.src[k], m.HP1, cols.nrows[k], cols.rows_per_chunk[k], cols.primal[k], cols.ncols[k], t % nx,
+                    t / nx, part + k * part_stride, (float(*)[64])smem);
   } else {
     species_partials(m, sys, ebar, qsig, b - 3 * nx * ny, sp, smem);
   }
@@ -1027,7 +1219,7 @@ struct GradSums {
   const float *part1, *part2, *cpart, *bpart;
   int64_t cstride;  // between the three column-sum arrays in cpart
   const double* sp;
-  int kch, cch, bch, sp_blocks;
+  int kch, cch_k, cch_n, bch, sp_blocks;  // cch_k, cch_n: row chunks of the bias and the W3 sums
   int HP, H1, H2, heads, head;  // heads: columns of W3
 };
 __global__ void __launch_bounds__(256) train_sums(DevModel m, GradSums g, gmnn_param_grads out) {
@@ -1047,17 +1239,17 @@ __global__ void __launch_bounds__(256) train_sums(DevModel m, GradSums g, gmnn_p
   }
   t -= n2;
   if (t < g.H1) {
-    store(out.b1, t, sum_chunks(g.cpart, g.cch, g.H1, t));
+    store(out.b1, t, sum_chunks(g.cpart, g.cch_k, g.H1, t));
     return;
   }
   t -= g.H1;
   if (t < g.H2) {
-    store(out.b2, t, sum_chunks(g.cpart + g.cstride, g.cch, g.H2, t));
+    store(out.b2, t, sum_chunks(g.cpart + g.cstride, g.cch_k, g.H2, t));
     return;
   }
   t -= g.H2;
   if (t < g.H2) {
-    const float v = sum_chunks(g.cpart + 2 * g.cstride, g.cch, g.H2, t);
+    const float v = sum_chunks(g.cpart + 2 * g.cstride, g.cch_n, g.H2, t);
     if (g.head >= 0) out.W3[t * g.heads + g.head] = v;
     else
       for (int h = 0; h < g.heads; ++h) out.W3[t * g.heads + h] = v;
@@ -1106,10 +1298,10 @@ struct TrainLayout {
   size_t psi, psidot, psibar, psidotbar, X1, Y1, X2, Y2, gbar, gdbar, w3g, qsig, part1, part2, bpart;
   size_t cpart, spart, bytes;
   int64_t cstride;     // between the column-sum arrays in cpart
-  int ccN;             // row chunks of the column sums
-  int64_t rcN;         // rows per chunk
+  int ccK, ccN;        // row chunks of the column sums over weight-product rows / over atoms
+  int64_t rcK, rcN;    // rows per chunk
   int sp_blocks;       // blocks of the per-species sums
-  int64_t K;           // weight-product rows: primal, then tangent
+  int64_t K;           // weight-product rows
   int kchunks;         // split-K chunks the partial buffers hold (the larger count)
   int beta_blocks;
 };
@@ -1123,7 +1315,7 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
     return o;
   };
   const size_t N = (size_t)n_atoms;
-  L.K = 2 * (int64_t)N;
+  L.K = ((int64_t)N + kRowAtoms - 1) / kRowAtoms * 16;
   L.kchunks = (int)((L.K + kWgRowsF32 - 1) / kWgRowsF32);
   L.beta_blocks = 256;
   L.psi = take(4 * N * 100);
@@ -1144,7 +1336,9 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   L.bpart = take(4 * (size_t)L.beta_blocks * nslots);
   L.rcN = N > 0 ? ((int64_t)N + kColChunks - 1) / kColChunks : 1;
   L.ccN = (int)(((int64_t)N + L.rcN - 1) / L.rcN);
-  L.cstride = (int64_t)HP * L.ccN;
+  L.rcK = L.K > 0 ? (L.K + kColChunks - 1) / kColChunks : 1;
+  L.ccK = (int)((L.K + L.rcK - 1) / L.rcK);
+  L.cstride = (int64_t)HP * std::max(L.ccK, L.ccN);
   L.cpart = take(4 * 3 * (size_t)L.cstride);
   L.sp_blocks = (int)((N + kSpeciesChunk - 1) / kSpeciesChunk);
   L.spart = take(8 * 2 * (size_t)(kMaxSpecies + 1) * (L.sp_blocks > 0 ? L.sp_blocks : 1));
@@ -1241,9 +1435,16 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
     st = ensure_lds_limit((const void*)kf, TrainFeatLds::bytes);
     if (st != GMNN_OK) return st;
     hipLaunchKernelGGL(kf, dim3((N + kTfAtoms - 1) / kTfAtoms), dim3(kTfThreads), TrainFeatLds::bytes, s, N, psi,
-                       psidot, X1, X1 + (int64_t)N * kFP);
+                       psidot, X1);
     st = launch_train_network(m, sys, bf16, TrainNetArgs{ebar, X1, Y1, X2, Y2, w3g, qsig, gbar, gdbar}, s);
-    if (st == GMNN_OK) st = launch_contract_back_dual(N, psi, psidot, gdbar, gbar, psidotbar, psibar, s);
+    if (st == GMNN_OK && bf16 && head >= 0) {
+      st = ensure_lds_limit((const void*)train_contract, TrainContractLds::bytes);
+      if (st == GMNN_OK)
+        hipLaunchKernelGGL(train_contract, dim3((N + kRowAtoms - 1) / kRowAtoms), dim3(kTrainThreads),
+                           TrainContractLds::bytes, s, N, psi, psidot, gbar, gdbar, psibar, psidotbar);
+    } else if (st == GMNN_OK) {
+      st = launch_contract_back_dual(N, psi, psidot, gdbar, gbar, psidotbar, psibar, s);
+    }
     if (st != GMNN_OK) return st;
   }
   if (dL_dpos && N > 0) {
@@ -1271,26 +1472,24 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
   const int64_t wg_rows = (staged && !bf16) ? kWgRowsF32 : kWgRows;
   const int kch = (int)((L.K + wg_rows - 1) / wg_rows);
   if (kch > 0) {
-    auto product = [&](const float* X, int ldx, const float* Y, float* part) {
-      if (staged)
-        hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
-                           dim3((ldx / kWgBlk) * (HP / kWgBlk), kch), dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K,
-                           wg_rows, part);
-      else
-        hipLaunchKernelGGL(bf16 ? weight_grad<2> : weight_grad<3>, dim3(((ldx / 64) * (HP / 64) + 3) / 4, kch),
-                           dim3(256), 0, s, X, ldx, Y, HP, ldx, HP, L.K, wg_rows, part);
-    };
-    product(X1, kFP, Y1, part1);
-    product(X2, HP, Y2, part2);
+    const WeightProducts g{{X1, X2}, {Y1, Y2}, {part1, part2}, HP, L.K, wg_rows};
+    if (staged)
+      hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
+                         dim3((kFP + HP) / kWgBlk * (HP / kWgBlk), kch), dim3(256), 0, s, g);
+    else
+      hipLaunchKernelGGL(bf16 ? weight_grad<2> : weight_grad<3>, dim3(((kFP + HP) / 64 * (HP / 64) + 3) / 4, kch),
+                         dim3(256), 0, s, g);
   }
   // bias, W3, scale/shift partials, then every gradient from its partials
   // (with no atoms there are no chunks: the sums of zero partials are zero)
   if (N > 0) {
-    const int nx = (std::max(H1, H2) + 63) / 64;
-    hipLaunchKernelGGL(train_partials, dim3(3 * nx * L.ccN + L.sp_blocks), dim3(kSpeciesChunk), 0, s, m, sys, ebar,
-                       qsig, ColumnSums{{Y1, Y2, w3g}, {H1, H2, H2}}, L.rcN, nx, L.ccN, cpart, L.cstride, spart);
+    const int nx = (std::max(H1, H2) + 63) / 64, ny = std::max(L.ccK, L.ccN);
+    const ColumnSums cols{{Y1, Y2, w3g}, {H1, H2, H2}, {L.ccK, L.ccK, L.ccN}, {true, true, false},
+                          {L.K, L.K, N}, {L.rcK, L.rcK, L.rcN}};
+    hipLaunchKernelGGL(train_partials, dim3(3 * nx * ny + L.sp_blocks), dim3(kSpeciesChunk), 0, s, m, sys, ebar, qsig,
+                       cols, nx, ny, cpart, L.cstride, spart);
   }
-  const GradSums sums{part1, part2, cpart, bpart, L.cstride, spart, kch, L.ccN, L.beta_blocks, L.sp_blocks,
+  const GradSums sums{part1, part2, cpart, bpart, L.cstride, spart, kch, L.ccK, L.ccN, L.beta_blocks, L.sp_blocks,
                       HP, H1, H2, heads, head};
   const int64_t total = (int64_t)kF * H1 + (int64_t)H1 * H2 + H1 + 2 * (int64_t)H2 +
                         (int64_t)nsp * nsp * kS * m.K + nsp + 1;
