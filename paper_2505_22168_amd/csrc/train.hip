@@ -26,6 +26,7 @@
 //                   products over all atoms, partials summed in a fixed order
 //   reductions      bias, W3, scale and shift gradients (fixed order)
 #include <algorithm>
+#include <cstdint>
 
 #include "common.h"
 #include "contract_lanes.h"
@@ -889,7 +890,7 @@ __global__ void __launch_bounds__(kPairBlock) pos_gather(DevSystem sys, const fl
 // Each wave owns a 64 x 64 block of C as 4 x 4 MFMA tiles, so every value
 // loaded feeds twelve (24) MFMAs.  M and N are multiples of 64.
 constexpr int kWgRows = 1024;    // rows per split-K chunk
-constexpr int kWgRowsF32 = 512;  // rows per chunk of the FP32 network's products (twice the blocks)
+constexpr int kWgRowsMin = 256;  // fewest rows per chunk of the FP32 network's staged products
 
 // acc[c] += the NP-part products of one A fragment with four B fragments; NP =
 // 3: A carries the k-step's sign (step_sign), which the sum takes out again
@@ -1302,9 +1303,29 @@ struct TrainLayout {
   int64_t rcK, rcN;    // rows per chunk
   int sp_blocks;       // blocks of the per-species sums
   int64_t K;           // weight-product rows
-  int kchunks;         // split-K chunks the partial buffers hold (the larger count)
+  int kchunks;         // split-K chunks the partial buffers hold
   int beta_blocks;
 };
+
+// Rows per split-K chunk of the FP32 network's staged products: whole rounds
+// of the blocks resident at once (two of 61 KB LDS per compute unit), few
+// rounds against few chunks, whose partials train_sums reads back (a chunk
+// costs about HP / 80 rows of products: 0.7 us at 2x512, where a row of a
+// round takes 0.11).  Against 512 rows always: a step of 7 heads at 1838 atoms
+// 2x256 1270 -> 1138 us, of 14 heads at 3633 atoms 2907 -> 2756.
+static int64_t weight_rows(int64_t K, int HP) {
+  const int tiles = (kFP + HP) / kWgBlk * (HP / kWgBlk), resident = 512;
+  int64_t best = kWgRows, best_cost = INT64_MAX;
+  for (int64_t rows = kWgRowsMin; rows <= kWgRows; rows += 32) {
+    const int64_t kch = (K + rows - 1) / rows, rounds = (tiles * kch + resident - 1) / resident;
+    const int64_t cost = rounds * rows + kch * HP / 80;
+    if (cost < best_cost) {
+      best = rows;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
 
 TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   TrainLayout L{};
@@ -1316,7 +1337,7 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   };
   const size_t N = (size_t)n_atoms;
   L.K = ((int64_t)N + kRowAtoms - 1) / kRowAtoms * 16;
-  L.kchunks = (int)((L.K + kWgRowsF32 - 1) / kWgRowsF32);
+  L.kchunks = (int)((L.K + kWgRowsMin - 1) / kWgRowsMin);
   L.beta_blocks = 256;
   L.psi = take(4 * N * 100);
   L.psidot = take(4 * N * 100);
@@ -1469,7 +1490,7 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
   // two parts per operand on the BF16 path, three on the FP32 path; widths
   // that are multiples of the staged kernel's block tile take it
   const bool staged = HP % kWgBlk == 0;
-  const int64_t wg_rows = (staged && !bf16) ? kWgRowsF32 : kWgRows;
+  const int64_t wg_rows = (staged && !bf16) ? weight_rows(L.K, HP) : kWgRows;
   const int kch = (int)((L.K + wg_rows - 1) / wg_rows);
   if (kch > 0) {
     const WeightProducts g{{X1, X2}, {Y1, Y2}, {part1, part2}, HP, L.K, wg_rows};
