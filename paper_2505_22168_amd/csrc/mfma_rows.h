@@ -11,9 +11,10 @@ namespace gmnn {
 // A product is taken from NP parts of both operands: 1 (plain BF16), 2
 // (split BF16: hh, hm, mh) or 3 (FP32: mma_six), in the order of the tile
 // readout's products (mfma.h).
-// k-steps of B in flight: measured best on the 2x512 network (BF16 3 and 2;
-// FP32 one three-part step, a second one spills)
-constexpr int rows_depth(int NP) { return NP == 1 ? 3 : NP == 2 ? 2 : 1; }
+// k-steps of B in flight: measured best on the 2x512 network (100,000 atoms,
+// BF16: 433 us with 2 plain and 2 split steps, 453 with 3 and 2, 460 with 1
+// and 2, 454 with 2 and 3; FP32: one three-part step, a second one spills)
+constexpr int rows_depth(int NP) { return NP == 3 ? 1 : 2; }
 
 template <int NP, int TPW>
 struct RowsRing {
