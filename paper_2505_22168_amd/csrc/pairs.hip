@@ -9,7 +9,8 @@
 //                  the derivative of E_i w.r.t. every pair vector d_p and the
 //                  per-atom virial sum_p g_p (x) d_p; pair_backward_heads does
 //                  it for every head of a shallow ensemble at once (Section
-//                  2.2, force variance).
+//                  2.2, force variance), pair_backward_rows for many heads as
+//                  matrix products.
 //   finish         F_k = sum_{q in row k} (g_q - g_rev(q)) (scatter-free: every
 //                  force is one gather over the reverse pair index), and in
 //                  extra blocks of the same grid the per-structure energies
@@ -19,8 +20,9 @@
 // Each atom row is processed by LPA lanes (8, 16, 32 or 64: eight, four, two or
 // one atom per wave, chosen by the execution plan); the 100 moment accumulators of a lane are
 // combined by a reduce-scatter (permlane swaps and DPP, no LDS, no atomics).
-// pair_moments and pair_backward take the row's pairs inside r_c only, queued
-// per lane group in LDS (the list's skin pairs do not occupy lanes).
+// pair_moments, pair_backward and pair_backward_rows take the row's pairs
+// inside r_c only, queued per lane group in LDS (the list's skin pairs do not
+// occupy lanes).
 #include "common.h"
 #include "model.h"
 #include "mfma.h"

@@ -111,9 +111,8 @@ __global__ void __launch_bounds__(kFtThreads) readout_features(DevSystem sys, co
 // w, w + 8, ... of every product, for all TM/16 row blocks; each weight
 // fragment loaded from L2 feeds TM/16 MFMAs.  Every product runs transposed:
 // the weight fragment is the MFMA's A operand and the activation fragment
-// its B operand (the A and B fragment layouts of the 16x16x32 BF16 and
-// 16x16x4 FP32 MFMAs coincide, so the packed weights and the LDS reads are
-// those of the plain orientation).  A lane's accumulator then holds four
+// its B operand (the two fragment layouts of the 16x16x32 BF16 MFMA coincide,
+// so the packed weights and the LDS reads are those of the plain orientation).  A lane's accumulator then holds four
 // consecutive hidden units (or features) of one atom, and every epilogue
 // store is one 8-byte (BF16) or 16-byte (FP32) write instead of four
 // scattered ones.  The block's barriers order LDS only (lds_barrier), so

@@ -63,3 +63,28 @@ def test_wide_tiles_add_up(precision):
     for k in PARAM_NAMES:
         err = float((got[k].double() - total[k]).norm() / total[k].norm())
         assert err < 1e-5, (k, err)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 65])
+def test_bf16_per_head_invariant_backward_at_group_edges(n):
+    """With one head the BF16 per-head double backward differs from the
+    head-mean one in the invariant backward's form alone (differences of the
+    exact polynomial over 8-atom groups against dual numbers): everything but
+    beta is bitwise equal, and beta agrees to the differences' rounding, a few
+    ulp of terms of the moments' size (1e-6), with a factor of ten to spare."""
+    g = need_gpu()
+    rng = np.random.default_rng(n)
+    L = max(6.0, (n / 0.1) ** (1.0 / 3.0))
+    pos, sp = random_box(rng, n, L, (15, 8, 2, 1, 4), min_sep=0.9)
+    batch = make_batch([(pos, sp, np.eye(3) * L, (1, 1, 1))])
+    model = g.Model.from_params(make_params(ModelSpec(n_species=5, hidden=(64, 64)), 7), "cuda")
+    print(f"per-head backward N={n}", flush=True)
+    system = g.System.from_batch(batch, "cuda")
+    nl = g.build_neighbors(system, 5.0)
+    dE, dF = rng.normal(size=(1, 1)), rng.normal(size=(1, n, 3)).astype(np.float32)
+    a = g.param_grads(model, system, nl, dE, dF, precision="bf16", per_head=True)
+    b = g.param_grads(model, system, nl, dE[:, 0], dF[0], precision="bf16")
+    for k in PARAM_NAMES:
+        if k != "beta":
+            assert torch.equal(a[k], b[k]), k
+    assert float((a["beta"] - b["beta"]).norm()) <= 1e-5 * float(b["beta"].norm())
