@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(kPairBlock) pair_backward_heads(DevModel m, De
 // own[i][h][3], so the gather reads the reverse pairs only.
 // What bounds it: the VALU work of forming and splitting the pairs' products
 // and, once an atom, its coefficients, at two waves a SIMD (28,160 atoms, 16
-// heads: 259 us against 471 us one pair per lane; the gather 102 against 180).
+// heads: 245 us against 471 us one pair per lane; the gather 102 against 180).
 // head_c (may be null): per-structure head weights [B][kMaxHeads] of the
 // virial (an uncertainty bias); null: the mean over heads
 struct RowsWave {
@@ -243,13 +243,14 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
   wave_lds_sync();
   CandIdx nxt = cand_index(sys, c, c.p0 + 64 + q);
 
-  // the atom's operands: row col = head, monomials of quarter uq
+  // the atom's operands: row col = head, monomials of quarter uq; every other
+  // k-step negated and its products subtracted (six_products_alternating)
   Split3 A[4], Q[3][2];
   {
     const float* pb = S.pb + col * RowsWave::kPbStride;
     const int t[5] = {of_quarter(uq, 0, 3, 6, 8), of_quarter(uq, 1, 4, 7, 9), of_quarter(uq, 2, 5, 14, 17),
                       of_quarter(uq, 10, 12, 15, 18), of_quarter(uq, 11, 13, 16, 19)};
-    auto a = [&](int k) { return pb[k / 5 * kPacked + t[k % 5]]; };
+    auto a = [&](int k) { return (k & 8 ? -1.0f : 1.0f) * pb[k / 5 * kPacked + t[k % 5]]; };
 #pragma unroll
     for (int ks = 0; ks < 3; ++ks) A[ks] = split3_of<8>([&](int e) { return a(8 * ks + e); });
     A[3] = split3_of<1>([&](int) { return a(24); });
@@ -266,7 +267,7 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
                              of_quarter(uq, 1.0f, 1.0f, 0.0f, 0.0f)}};
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
-      auto v = [&](int k) { return fd[x][k % 3] * pb[k / 3 * kPacked + td[x][k % 3]]; };
+      auto v = [&](int k) { return (k & 8 ? -1.0f : 1.0f) * fd[x][k % 3] * pb[k / 3 * kPacked + td[x][k % 3]]; };
       Q[x][0] = split3_of<8>(v);
       Q[x][1] = split3_of<7>([&](int e) { return v(8 + e); });
     }
@@ -317,23 +318,27 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
       mq[2] = of_quarter(uq, mo[2], mo[5], mo[14], mo[17]);
       mq[3] = of_quarter(uq, mo[10], mo[12], mo[15], mo[18]);
       mq[4] = of_quarter(uq, mo[11], mo[13], mo[16], mo[19]);
-      floatx4 ta[4], g[3], radial_part;
-      {
+      floatx4 g[3], radial_part;
+#pragma unroll
+      for (int ks = 0; ks < 4; ks += 2) {  // two at a time: all four spill
         auto v = [&](int k) { return dR[k / 5] * mq[k % 5]; };
-        Split3 B[4];
-#pragma unroll
-        for (int ks = 0; ks < 3; ++ks) B[ks] = split3_of<8>([&](int e) { return v(8 * ks + e); });
-        B[3] = split3_of<1>([&](int) { return v(24); });
-        six_products(ta, [&](int n) -> const Split3& { return A[n]; }, [&](int n) -> const Split3& { return B[n]; });
+        Split3 B[2];
+        B[0] = split3_of<8>([&](int e) { return v(8 * ks + e); });
+        B[1] = ks ? split3_of<1>([&](int) { return v(24); }) : split3_of<8>([&](int e) { return v(8 + e); });
+        floatx4 t[2];
+        six_products_alternating(t, [&](int n) -> const Split3& { return A[ks + n]; },
+                                 [&](int n) -> const Split3& { return B[n]; });
+        radial_part = ks ? radial_part + (t[0] - t[1]) : t[0] - t[1];
       }
-      radial_part = (ta[0] + ta[1]) + (ta[2] + ta[3]);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) g[a] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         auto v = [&](int e) { return R[(8 * ks + e) / 3] * mq[(8 * ks + e) % 3]; };
         const Split3 B = ks ? split3_of<7>(v) : split3_of<8>(v);
-        mma_six(g, [&](int n) -> const Split3& { return Q[n][ks]; }, [&](int) -> const Split3& { return B; });
+        floatx4 t[3];
+        six_products_alternating(t, [&](int n) -> const Split3& { return Q[n][ks]; },
+                                 [&](int) -> const Split3& { return B; });
+#pragma unroll
+        for (int a = 0; a < 3; ++a) g[a] = ks ? g[a] - t[a] : t[a];
       }
       // column col = pair c0 + col, rows = heads 4 uq + j
       const bool in = c0 + col < take;
