@@ -55,16 +55,16 @@ __device__ __forceinline__ Split3 split3x8(floatx4 a, floatx4 b) {
   return s;
 }
 
-// one k-step of N FP32 products, t[n] = x(n) y(n): the five smaller part
-// products, smallest first from zero, and the largest from zero, added in FP32.
-// An MFMA aligns the sum it adds to with its products and drops what falls
-// below (towards minus infinity), so a long sum kept in it drifts: by 1e-6 of
-// a force over a whole product, and still by 2e-9 of the terms, which doubles
-// the error of a solid's stress, where only the largest part of a step adds
-// to the smaller ones' sum; apart, by less than 5e-11.  The N chains are
-// interleaved: an MFMA waits for the one before it in its own chain.  SWAP: y
-// is the MFMA's A operand (the order of the part products stays, so both
-// orientations agree bit for bit).
+// one k-step of N FP32 products, t[n] = x(n) y(n), smallest part products first
+// from zero, to be added to the sum in FP32.  An MFMA aligns the sum it adds to
+// with its products and drops what falls below, towards minus infinity: a long
+// sum kept in it drifts by 1e-6 of a force, and a step's six products still by
+// 2e-9 of their terms, which doubles the error of a solid's stress.  So x is
+// negated in every other k-step (step_sign; exact) and those steps' products
+// are subtracted: the drift cancels.  The N chains are interleaved: an MFMA
+// waits for the one before it in its own chain.  SWAP: y is the MFMA's A
+// operand (the order of the part products stays, so both orientations agree
+// bit for bit).
 template <bool SWAP = false, int N, typename X, typename Y>
 __device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
 #define GMNN_PART(PX, PY, FROM)                                                                           \
@@ -76,35 +76,14 @@ __device__ __forceinline__ void six_products(floatx4 (&t)[N], X x, Y y) {
   GMNN_PART(m, m, t[n]);
   GMNN_PART(m, h, t[n]);
   GMNN_PART(h, m, t[n]);
-#undef GMNN_PART
-#pragma unroll
-  for (int n = 0; n < N; ++n)
-    t[n] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(SWAP ? y(n).h : x(n).h, SWAP ? x(n).h : y(n).h,
-                                                    (floatx4{0.0f, 0.0f, 0.0f, 0.0f}), 0, 0, 0);
-}
-// ... with the largest added inside the MFMA (one register set, no extra adds):
-// for callers that negate x in every other k-step and subtract those products,
-// so that what is dropped towards minus infinity cancels (2e-9 of the terms a
-// step, alternating)
-template <int N, typename X, typename Y>
-__device__ __forceinline__ void six_products_alternating(floatx4 (&t)[N], X x, Y y) {
-#define GMNN_PART(PX, PY, FROM)         \
-  _Pragma("unroll") for (int n = 0; n < N; ++n) \
-      t[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x(n).PX, y(n).PY, FROM, 0, 0, 0)
-  GMNN_PART(l, h, (floatx4{0.0f, 0.0f, 0.0f, 0.0f}));
-  GMNN_PART(h, l, t[n]);
-  GMNN_PART(m, m, t[n]);
-  GMNN_PART(m, h, t[n]);
-  GMNN_PART(h, m, t[n]);
   GMNN_PART(h, h, t[n]);
 #undef GMNN_PART
 }
-template <bool SWAP = false, int N, typename X, typename Y>
-__device__ __forceinline__ void mma_six(floatx4 (&sum)[N], X x, Y y) {
-  floatx4 t[N];
-  six_products<SWAP>(t, x, y);
+// the sign of k-step kb's x, and a signed step's products into the sum
+__device__ __forceinline__ float step_sign(int kb) { return kb & 1 ? -1.0f : 1.0f; }
+__device__ __forceinline__ void add_step(floatx4& sum, const floatx4& t, float sign) {
 #pragma unroll
-  for (int n = 0; n < N; ++n) sum[n] += t[n];
+  for (int j = 0; j < 4; ++j) sum[j] = __builtin_fmaf(sign, t[j], sum[j]);
 }
 
 // k-steps 0 .. KB - 1 of a product whose fragments come through a ring of PF
@@ -215,13 +194,14 @@ __device__ __forceinline__ void mma_ring(BRing<BF16, TPW, DEPTH>& r, const void*
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const float* p = (const float*)A + row + (g * U + u) * 32;
-            a[u] = split3x8(*(const floatx4*)p, *(const floatx4*)(p + 4));
+            const float sign = step_sign(g * U + u);
+            a[u] = split3x8(sign * *(const floatx4*)p, sign * *(const floatx4*)(p + 4));
           }
           floatx4 t[U * TPW];
           six_products(t, [&](int n) -> const Split3& { return a[n / TPW]; },
                        [&](int n) -> const Split3& { return r.b[slot * U + n / TPW][n % TPW]; });
 #pragma unroll
-          for (int n = 0; n < U * TPW; ++n) acc[n % TPW] += t[n];
+          for (int n = 0; n < U * TPW; ++n) add_step(acc[n % TPW], t[n], step_sign(g * U + n / TPW));
         },
         [&](int slot, int g) {
 #pragma unroll

@@ -9,7 +9,7 @@
 namespace gmnn {
 
 // A product is taken from NP parts of both operands: 1 (plain BF16), 2
-// (split BF16: hh, hm, mh) or 3 (FP32: mma_six), in the order of the tile
+// (split BF16: hh, hm, mh) or 3 (FP32: six_products), in the order of the tile
 // readout's products (mfma.h).
 // k-steps of B in flight: measured best on the 2x512 network (100,000 atoms,
 // BF16: 433 us with 2 plain and 2 split steps, 453 with 3 and 2, 460 with 1
@@ -70,12 +70,10 @@ __device__ __forceinline__ void mma_rows(RowsRing<NP, TPW>& ring, const __bf16* 
         const Split3 b{ring.b[0][i][0], ring.b[0][i][1], ring.b[0][i][2]};
         auto fa = [&](int r) -> const Split3& { return a[r]; };
         auto fb = [&](int) -> const Split3& { return b; };
-        floatx4 col[MB];
+        floatx4 t[MB];
+        six_products<!ATOM_ROWS>(t, fa, fb);
 #pragma unroll
-        for (int r = 0; r < MB; ++r) col[r] = acc[r][i];
-        mma_six<!ATOM_ROWS>(col, fa, fb);
-#pragma unroll
-        for (int r = 0; r < MB; ++r) acc[r][i] = col[r];
+        for (int r = 0; r < MB; ++r) add_step(acc[r][i], t[r], step_sign(kb));
         // (past the last step: the same step's fragments again, unused)
         frag_parts<NP>(ring.b[0][i], B, frag_lane(nb0, KB), i * nbs, KB, min(kb + 1, KB - 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -121,12 +119,13 @@ __device__ inline void zero_rows(floatx4 (&acc)[MB][TPW]) {
 
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
-// four consecutive activations of one row in NP parts, part q at
-// base + q * part elements
+// four consecutive activations of one row, columns col .. col + 3, in NP parts,
+// part q at base + q * part elements (three parts: with their k-step's sign)
 template <int NP>
-__device__ __forceinline__ void st4(__bf16* base, int part, int idx, floatx4 v) {
+__device__ __forceinline__ void st4(__bf16* base, int part, int idx, int col, floatx4 v) {
   bf16x4 o[3];
   if constexpr (NP == 3) {
+    v = v * step_sign(col / 32);
 #pragma unroll
     for (int j = 0; j < 4; j += 2) {
       bf16x2 h, m, l;

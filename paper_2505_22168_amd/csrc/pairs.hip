@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
   CandIdx nxt = cand_index(sys, c, c.p0 + 64 + q);
 
   // the atom's operands: row col = head, monomials of quarter uq; every other
-  // k-step negated and its products subtracted (six_products_alternating)
+  // k-step negated and its products subtracted (six_products)
   Split3 A[4], Q[3][2];
   {
     const float* pb = S.pb + col * RowsWave::kPbStride;
@@ -326,7 +326,7 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
         B[0] = split3_of<8>([&](int e) { return v(8 * ks + e); });
         B[1] = ks ? split3_of<1>([&](int) { return v(24); }) : split3_of<8>([&](int e) { return v(8 + e); });
         floatx4 t[2];
-        six_products_alternating(t, [&](int n) -> const Split3& { return A[ks + n]; },
+        six_products(t, [&](int n) -> const Split3& { return A[ks + n]; },
                                  [&](int n) -> const Split3& { return B[n]; });
         radial_part = ks ? radial_part + (t[0] - t[1]) : t[0] - t[1];
       }
@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
         auto v = [&](int e) { return R[(8 * ks + e) / 3] * mq[(8 * ks + e) % 3]; };
         const Split3 B = ks ? split3_of<7>(v) : split3_of<8>(v);
         floatx4 t[3];
-        six_products_alternating(t, [&](int n) -> const Split3& { return Q[n][ks]; },
+        six_products(t, [&](int n) -> const Split3& { return Q[n][ks]; },
                                  [&](int) -> const Split3& { return B; });
 #pragma unroll
         for (int a = 0; a < 3; ++a) g[a] = ks ? g[a] - t[a] : t[a];

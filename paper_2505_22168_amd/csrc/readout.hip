@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(kRoThreads)
       const int part = t / (TM * C16), tt = t % (TM * C16);
       if (part >= NS) continue;
       if constexpr (BF16) *(uint4*)(sA + part * PG + (tt / C16) * L::G + (tt % C16) * 8) = v[u];
-      else st4<3>(sA, PG, (tt / C16) * L::G + (tt % C16) * 4, __builtin_bit_cast(floatx4, v[u]));
+      else st4<3>(sA, PG, (tt / C16) * L::G + (tt % C16) * 4, (tt % C16) * 4, __builtin_bit_cast(floatx4, v[u]));
     }
     for (int a = tid; a < TM; a += kRoThreads) {
       float sc = 0.0f, sh = 0.0f;
@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(kRoThreads)
       if (nb >= NBH) continue;
 #pragma unroll
       for (int r = 0; r < MB; ++r)
-        st4<NF>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, acc[r][i]);
+        st4<NF>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, nb * 16 + uq, acc[r][i]);
     }
   }
   lds_barrier();
@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(kRoThreads)
           *(floatx4*)(o + (int64_t)sys.n_atoms * HP) = d * sScale[row];
         }
         const floatx4 wr = m.head_w ? *(const floatx4*)(m.head_w + (int64_t)sStruct[row] * HP + col) : wb;
-        st4<NBK>(sB, PH, row * L::H + col, d * sScale[row] * wr);
+        st4<NBK>(sB, PH, row * L::H + col, col, d * sScale[row] * wr);
       }
     }
     // BF16: the partials of all heads at once; FP32: kEpHeads at a time
@@ -362,7 +362,7 @@ __global__ void __launch_bounds__(kRoThreads)
       if (nb >= NBH) continue;
 #pragma unroll
       for (int r = 0; r < MB; ++r)
-        st4<NBK>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, acc[r][i] * dsw1[r][i]);
+        st4<NBK>(sA, PH, (r * 16 + ar) * L::H + nb * 16 + uq, nb * 16 + uq, acc[r][i] * dsw1[r][i]);
     }
   }
   lds_barrier();
@@ -453,7 +453,7 @@ __global__ void __launch_bounds__(kRoThreads)
       if (r < nh)
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = d2[j] * m.w3[(col + j) * m.M + head0 + hb + r];
-      st4<NP>(sT, PH, (r * 16 + ar) * L::H + col, v);
+      st4<NP>(sT, PH, (r * 16 + ar) * L::H + col, col, v);
     }
   }
   lds_barrier();
@@ -468,7 +468,8 @@ __global__ void __launch_bounds__(kRoThreads)
       if (!has_block(i, w, NW, NBH)) continue;
 #pragma unroll
       for (int r = 0; r < MB; ++r)
-        st4<NP>(sT, PH, (r * 16 + ar) * L::H + (w + i * NW) * 16 + uq, acc[r][i] * dsw1[i]);
+        st4<NP>(sT, PH, (r * 16 + ar) * L::H + (w + i * NW) * 16 + uq, (w + i * NW) * 16 + uq,
+                acc[r][i] * dsw1[i]);
     }
   }
   lds_barrier();

@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(kTrainThreads)
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       const int t = tid + u * kTrainThreads;
-      st4<NP>(sT, PG, (t / C4) * L::G + (t % C4) * 4, v[u]);
+      st4<NP>(sT, PG, (t / C4) * L::G + (t % C4) * 4, (t % C4) * 4, v[u]);
     }
     for (int a = tid; a < 16 * AB; a += kTrainThreads) {
       sScale[a] = a < n_rows ? m.scale[sys.species[row0 + a]] : 0.0f;
@@ -320,7 +320,10 @@ __global__ void __launch_bounds__(kTrainThreads)
     for (int i = 0; i < TPW; ++i) {
       if (!has_block(i, w, NW, NBH)) continue;
 #pragma unroll
-      for (int r = 0; r < MB; ++r) st4<NP>(sT, PH, (r * 16 + ar) * L::H + (w + i * NW) * 16 + uq, acc[r][i]);
+      for (int r = 0; r < MB; ++r) {
+        const int col = (w + i * NW) * 16 + uq;
+        st4<NP>(sT, PH, (r * 16 + ar) * L::H + col, col, acc[r][i]);
+      }
     }
     lds_barrier();
   };
@@ -900,12 +903,10 @@ __device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&
   if constexpr (NP == 3) {
     const Split3 x{a[0], a[1], a[2]};
     floatx4 t[4];
-    six_products_alternating(t, [&](int) -> const Split3& { return x; },
+    six_products(t, [&](int) -> const Split3& { return x; },
                              [&](int c) { return Split3{b[c][0], b[c][1], b[c][2]}; });
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[c][j] = __builtin_fmaf(sign, t[c][j], acc[c][j]);
+    for (int c = 0; c < 4; ++c) add_step(acc[c], t[c], sign);
   } else {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -914,10 +915,6 @@ __device__ __forceinline__ void mma_parts(const bf16x8 (&a)[NP], const bf16x8 (&
       acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[c][0], acc[c], 0, 0, 0);
     }
   }
-}
-template <int NP>
-__device__ __forceinline__ float step_sign(int64_t k) {
-  return NP == 3 && (k & 32) ? -1.0f : 1.0f;
 }
 // the NP parts of eight loaded values as fragments
 template <int NP>
@@ -987,7 +984,7 @@ __global__ void __launch_bounds__(256) weight_grad(WeightProducts g) {
         b[r][e] = ok ? bp[kk * ldB + r * 16] : 0.0f;
       }
     }
-    const float sign = step_sign<NP>(k - kb);
+    const float sign = step_sign((int)((k - kb) / 32));
     bf16x8 bs[4][NP];
 #pragma unroll
     for (int c = 0; c < 4; ++c) put_parts<NP>(b[c], 1.0f, bs[c]);
@@ -1055,7 +1052,7 @@ __global__ void __launch_bounds__(256) weight_grad_staged(WeightProducts g) {
   };
   if (kb < ke) fetch(kb);
   for (int64_t k = kb; k < ke; k += 32) {
-    const float sign = step_sign<NP>(k - kb);
+    const float sign = step_sign((int)((k - kb) / 32));
     __syncthreads();  // the previous step's fragment reads are done
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
