@@ -640,14 +640,15 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   // against 207 us at 8192 atoms, but 134 against 113 at 4096); three heads
   // and less in FP32 stay on the tile (2x256, 3 heads: 267 against 237 us).
   // Pair backward: the matrix form has 16 rows whatever the heads, the lane
-  // form's time grows with them; they meet at kManyHeads (28,160 atoms, 2x128
-  // BF16, evaluation: 6 heads 767 against 634 us, 8 heads 796 against 800, 16
-  // heads 1127 against 1451).
-  constexpr int kManyHeads = 8;
+  // form's time grows with them; from kRowHeads heads on the matrix form wins
+  // (2x128 BF16, evaluation at 512, 4096 and 28,160 atoms: 6 heads 94, 141 and
+  // 618 us against 97, 144 and 634; 4 heads 72, 111 and 500 against 75, 114
+  // and 484).
+  constexpr int kManyHeads = 8, kRowHeads = 6;
   const bool heads_free = !fused && var && !(flags & GMNN_HEADS_TILE);
-  const bool rows = heads_free && nh >= kManyHeads;
+  const bool rows = heads_free && nh >= kRowHeads;
   HeadScratch hs;
-  const bool stream_heads = heads_free && (rows || (N > 16 * kComputeUnits && (bf16 || nh >= 4))) &&
+  const bool stream_heads = heads_free && (nh >= kManyHeads || (N > 16 * kComputeUnits && (bf16 || nh >= 4))) &&
                             head_scratch(m, nl, L, W, N, nh, hs);
   const int lpa = P.lpa;
   // the fused schedule sums each structure in one block from the tiles'

@@ -19,7 +19,8 @@ from paper_2505_22168_amd import _capi as A
 pytestmark = gpu
 
 
-@pytest.mark.parametrize("n,width,heads", [(3, 64, 2), (16, 128, 16), (65, 64, 9), (65, 256, 8), (130, 256, 13)])
+@pytest.mark.parametrize("n,width,heads", [(3, 64, 2), (16, 128, 16), (65, 64, 9), (65, 256, 8), (130, 256, 13), (37, 128, 6),
+                                           (64, 64, 7)])
 @pytest.mark.parametrize("room", [False, True])
 def test_heads_match_oracle(n, width, heads, room):
     g = need_gpu()
