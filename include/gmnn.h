@@ -524,8 +524,10 @@ gmnn_status gmnn_last_layer_features(const gmnn_model* m, const gmnn_system* sys
  * [dim] and to the entries selected before it is largest; ties go to the
  * smaller index.  With no training entries the first pick is the entry of
  * largest norm (reading: the paper's minimum runs over an empty set there).
+ * An entry without a distance (NaN features, or a training set of nothing
+ * else) counts below every entry that has one.
  * selected: device [n_select] int32, in selection order.  Distances in FP64.
- * Workspace: gmnn_select_workspace_bytes(n_pool).  3 n_select + 1 launches,
+ * Workspace: gmnn_select_workspace_bytes(n_pool).  n_select + 1 launches,
  * no host synchronisation. */
 size_t gmnn_select_workspace_bytes(int64_t n_pool);
 gmnn_status gmnn_select_max_distance(const double* pool, int64_t n_pool, int32_t dim, const double* train,

@@ -8,7 +8,8 @@
 //   selection       greedy maximum-distance selection (eq. maxdist): each
 //                   step picks the pool structure whose smallest distance to
 //                   the training set and the structures picked so far is
-//                   largest; distances in FP64, ties to the smallest index.
+//                   largest; distances in FP64, ties to the smallest index,
+//                   entries without a distance (NaN) last.
 //                   One launch per pick: every block finds the pick from the
 //                   previous launch's block maxima, takes the distances of
 //                   its rows to it, and leaves its own maximum.
@@ -90,6 +91,10 @@ struct Best {
   int64_t i;
 };
 __device__ inline Best better(Best a, Best b) { return b.v > a.v || (b.v == a.v && b.i < a.i) ? b : a; }
+// entry i with minimum v as `better` compares them.  A NaN compares with
+// nothing, which would leave a pool of them without a valid pick: it counts
+// below every distance and above the entries that have left the pool (-1).
+__device__ inline Best entry(double v, int64_t i) { return Best{isnan(v) ? -0.5 : v, i}; }
 // the block's best entry (ties to the smallest index), for every thread
 __device__ inline Best block_best(Best x, Best* red) {
 #pragma unroll
@@ -199,7 +204,7 @@ __global__ void __launch_bounds__(kSelBlock) sel_step(const double* __restrict__
         v = m < 0.0 ? m : i == pick ? -1.0 : replace ? low : fmin(m, low);
       }
       mind[i] = v;
-      best = better(best, Best{v, i});
+      best = better(best, entry(v, i));
     }
   }
   best = block_best(best, s_red);
