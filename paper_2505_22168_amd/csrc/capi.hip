@@ -88,9 +88,8 @@ struct Plan {
   int lpa;      // lanes per atom row in the pair and gather kernels
   bool stream;  // split schedule: readout as three launches (64-row network tiles)
 };
-// the built-in fused plan halves its tiles (8 atoms) while 16-atom tiles
-// would leave compute units idle
-constexpr int kComputeUnits = 256;
+// (the built-in fused plan halves its tiles, 8 atoms, while 16-atom ones
+// would leave compute units idle)
 // at and above this many atoms the built-in plan streams the readout
 constexpr int kStreamMinAtoms = 16384;
 

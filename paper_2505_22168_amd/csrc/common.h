@@ -37,6 +37,7 @@ __host__ __device__ inline uint64_t pair_key(int j, int sx, int sy, int sz) {
 // L2.  A bijection of [0, nb).
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;
+constexpr int kComputeUnits = 256;
 __device__ inline int xcd_block(int b, int nb) {
   const int q = nb / kXcds, r = nb % kXcds;
   const int x = b % kXcds, k = b / kXcds;

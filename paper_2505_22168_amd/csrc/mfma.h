@@ -122,11 +122,24 @@ struct BRing {
 
 // Fragment (nb0 + i nbs, kb) of one part of B, as a buffer load: the wave's
 // block and the lane in one 32-bit offset (frag_lane), i and kb in a scalar
-// one, so a product's loads share a single address register.
+// one, so a product's loads share a single address register.  Three-part
+// fragments and four column blocks a wave need the registers (FP32 2x256 tile,
+// 48 atoms: 45.8 us, 47.0 with plain addresses; BF16 2x512: 49.0 and 49.4);
+// fewer BF16 fragments take plain addresses (frag_plain: 2x64 at 582 atoms 32.2
+// us against 32.5, 2x256 at 1400 39.5 against 39.9).
 __device__ __forceinline__ int frag_lane(int nb0, int KB) { return (nb0 * KB * 64 + (threadIdx.x & 63)) * 16; }
 __device__ __forceinline__ bf16x8 frag_load(const bf16x8* part, int lane, int inb, int KB, int kb) {
   const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)part, 0, 0x7fffffff, 0x00027000);
   return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, lane, (inb * KB + kb) * 1024, 0));
+}
+
+__device__ __forceinline__ bf16x8 frag_plain(const bf16x8* part, int lane, int inb, int KB, int kb) {
+  return *(const bf16x8*)((const char*)part + lane + (size_t)((inb * KB + kb) * 1024));
+}
+template <int TPW>
+__device__ __forceinline__ bf16x8 frag_bf16(const bf16x8* part, int lane, int inb, int KB, int kb) {
+  if constexpr (TPW < 4) return frag_plain(part, lane, inb, KB, kb);
+  else return frag_load(part, lane, inb, KB, kb);
 }
 
 // whether a wave has an i-th column block (known at compile time where the
@@ -143,7 +156,7 @@ __device__ __forceinline__ void ring_load(BRing<BF16, TPW, DEPTH>& r, int slot, 
   for (int i = 0; i < TPW; ++i) {
     if (has_block(i, nb0, nbs, NB) && kb < KB) {
       auto part = [&](const bf16x8* p) { return frag_load(p, lane, i * nbs, KB, kb); };
-      if constexpr (BF16) r.b[slot][i] = part(B.h);
+      if constexpr (BF16) r.b[slot][i] = frag_bf16<TPW>(B.h, lane, i * nbs, KB, kb);
       else r.b[slot][i] = Split3{part(B.h), part(B.m), part(B.l)};
     }
   }
@@ -239,8 +252,8 @@ __device__ __forceinline__ void split_ring_load(BRing<true, 2 * TPW, SD>& r, int
 #pragma unroll
   for (int i = 0; i < TPW; ++i) {
     if (has_block(i, nb0, nbs, NB) && kb < KB) {
-      r.b[slot][i] = frag_load(B.h, lane, i * nbs, KB, kb);
-      r.b[slot][TPW + i] = frag_load(B.m, lane, i * nbs, KB, kb);
+      r.b[slot][i] = frag_bf16<TPW>(B.h, lane, i * nbs, KB, kb);
+      r.b[slot][TPW + i] = frag_bf16<TPW>(B.m, lane, i * nbs, KB, kb);
     }
   }
 }

@@ -66,6 +66,39 @@ struct TileLds {
   static constexpr size_t bytes = ea + (FUSED ? al(4 * (size_t)TM * kMaxHeads) : 0);
 };
 
+// Few fused tiles with large weights: each tile streams all of them, a few
+// k-steps ahead of its products, and where they are not in its XCD's L2 (three
+// models in turn are enough: 4 MB) waits for every group of fragments.  While
+// the tiles form their moments, kWarmBlocks blocks on compute units that have no
+// tile read the weights once, so that each XCD's L2 holds them.  Measured with
+// three models in turn at 48 and 1400 atoms: FP32 2x256 (1.97 MB) 54.8 -> 47.9 and
+// 53.0 -> 48.7 us, BF16 2x512 (2.75 MB) 57.1 -> 50.6 and 55.0 -> 51.9; one model
+// alone 45.8 -> 46.2 and 48.8 -> 49.0.  BF16 2x256 (0.98 MB) loses: 36.3 -> 37.2,
+// and the narrower ones 0.6 us.
+constexpr int kWarmBlocks = 64;  // eight per XCD
+template <int HP, bool BF16>
+constexpr bool warms_weights() { return (BF16 ? 6 : 12) * (size_t)HP * (kFP + HP) >= 1536 * 1024; }
+
+template <int HP, bool BF16>
+__device__ __forceinline__ void warm_weights(const DevModel& m, int part) {
+  auto pass = [&](const bf16x8* p, int K, int N) {
+    const int n = K * N / 8;
+    for (int t = part * kTileThreads + threadIdx.x; t < n; t += kWarmBlocks / kXcds * kTileThreads) {
+      const bf16x8 v = p[t];
+      asm volatile("" ::"v"(v));  // loaded for the cache alone
+    }
+  };
+  auto all = [&](const Weights& w, int K, int N, bool split) {
+    pass(w.h, K, N);
+    if (!BF16 || split) pass(w.m, K, N);
+    if (!BF16) pass(w.l, K, N);
+  };
+  all(m.w1, kFP, HP, true);
+  all(m.w2, HP, HP, true);
+  all(m.w2t, HP, HP, false);
+  all(m.w1t, HP, kFP, false);
+}
+
 // psibar_out (unfused): dE/dG of the head mean (dg_index), or with PERHEAD
 // dE/dPsi [nh][N][100]; gpair: [nh][gstride][3] (fused);
 // nh = n_heads with PERHEAD (one backward per head), else 1 (head mean).
@@ -105,7 +138,13 @@ __global__ void __launch_bounds__(kTileThreads)
 
   const int tid = threadIdx.x;
   const int w = tid >> 6, l = tid & 63;
-  const int row0 = xcd_block(blockIdx.x, gridDim.x) * TA;
+  constexpr bool WARM = FUSED && warms_weights<HP, BF16>();
+  const int n_tiles = WARM ? (sys.n_atoms + TA - 1) / TA : (int)gridDim.x;
+  if (WARM && (int)blockIdx.x >= n_tiles) {
+    warm_weights<HP, BF16>(m, (blockIdx.x - n_tiles) / kXcds);
+    return;
+  }
+  const int row0 = xcd_block(blockIdx.x, n_tiles) * TA;
   const int n_rows = min(TA, sys.n_atoms - row0);
   const int nh = PERHEAD ? m.M : 1;
 
@@ -316,7 +355,8 @@ static gmnn_status launch_tile_t(const DevModel& m, const DevSystem& sys, const 
   if (st != GMNN_OK) return st;
   const int grid = (sys.n_atoms + TA - 1) / TA;
   if (grid == 0) return GMNN_OK;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(kTileThreads), L::bytes, stream, m, sys, psi, atomic_e, psibar, gpair,
+  const int warm = FUSED && warms_weights<HP, BF16>() && grid + kWarmBlocks <= kComputeUnits ? kWarmBlocks : 0;
+  hipLaunchKernelGGL(k, dim3(grid + warm), dim3(kTileThreads), L::bytes, stream, m, sys, psi, atomic_e, psibar, gpair,
                      virial, gstride, tile_rec);
   return hipGetLastError() == hipSuccess ? GMNN_OK : GMNN_ERR_HIP;
 }
