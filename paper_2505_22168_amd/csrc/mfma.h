@@ -89,11 +89,13 @@ __device__ __forceinline__ void add_step(floatx4& sum, const floatx4& t, float s
 // k-steps 0 .. KB - 1 of a product whose fragments come through a ring of PF
 // slots, the first PF of them already issued: step(slot, kb), then
 // load(slot, kb + PF).  The last steps are peeled, so no branch guards a load
-// (a guarded one would put the ring in scratch memory).
-template <int PF, typename Step, typename Load>
+// (a guarded one would put the ring in scratch memory).  The 64-wide BF16
+// tile, where half the waves have no column block, takes the loop unrolled
+// (582 atoms: 31.9 us against 32.3; 2x128 33.2 against 33.0, 2x512 52.3 against 51.9).
+template <int PF, int UNROLL = 1, typename Step, typename Load>
 __device__ __forceinline__ void pipeline(int KB, Step step, Load load) {
   const int full = KB > PF ? (KB - PF) / PF * PF : 0;
-#pragma unroll 1
+#pragma unroll UNROLL
   for (int kb = 0; kb < full; kb += PF) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
@@ -181,16 +183,16 @@ __device__ __forceinline__ void mma_ring(BRing<BF16, TPW, DEPTH>& r, const void*
   const int KB = K / 32;
   const int row = (rb * 16 + (l & 15)) * lda + (l >> 4) * 8;
   if constexpr (BF16) {
-    pipeline<PF>(
-        KB,
-        [&](int slot, int kb) {
-          const bf16x8 a = *(const bf16x8*)((const __bf16*)A + row + kb * 32);
+    auto step = [&](int slot, int kb) {
+      const bf16x8 a = *(const bf16x8*)((const __bf16*)A + row + kb * 32);
 #pragma unroll
-          for (int i = 0; i < TPW; ++i)
-            if (has_block(i, nb0, nbs, NB))
-              acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
-        },
-        [&](int slot, int kb) { ring_load(r, slot, B, KB, kb, nb0, nbs, NB); });
+      for (int i = 0; i < TPW; ++i)
+        if (has_block(i, nb0, nbs, NB))
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, r.b[slot][i], acc[i], 0, 0, 0);
+    };
+    auto load = [&](int slot, int kb) { ring_load(r, slot, B, KB, kb, nb0, nbs, NB); };
+    if (NB < nbs) pipeline<PF, 4>(KB, step, load);
+    else pipeline<PF>(KB, step, load);
   } else {
     // a wave with one column block runs two k-steps at once: one chain of six
     // dependent MFMAs would leave the pipe waiting (every K here is a multiple
@@ -295,7 +297,9 @@ __device__ __forceinline__ void fwd_mma(FwdRing<BF16, TPW, DEPTH>& r, const void
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, r.b[slot][i], acc[i], 0, 0, 0);
       }
     };
-    pipeline<SD>(KB, step, [&](int slot, int kb) { split_ring_load<TPW, SD>(r, slot, B, KB, kb, nb0, nbs, NB); });
+    auto load = [&](int slot, int kb) { split_ring_load<TPW, SD>(r, slot, B, KB, kb, nb0, nbs, NB); };
+    if (NB < nbs) pipeline<SD, 4>(KB, step, load);
+    else pipeline<SD>(KB, step, load);
   } else {
     mma_ring(r, A, lda, rb, B, K, nb0, nbs, NB, acc);
   }
