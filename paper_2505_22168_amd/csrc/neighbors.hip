@@ -416,6 +416,10 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
   const int K = (g.pbc[2] ? floor_div(hi2, g.nc[2]) : 0) - s2_lo + 1;
   const int T = (2 * g.m[0] + 1) * w1 * K;
   const float inv_k = 1.0f / (float)K, inv_w = 1.0f / (float)w1;
+  // quotients of t by reciprocals in FP32: t + 0.5 is exact, the reciprocal and
+  // the product are off by 2^-24 each, together less than half a step of t
+  // while t < 2^22 (cells far from reduced have more runs and divide)
+  const bool by_reciprocal = T <= (1 << 22);
   int count = 0;
   int base = 0;         // MODE 1: keys collected so far
   int n = 0;            // MODE 1: the row's length
@@ -432,9 +436,9 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
     const int t = t0 + l;
     int cnt = 0, start = 0, swp = 0;
     if (t < T) {
-      // t = (o0 * w1 + o1) * K + o2 (exact in FP32: a handful of runs)
-      const int q0 = (int)(((float)t + 0.5f) * inv_k), o2 = t - q0 * K;
-      const int q1 = (int)(((float)q0 + 0.5f) * inv_w), o1 = q0 - q1 * w1;
+      // t = (o0 * w1 + o1) * K + o2
+      const int q0 = by_reciprocal ? (int)(((float)t + 0.5f) * inv_k) : t / K, o2 = t - q0 * K;
+      const int q1 = by_reciprocal ? (int)(((float)q0 + 0.5f) * inv_w) : q0 / w1, o1 = q0 - q1 * w1;
       const int cell[2] = {ci[0] + q1 - g.m[0], ci[1] + o1 - g.m[1]};
       int cc[2], sw[3];
       bool ok = true;
