@@ -21,8 +21,8 @@ template <int LPA>
 __global__ void pair_backward(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* virial);
 __global__ void pair_backward_heads(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* virial, int nh,
                                     int64_t gstride, const float* head_c);
-__global__ void pair_backward_rows(DevModel m, DevSystem sys, const float* psibar, float* gpair, float* own,
-                                   float* virial, int nh, const float* head_c);
+__global__ void pair_backward_rows(DevModel m, DevSystem sys, float* psibar, float* gpair, float* virial, int nh,
+                                   const float* head_c);
 template <int LPA, int VAR>
 __global__ void finish(int M, DevSystem sys, const float* gpair, const float* atomic_e, const float* virial,
                        int want_stress, int nb_gather, int64_t gstride, const float* own, int nchunk, double* partial,
@@ -43,7 +43,7 @@ size_t stream_dg_bytes(int n_atoms);
 size_t tile_lds_bytes(int hp, bool bf16, bool fused, bool perhead);
 __global__ void ll_features(DevModel m, DevSystem sys, int H2, const float* h2, double* phi);
 bool train_supported(const DevModel& m);
-size_t train_workspace_bytes(int n_atoms, int HP, int nsp);
+size_t train_workspace_bytes(int n_atoms, int HP, int nsp, bool bf16);
 size_t heads_backward_extra_bytes(const DevModel& m, int n_structs);
 gmnn_status train_backward_heads(const DevModel& m, const DevSystem& sys, bool bf16, bool lanes16, int H1, int H2,
                                  int n_structs, const double* dE, const float* dF, gmnn_param_grads* g, void* ws,
@@ -307,7 +307,7 @@ static DevSystem dev_system(const gmnn_system* s, const gmnn_neighbors* nl) {
 }
 
 struct EfLayout {
-  size_t psi = 0, psibar = 0, atomic_e = 0, gpair = 0, own = 0, virial = 0, g = 0, dg = 0, partial = 0, counters = 0,
+  size_t psi = 0, psibar = 0, atomic_e = 0, gpair = 0, virial = 0, g = 0, dg = 0, partial = 0, counters = 0,
          tilerec = 0, head_c = 0, head_w = 0, bytes = 0;
 };
 
@@ -324,14 +324,13 @@ static EfLayout ef_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   L.psi = take(4 * N * kS * kPacked);
   L.psibar = take(4 * N * kS * kPacked * nh);
   L.atomic_e = take(4 * N * (size_t)m->n_heads);
-  L.gpair = take(12 * (size_t)nl->capacity * nh);
-  L.own = (flags & GMNN_WANT_FORCE_VAR) ? take(12 * N * nh) : 0;  // the rows' sums of gpair, [N][nh][3]
   L.virial = take(4 * 9 * N);
   L.g = take(stream_g_bytes((int)N, (flags & GMNN_PREC_BF16) != 0));
   L.dg = take(stream_dg_bytes((int)N));
   L.partial = take(8 * (size_t)(kMaxHeads + 9) * sys->n_structs * reduce_chunks(sys));
   L.counters = take(4 * (size_t)sys->n_structs);
   L.tilerec = take(8 * (size_t)(kMaxHeads + 9) * ((N + 7) / 8));  // fused: one record per tile of >= 8 atoms
+  L.gpair = take(12 * (size_t)nl->capacity * nh);  // gpair, g, dg: one run (head_scratch)
   // uncertainty bias: head weights c [B][kMaxHeads] and weighted W3 vectors [B][HP2]
   L.head_c = take(4 * (size_t)kMaxHeads * sys->n_structs);
   L.head_w = take(4 * (size_t)packed_layout(m->hidden1, m->hidden2, m->n_heads).HP2 * sys->n_structs);
@@ -484,7 +483,7 @@ static BwLayout bw_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   const PackedLayout P = packed_layout(m->hidden1, m->hidden2, m->n_heads);
   BwLayout L;
-  L.train = al(train_workspace_bytes(sys->n_atoms, P.HP1, m->n_species));
+  L.train = al(train_workspace_bytes(sys->n_atoms, P.HP1, m->n_species, (flags & GMNN_PREC_BF16) != 0));
   L.gpos = L.train;
   L.heads = L.gpos + al(12 * (size_t)std::max<int64_t>(nl->capacity, 0));
   L.bytes = L.heads + ((flags & GMNN_BACKWARD_PER_HEAD)
@@ -594,7 +593,6 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   float* psibar = (float*)(W + L.psibar);
   float* atomic_e = out->atomic_energy ? out->atomic_energy : (float*)(W + L.atomic_e);
   float* gpair = (float*)(W + L.gpair);
-  float* own = (flags & GMNN_WANT_FORCE_VAR) ? (float*)(W + L.own) : nullptr;
   float* virial = (float*)(W + L.virial);
   double* partial = (double*)(W + L.partial);
   int* counters = (int*)(W + L.counters);
@@ -746,7 +744,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
       } else if (rows) {
         const size_t lds = sizeof(float) * kHeadsAtoms * (size_t)m->n_species * kS * kMaxBasis;
         hipLaunchKernelGGL(pair_backward_rows, dim3((N + kHeadsAtoms - 1) / kHeadsAtoms), dim3(kPairThreads), lds,
-                           s, dm, ds, psibar, gpair, own, virial, nh, udd ? head_c : nullptr);
+                           s, dm, ds, psibar, gpair, virial, nh, udd ? head_c : nullptr);
       } else if (lpa == 64) PAIR_BACKWARD(64);
       else if (lpa == 32) PAIR_BACKWARD(32);
       else if (lpa == 16) PAIR_BACKWARD(16);
@@ -761,7 +759,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   const dim3 fgrid(nbg + sys->n_structs * nchunk);
 #define FINISH(LPA, VAR)                                                                                       \
   hipLaunchKernelGGL((finish<LPA, VAR>), fgrid, dim3(kPairThreads), 0, s, m->n_heads, ds, gpair, atomic_e, virial, \
-                     want_stress, nbg, gstride, own, nchunk, partial, counters, out->forces, out->force_var,        \
+                     want_stress, nbg, gstride, psibar, nchunk, partial, counters, out->forces, out->force_var,        \
                      out->energy, out->energy_var, out->energy_mean, out->stress, fused ? tilerec : nullptr,        \
                      fused ? ta : 0, (udd && var) ? head_c : nullptr, var ? out->forces_heads : nullptr)
   if (rows) FINISH(64, kGatherRecords);

@@ -156,8 +156,9 @@ __global__ void __launch_bounds__(kPairBlock) pair_backward_heads(DevModel m, De
 // A wave takes an atom: its pairs inside r_c are queued (ring_append), up to
 // 64 at a time get their radial functions one pair per lane, and run as
 // blocks of 16 columns.  Gradients go out head-interleaved, gpair[p][h][3]
-// (192 contiguous bytes a pair at 16 heads), and their sum over the row to
-// own[i][h][3], so the gather reads the reverse pairs only.
+// (192 contiguous bytes a pair at 16 heads), and their sum over the row, [h][3],
+// to the place of the atom's first coefficients in psibar (only this wave reads
+// them), so the gather reads the reverse pairs only.
 // What bounds it: the VALU work of forming and splitting the pairs' products
 // and, once an atom, its coefficients, at two waves a SIMD (28,160 atoms, 16
 // heads: 245 us against 471 us one pair per lane; the gather 102 against 180).
@@ -196,9 +197,8 @@ __device__ __forceinline__ Split3 split3_of(F value) {
 }
 
 __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu(2)))
-    pair_backward_rows(DevModel m, DevSystem sys, const float* __restrict__ psibar, float* __restrict__ gpair,
-                        float* __restrict__ own, float* __restrict__ virial, int nh,
-                        const float* __restrict__ head_c) {
+    pair_backward_rows(DevModel m, DevSystem sys, float* psibar, float* __restrict__ gpair,
+                       float* __restrict__ virial, int nh, const float* __restrict__ head_c) {
   extern __shared__ float s_beta[];
   __shared__ RowsWave s_wave[kHeadsAtoms];
   constexpr int NP = kS * kPacked;
@@ -396,7 +396,8 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
   for (int k = 0; k < 12; ++k) sum[k] = row16_sum(sum[k]);
   if (col == 0) {
-    float* o = own + ((int64_t)i * nh + 4 * uq) * 3;
+    static_assert(3 * kMaxHeads <= kS * kPacked, "the sums fit the atom's coefficients");
+    float* o = psibar + (int64_t)i * (kS * kPacked) + 12 * uq;
 #pragma unroll
     for (int k = 0; k < 12; ++k)
       if (4 * uq + k / 3 < nh) o[k] = sum[k];
@@ -417,8 +418,8 @@ __global__ void __launch_bounds__(kPairBlock) __attribute__((amdgpu_waves_per_eu
 // holds the gradients of all heads and the kernel writes the mean force and
 // the per-atom force variance (1/M) sum_m |F^m - Fbar|^2: kGatherHeads, one set
 // per head ([M][gstride][3]); kGatherRecords, one record per pair ([P][M][3],
-// a wave per atom), with the rows' sums sum_{q in row k} g_q in own
-// ([N][M][3]), so that only the reverse pairs are read
+// a wave per atom), with the rows' sums sum_{q in row k} g_q at
+// own[100 k] ([M][3]), so that only the reverse pairs are read
 // float4 q of x (elements 4q .. 4q+3) with the elements outside [e0, e1)
 // read as zero; the float4 that ends past the array (end elements), or any
 // float4 of an array that is not 16-byte aligned, is read element by element
@@ -679,7 +680,7 @@ __global__ void __launch_bounds__(kPairBlock) finish(int M, DevSystem sys, const
           const float* flat = (const float*)part;
           float x = 0.0f;
           for (int k = 0; k < G; ++k) x += flat[4 * (k * Q + q / V) + q % V];
-          tot[q] = own[(int64_t)i * E + q] - x;
+          tot[q] = own[(int64_t)i * (kS * kPacked) + q] - x;
         }
         wave_lds_sync();
 #pragma unroll

@@ -1300,7 +1300,8 @@ struct TrainLayout {
   int64_t rcK, rcN;    // rows per chunk
   int sp_blocks;       // blocks of the per-species sums
   int64_t K;           // weight-product rows
-  int kchunks;         // split-K chunks the partial buffers hold
+  int64_t wg_rows;     // rows per split-K chunk
+  int kchunks;         // split-K chunks
   int beta_blocks;
 };
 
@@ -1324,7 +1325,13 @@ static int64_t weight_rows(int64_t K, int HP) {
   return best;
 }
 
-TrainLayout train_layout(int n_atoms, int HP, int nsp) {
+// widths that are multiples of the staged kernel's block tile take it; BF16
+// products and narrower widths keep whole chunks of kWgRows
+static int64_t product_rows(int64_t K, int HP, bool bf16) {
+  return HP % kWgBlk == 0 && !bf16 ? weight_rows(K, HP) : kWgRows;
+}
+
+TrainLayout train_layout(int n_atoms, int HP, int nsp, bool bf16) {
   TrainLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1334,7 +1341,8 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   };
   const size_t N = (size_t)n_atoms;
   L.K = ((int64_t)N + kRowAtoms - 1) / kRowAtoms * 16;
-  L.kchunks = (int)((L.K + kWgRowsMin - 1) / kWgRowsMin);
+  L.wg_rows = product_rows(L.K, HP, bf16);
+  L.kchunks = (int)((L.K + L.wg_rows - 1) / L.wg_rows);
   L.beta_blocks = 256;
   L.psi = take(4 * N * 100);
   L.psidot = take(4 * N * 100);
@@ -1344,12 +1352,18 @@ TrainLayout train_layout(int n_atoms, int HP, int nsp) {
   L.Y1 = take(4 * (size_t)L.K * HP);
   L.X2 = take(4 * (size_t)L.K * HP);
   L.Y2 = take(4 * (size_t)L.K * HP);
-  L.gbar = take(4 * N * kFP);
-  L.gdbar = take(4 * N * kFP);
   L.w3g = take(4 * N * HP);
   L.qsig = take(4 * N);
+  // the invariants' adjoints are read before the weight products write their
+  // partials: one region for both
+  const size_t shared = off;
+  L.gbar = take(4 * N * kFP);
+  L.gdbar = take(4 * N * kFP);
+  const size_t adjoints_end = off;
+  off = shared;
   L.part1 = take(4 * (size_t)L.kchunks * kFP * HP);
   L.part2 = take(4 * (size_t)L.kchunks * HP * HP);
+  off = std::max(off, adjoints_end);
   const size_t nslots = (size_t)nsp * nsp * kS * kMaxBasis;
   L.bpart = take(4 * (size_t)L.beta_blocks * nslots);
   L.rcN = N > 0 ? ((int64_t)N + kColChunks - 1) / kColChunks : 1;
@@ -1371,7 +1385,9 @@ bool train_supported(const DevModel& m) {
   return m.n_species <= kMaxSpecies && (m.HP1 == 64 || m.HP1 == 128 || m.HP1 == 256 || m.HP1 == 512);
 }
 
-size_t train_workspace_bytes(int n_atoms, int HP, int nsp) { return train_layout(n_atoms, HP, nsp).bytes; }
+size_t train_workspace_bytes(int n_atoms, int HP, int nsp, bool bf16) {
+  return train_layout(n_atoms, HP, nsp, bf16).bytes;
+}
 
 struct TrainNetArgs {
   const double* ebar;
@@ -1416,7 +1432,7 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
                            float* dL_dpos, float* gpos, int head, int heads, hipStream_t s) {
   const int HP = m.HP1;
   const int nsp = m.n_species;
-  const TrainLayout L = train_layout(sys.n_atoms, HP, nsp);
+  const TrainLayout L = train_layout(sys.n_atoms, HP, nsp, bf16);
   if (ws_bytes < L.bytes) return GMNN_ERR_WORKSPACE;
   char* W = (char*)ws;
   float* psi = (float*)(W + L.psi);
@@ -1484,13 +1500,11 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
                        psibar, psidotbar, bpart);
   }
   // weight products, split over chunks of rows, partials summed in chunk order:
-  // two parts per operand on the BF16 path, three on the FP32 path; widths
-  // that are multiples of the staged kernel's block tile take it
+  // two parts per operand on the BF16 path, three on the FP32 path
   const bool staged = HP % kWgBlk == 0;
-  const int64_t wg_rows = (staged && !bf16) ? weight_rows(L.K, HP) : kWgRows;
-  const int kch = (int)((L.K + wg_rows - 1) / wg_rows);
+  const int kch = L.kchunks;
   if (kch > 0) {
-    const WeightProducts g{{X1, X2}, {Y1, Y2}, {part1, part2}, HP, L.K, wg_rows};
+    const WeightProducts g{{X1, X2}, {Y1, Y2}, {part1, part2}, HP, L.K, L.wg_rows};
     if (staged)
       hipLaunchKernelGGL(bf16 ? weight_grad_staged<2> : weight_grad_staged<3>,
                          dim3((kFP + HP) / kWgBlk * (HP / kWgBlk), kch), dim3(256), 0, s, g);
