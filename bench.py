@@ -179,8 +179,11 @@ def run_path(g, A, model, system, nl, precision, steps, warmup, events, plan="au
         # small systems run moments, readout and pair backward in one launch
         stage_ms = {"fused_tile": stage_ms["pair_moments"], "finish": stage_ms["finish"]}
     elif ev.plan["readout"] != A.GMNN_READOUT_STREAM:
-        # the tile readout is one kernel (invariants, network, invariant backward)
-        stage_ms = {"pair_moments": stage_ms["pair_moments"], "readout_tile": stage_ms["readout_features"],
+        # the readout in one bracket, or, where its tiles would need several
+        # rounds, in the streamed kernels' three: all of it, one empty bracket's
+        # cost (taken off below) included
+        readout = sum(stage_ms[k] for k in ("readout_features", "readout_network", "readout_backward"))
+        stage_ms = {"pair_moments": stage_ms["pair_moments"], "readout_tile": readout - 2 * overhead,
                     "pair_backward": stage_ms["pair_backward"], "finish": stage_ms["finish"]}
     stage_ms = {k: max(v - overhead, 0.0) for k, v in stage_ms.items()}
     stage_ms["_event_overhead"] = overhead

@@ -305,7 +305,10 @@ typedef struct gmnn_plan {
 
 /* Resolve the zero fields of `plan` (NULL: all zero) for these shapes and
  * flags into `resolved` (may be NULL).  GMNN_ERR_UNSUPPORTED if the plan
- * cannot run them, GMNN_ERR_INVALID_ARG for an unknown field value.  Host only. */
+ * cannot run them, GMNN_ERR_INVALID_ARG for an unknown field value.  A plan
+ * names the form of the evaluation; two forms run on other kernels at some
+ * sizes, as stated above, and are resolved under their own name: TILE on
+ * STREAM's kernels, and FP32 tiles of 8 atoms as tiles of 16.  Host only. */
 gmnn_status gmnn_resolve_plan(const gmnn_model* m, const gmnn_system* sys, uint32_t flags,
                               const gmnn_plan* plan, gmnn_plan* resolved);
 
@@ -350,13 +353,15 @@ gmnn_status gmnn_energy_forces_udd(const gmnn_model* m, const gmnn_system* sys,
  * and right after each kernel stage, for profiling: stage_events[2k] /
  * [2k+1] bracket stage k =
  *   0 pair moments (FUSED: the tile kernel, which also covers stages 1-4)
- *   1 invariants (streamed readout; the tile readout's one kernel covers 1-3)
- *   2 network forward and backward (streamed readout)
- *   3 invariant backward (streamed readout)
+ *   1 invariants (the streamed readout's kernel); where 16-atom tiles run
+ *     the readout, and with GMNN_WANT_FORCE_VAR, the whole readout
+ *   2 network forward and backward (the streamed readout's kernel)
+ *   3 invariant backward (the streamed readout's kernel)
  *   4 pair backward
  *   5 force gather + per-structure reductions
  * (GMNN_TIMED_EVENTS = 12 events, created by the caller with hipEventCreate;
- * NULL: none).  A stage a plan does not run gets two adjacent events. */
+ * NULL: none).  A stage that is not run gets two adjacent events; a TILE
+ * readout that runs on STREAM's kernels is bracketed as STREAM's. */
 #define GMNN_TIMED_STAGES 6
 #define GMNN_TIMED_EVENTS (2 * GMNN_TIMED_STAGES)
 gmnn_status gmnn_energy_forces_timed(const gmnn_model* m, const gmnn_system* sys,
@@ -365,9 +370,10 @@ gmnn_status gmnn_energy_forces_timed(const gmnn_model* m, const gmnn_system* sys
                                      void* stream, void* const* stage_events);
 
 /* Autotuner: runs gmnn_energy_forces under every plan these shapes support
- * (2 warm-up calls, then `reps` calls each bracketed by hipEvents on
- * `stream`), and returns in *best the plan of least median time.  The
- * candidates and their median / minimum times in microseconds go to
+ * (of plans that run the same kernels only the one that names them; 2 warm-up
+ * calls, then `reps` calls each bracketed by hipEvents on `stream`), and
+ * returns in *best the plan of least median time.  The candidates and their
+ * median / minimum times in microseconds go to
  * entries[0 .. min(max_entries, *n_entries)) (entries may be NULL when
  * max_entries is 0).  Synchronises `stream`; `out` ends holding the results
  * of the chosen plan.  Same workspace as gmnn_energy_forces.  The choice

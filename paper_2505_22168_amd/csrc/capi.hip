@@ -112,6 +112,11 @@ static bool tall_tiles(const gmnn_model* m, int n_atoms) {
   return rounds > (packed_layout(m->hidden1, m->hidden2, m->n_heads).HP1 >= 512 ? 1 : 2);
 }
 
+// whether a plan's head-mean readout runs on the streamed kernels
+static bool streams_readout(const Plan& P, const gmnn_model* m, int n_atoms, uint32_t flags) {
+  return P.stream || (!P.fused && !(flags & GMNN_WANT_FORCE_VAR) && tall_tiles(m, n_atoms));
+}
+
 // Atoms per fused tile at launch: a second round of 8-atom tiles takes longer
 // than one of 16-atom tiles (FP32 2x256, 3000 atoms: 90.5 against 51.3 us per
 // evaluation; 2000 atoms, one round: 51.2 against 49.6).  BF16 keeps the
@@ -626,7 +631,7 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   float* head_w = (float*)(W + L.head_w);
   const bool fused = P.fused;
   const int ta = launch_tile_atoms(P.ta, bf16, N);
-  const bool stream_readout = P.stream || (!fused && !var && tall_tiles(m, N));
+  const bool stream_readout = streams_readout(P, m, N, flags);
   // One backward per head.  Readout: the tile runs an atom's heads one after
   // the other, the streamed kernels several at a time, with swish' of both
   // layers and dE/dG of a group of heads in memory that is free until the pair
@@ -887,6 +892,10 @@ gmnn_status gmnn_autotune(const gmnn_model* m, const gmnn_system* sys, const gmn
       if (resolve_plan(m, sys, flags, &cand, P) != GMNN_OK) continue;
       // warm-up (also surfaces argument errors before anything is timed)
       for (int w = 0; w < 2 && st == GMNN_OK; ++w)
+      // a plan that would run another candidate's kernels is timed as that one
+      // alone: a TILE readout on the streamed kernels, 8-atom tiles as 16-atom ones
+      if (streams_readout(P, m, sys->n_atoms, flags) != P.stream) continue;
+      if (launch_tile_atoms(P.ta, (flags & GMNN_PREC_BF16) != 0, sys->n_atoms) != P.ta) continue;
         st = gmnn_energy_forces_plan(m, sys, nl, flags, &cand, out, workspace, workspace_bytes, stream);
       for (int r = 0; r < reps && st == GMNN_OK; ++r) {
         if (hipEventRecord(e0, s) != hipSuccess) st = GMNN_ERR_HIP;
