@@ -330,12 +330,12 @@ static EfLayout ef_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
   L.psibar = take(4 * N * kS * kPacked * nh);
   L.atomic_e = take(4 * N * (size_t)m->n_heads);
   L.virial = take(4 * 9 * N);
+  L.gpair = take(12 * (size_t)nl->capacity * nh);  // gpair, g, dg: one run (head_scratch)
   L.g = take(stream_g_bytes((int)N, (flags & GMNN_PREC_BF16) != 0));
   L.dg = take(stream_dg_bytes((int)N));
   L.partial = take(8 * (size_t)(kMaxHeads + 9) * sys->n_structs * reduce_chunks(sys));
   L.counters = take(4 * (size_t)sys->n_structs);
   L.tilerec = take(8 * (size_t)(kMaxHeads + 9) * ((N + 7) / 8));  // fused: one record per tile of >= 8 atoms
-  L.gpair = take(12 * (size_t)nl->capacity * nh);  // gpair, g, dg: one run (head_scratch)
   // uncertainty bias: head weights c [B][kMaxHeads] and weighted W3 vectors [B][HP2]
   L.head_c = take(4 * (size_t)kMaxHeads * sys->n_structs);
   L.head_w = take(4 * (size_t)packed_layout(m->hidden1, m->hidden2, m->n_heads).HP2 * sys->n_structs);
@@ -345,11 +345,10 @@ static EfLayout ef_layout(const gmnn_model* m, const gmnn_system* sys, const gmn
 
 // Scratch of the streamed per-head backwards inside an evaluation's
 // workspace: swish' [2][N][HP] in the per-pair gradients' region, and dE/dG of
-// `group` heads in the rest of it, or, where that is larger, in the G and
-// dE/dG regions (adjacent, two heads).  Groups of at most kHeadGroupBytes keep
-// dE/dG between its two kernels inside the 256 MB last-level cache.  False if
-// the list is too short to leave the room: the readout tile runs the heads
-// one after the other then.
+// `group` heads in the rest of it and the G and dE/dG regions behind it.
+// Groups of at most kHeadGroupBytes keep dE/dG between its two kernels inside
+// the 256 MB last-level cache.  False if the list is too short to leave the
+// room: the readout tile runs the heads one after the other then.
 struct HeadScratch {
   float* dsw = nullptr;
   float* dG = nullptr;
@@ -360,14 +359,14 @@ static bool head_scratch(const gmnn_model* m, const gmnn_neighbors* nl, const Ef
                          HeadScratch& hs) {
   if (N == 0) return false;
   const size_t HP = (size_t)packed_layout(m->hidden1, m->hidden2, m->n_heads).HP1;
-  const size_t pairs = 12 * (size_t)nl->capacity * nh, one = 4 * (size_t)kFP * N;
+  const size_t one = 4 * (size_t)kFP * N;
   const size_t dsw = (2 * 4 * HP * N + 255) & ~size_t(255);
-  if (dsw > pairs) return false;
-  const size_t rest = (pairs - dsw) / one;
+  if (dsw > 12 * (size_t)nl->capacity * nh) return false;  // (G is read while swish' is written)
+  const size_t rest = (L.dg + stream_dg_bytes(N) - L.gpair - dsw) / one;  // two at least: G and dE/dG
   hs.dsw = (float*)(W + L.gpair);
-  hs.dG = rest > 2 ? (float*)(W + L.gpair + dsw) : (float*)(W + L.g);
+  hs.dG = (float*)(W + L.gpair + dsw);
   // whole blocks of four heads, at least one where there is room
-  const int most = (int)std::min<size_t>(std::max<size_t>(rest, 2), std::max<size_t>(kHeadGroupBytes / one, 4));
+  const int most = (int)std::min<size_t>(rest, std::max<size_t>(kHeadGroupBytes / one, 4));
   hs.group = std::min(nh, most >= 4 ? most / 4 * 4 : most);
   return true;
 }
@@ -636,19 +635,22 @@ static gmnn_status ef_run(const gmnn_model* m, const gmnn_system* sys, const gmn
   // the other, the streamed kernels several at a time, with swish' of both
   // layers and dE/dG of a group of heads in memory that is free until the pair
   // backward (the per-pair gradients' region) or after the forward (G, dE/dG).
-  // Streaming wins from kManyHeads heads on at any size (2x128 BF16, 8 heads:
-  // 87.6 against 125 us at 64 atoms, 264 against 318 at 8192), and below that
-  // once the tile needs a second round of the compute units (4 heads: 191
-  // against 207 us at 8192 atoms, but 134 against 113 at 4096); three heads
-  // and less in FP32 stay on the tile (2x256, 3 heads: 267 against 237 us).
+  // Streaming wins from kManyHeads heads on (8 heads, 64 to 2048 atoms: 2x64 BF16
+  // 78 to 110 us against 101 to 129, 2x256 97 to 130 against 121 to 150, 2x512
+  // 125 to 181 against 171 to 201, FP32 2x256 137 to 170 against 163 to 192), and
+  // below that once the tile needs a second round of the compute units (2x64
+  // BF16, 4 heads: 130 against 151 us at 4200 atoms, 2x128 134 against 113 at
+  // 4096); three heads and less in FP32 stay on the tile (2x256, 3 heads: 267
+  // against 237 us).
   // Pair backward: the matrix form has 16 rows whatever the heads, the lane
-  // form's time grows with them; from kRowHeads heads on the matrix form wins
-  // (2x128 BF16, evaluation at 512, 4096 and 28,160 atoms: 6 heads 94, 141 and
-  // 618 us against 97, 144 and 634; 4 heads 72, 111 and 500 against 75, 114
-  // and 484).
-  constexpr int kManyHeads = 8, kRowHeads = 6;
+  // form's time grows with them and with the atoms, so the matrix form takes
+  // kManyHeads heads at any size and kRowHeads from kRowAtomsMin atoms on (2x64
+  // BF16, 6 heads: 82.6 against 80.9 us at 256 atoms, 83.5 against 82.2 at 512, 87.4
+  // against 89.4 at 768, 95.1 against 98.3 at 1536; 4 heads at 2x128: 72, 111 and
+  // 500 us against 75, 114 and 484 at 512, 4096 and 28,160 atoms).
+  constexpr int kManyHeads = 8, kRowHeads = 6, kRowAtomsMin = 768;
   const bool heads_free = !fused && var && !(flags & GMNN_HEADS_TILE);
-  const bool rows = heads_free && nh >= kRowHeads;
+  const bool rows = heads_free && (nh >= kManyHeads || (nh >= kRowHeads && N >= kRowAtomsMin));
   HeadScratch hs;
   const bool stream_heads = heads_free && (nh >= kManyHeads || (N > 16 * kComputeUnits && (bf16 || nh >= 4))) &&
                             head_scratch(m, nl, L, W, N, nh, hs);
@@ -890,12 +892,12 @@ gmnn_status gmnn_autotune(const gmnn_model* m, const gmnn_system* sys, const gmn
       const gmnn_plan cand = {kSched[si], kLanes[li], kReadout[si], kTileAtoms[si]};
       Plan P;
       if (resolve_plan(m, sys, flags, &cand, P) != GMNN_OK) continue;
-      // warm-up (also surfaces argument errors before anything is timed)
-      for (int w = 0; w < 2 && st == GMNN_OK; ++w)
       // a plan that would run another candidate's kernels is timed as that one
       // alone: a TILE readout on the streamed kernels, 8-atom tiles as 16-atom ones
       if (streams_readout(P, m, sys->n_atoms, flags) != P.stream) continue;
       if (launch_tile_atoms(P.ta, (flags & GMNN_PREC_BF16) != 0, sys->n_atoms) != P.ta) continue;
+      // warm-up (also surfaces argument errors before anything is timed)
+      for (int w = 0; w < 2 && st == GMNN_OK; ++w)
         st = gmnn_energy_forces_plan(m, sys, nl, flags, &cand, out, workspace, workspace_bytes, stream);
       for (int r = 0; r < reps && st == GMNN_OK; ++r) {
         if (hipEventRecord(e0, s) != hipSuccess) st = GMNN_ERR_HIP;
