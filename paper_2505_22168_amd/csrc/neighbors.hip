@@ -383,7 +383,7 @@ constexpr int kRowKeys = 512;    // keys of a row sorted in LDS; longer rows are
 //
 // MODE 0: count neighbours of every atom; MODE 1: collect, sort, write.
 template <int MODE>
-__global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
+__global__ void __launch_bounds__(64 * kRowsWaves) __attribute__((amdgpu_waves_per_eu(5))) nl_rows(
     const float* __restrict__ pos, int n_atoms, const StructGrid* __restrict__ grids,
     const int32_t* __restrict__ atom_struct, const int4* __restrict__ atom_img,
     const int64_t* __restrict__ cell_start, const CellAtom* __restrict__ cell_atoms,
@@ -415,11 +415,7 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
   const int s2_lo = g.pbc[2] ? floor_div(lo2, g.nc[2]) : 0;
   const int K = (g.pbc[2] ? floor_div(hi2, g.nc[2]) : 0) - s2_lo + 1;
   const int T = (2 * g.m[0] + 1) * w1 * K;
-  const float inv_k = 1.0f / (float)K, inv_w = 1.0f / (float)w1;
-  // quotients of t by reciprocals in FP32: t + 0.5 is exact, the reciprocal and
-  // the product are off by 2^-24 each, together less than half a step of t
-  // while t < 2^22 (cells far from reduced have more runs and divide)
-  const bool by_reciprocal = T <= (1 << 22);
+  const float inv_k = (1.0f - 0x1p-21f) / (float)K, inv_w = 1.0f / (float)w1;
   int count = 0;
   int base = 0;         // MODE 1: keys collected so far
   int n = 0;            // MODE 1: the row's length
@@ -436,9 +432,18 @@ __global__ void __launch_bounds__(64 * kRowsWaves) nl_rows(
     const int t = t0 + l;
     int cnt = 0, start = 0, swp = 0;
     if (t < T) {
-      // t = (o0 * w1 + o1) * K + o2
-      const int q0 = by_reciprocal ? (int)(((float)t + 0.5f) * inv_k) : t / K, o2 = t - q0 * K;
-      const int q1 = by_reciprocal ? (int)(((float)q0 + 0.5f) * inv_w) : q0 / w1, o1 = q0 - q1 * w1;
+      // t = (o0 * w1 + o1) * K + o2.  inv_k is low by 2^-21, more than the
+      // roundings of t, 1 / K and the product together, so q0 comes out right
+      // or one short (images have 8 bits: q0 < 2^16).  q1: the reciprocal and
+      // the product are off by 2^-24 each, less than half a step of q0 + 0.5.
+      // (Divisions raise the registers past 96 and cost the list of 100,000
+      // atoms 5%; so did this until five waves a SIMD were asked for.)
+      int q0 = (int)((float)t * inv_k), o2 = t - q0 * K;
+      if (o2 >= K) {
+        ++q0;
+        o2 -= K;
+      }
+      const int q1 = (int)(((float)q0 + 0.5f) * inv_w), o1 = q0 - q1 * w1;
       const int cell[2] = {ci[0] + q1 - g.m[0], ci[1] + o1 - g.m[1]};
       int cc[2], sw[3];
       bool ok = true;
