@@ -91,10 +91,6 @@ struct Best {
   int64_t i;
 };
 __device__ inline Best better(Best a, Best b) { return b.v > a.v || (b.v == a.v && b.i < a.i) ? b : a; }
-// entry i with minimum v as `better` compares them.  A NaN compares with
-// nothing, which would leave a pool of them without a valid pick: it counts
-// below every distance and above the entries that have left the pool (-1).
-__device__ inline Best entry(double v, int64_t i) { return Best{isnan(v) ? -0.5 : v, i}; }
 // the block's best entry (ties to the smallest index), for every thread
 __device__ inline Best block_best(Best x, Best* red) {
 #pragma unroll
@@ -204,7 +200,10 @@ __global__ void __launch_bounds__(kSelBlock) sel_step(const double* __restrict__
         v = m < 0.0 ? m : i == pick ? -1.0 : replace ? low : fmin(m, low);
       }
       mind[i] = v;
-      best = better(best, entry(v, i));
+      // a NaN compares with nothing, which would leave a pool of them without a
+      // valid pick: it counts below every distance (the larger of it and a
+      // number is the number)
+      if (!(v < 0.0)) best = better(best, Best{fmax(v, -0.5), i});
     }
   }
   best = block_best(best, s_red);
