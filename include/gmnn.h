@@ -284,11 +284,11 @@ gmnn_status gmnn_energy_forces_noalloc(const gmnn_model* m, const gmnn_system* s
  *                    with GMNN_WANT_FORCE_VAR).
  * lanes_per_atom (8, 16, 32 or 64) is the number of lanes that share one atom's
  * neighbour row in the pair and gather kernels.  Zero fields mean "built-in
- * choice": FUSED with 64 lanes below 16384 atoms where it is allowed (else
- * SPLIT, with 64 lanes below 8192 atoms and 16 beyond), SPLIT with 16 lanes
- * and the STREAM readout from 16384 atoms on (TILE where STREAM is not
- * allowed), 8-atom fused tiles while 16-atom ones would number fewer than
- * 256 (the compute units of one MI355X). */
+ * choice": FUSED with 64 lanes below 16384 atoms (FP32: up to 8192) where it
+ * is allowed (else SPLIT, with 64 lanes below 8192 atoms and 16 beyond), SPLIT
+ * with 16 lanes and the STREAM readout from 16384 atoms on (TILE where STREAM
+ * is not allowed), 8-atom fused tiles while 16-atom ones would number fewer
+ * than 256 (the compute units of one MI355X). */
 #define GMNN_SCHEDULE_AUTO 0
 #define GMNN_SCHEDULE_FUSED 1
 #define GMNN_SCHEDULE_SPLIT 2

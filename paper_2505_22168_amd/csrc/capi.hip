@@ -56,9 +56,16 @@ gmnn_status train_backward(const DevModel& m, const DevSystem& sys, bool bf16, b
 constexpr int kPairThreads = 256;
 // below this many atoms the built-in plan takes the fused (latency) schedule,
 // and no structure of a fused evaluation may be larger (one block sums each
-// structure from its tiles' records); measured: the fused schedule still
-// wins at 11,000 atoms, the streamed readout takes over from 16384
+// structure from its tiles' records).  FP32 takes it up to two rounds of
+// 16-atom tiles (2x256: 106 us at 8000 atoms against 118 split, 144 against 125
+// at 8200, 194 against 159 at 16,000; 2x64: 76 against 89, 101 against 94, 144
+// against 125).  BF16 keeps the line although split evaluations are the faster
+// ones from three rounds on (2x256 118 against 119 us at 11,000 atoms and 153
+// against 137 at 16,000, 2x512 161 against 133 and 211 against 187): the two sum
+// an atom's pairs in different orders, which moves BF16 forces by 1e-4; an
+// autotuned plan takes the faster one
 constexpr int kFusedMaxAtoms = 16384;
+constexpr int kFusedFp32Atoms = 8192;
 // below this many atoms the split schedule's pair kernels take 64 lanes per row
 constexpr int kWideLanesMaxAtoms = 8192;
 // per-structure reductions of per-atom values split into chunks of at most
@@ -127,7 +134,7 @@ static int launch_tile_atoms(int ta, bool bf16, int n_atoms) {
 }
 
 // fills the AUTO fields of `in` (built-in heuristic: the fused schedule for
-// systems of fewer than kFusedMaxAtoms atoms, 64 lanes per atom there and for
+// systems of fewer than kFusedMaxAtoms atoms, FP32 up to kFusedFp32Atoms, 64 lanes per atom there and for
 // split systems below kWideLanesMaxAtoms, 16 beyond, 8-atom fused tiles below
 // one 16-atom tile per compute unit);
 // UNSUPPORTED for a plan these shapes cannot run
@@ -139,7 +146,7 @@ static gmnn_status resolve_plan(const gmnn_model* m, const gmnn_system* sys, uin
   if (sched != GMNN_SCHEDULE_AUTO && sched != GMNN_SCHEDULE_FUSED && sched != GMNN_SCHEDULE_SPLIT)
     return GMNN_ERR_INVALID_ARG;
   if (lpa != 0 && lpa != 8 && lpa != 16 && lpa != 32 && lpa != 64) return GMNN_ERR_INVALID_ARG;
-  const bool small = sys->n_atoms < kFusedMaxAtoms;
+  const bool small = (flags & GMNN_PREC_BF16) ? sys->n_atoms < kFusedMaxAtoms : sys->n_atoms <= kFusedFp32Atoms;
   const bool can_fuse = fused_allowed(m, sys, flags, L.HP1);
   if (sched == GMNN_SCHEDULE_FUSED && !can_fuse) return GMNN_ERR_UNSUPPORTED;
   out.fused = sched == GMNN_SCHEDULE_FUSED || (sched == GMNN_SCHEDULE_AUTO && small && can_fuse);
