@@ -1,7 +1,7 @@
 // Streamed readout for large systems (three launches instead of the tile):
 //
 //   readout_features  invariants of the moments (Section 2.1, eq.
-//                     contraction), 16 atoms per block -> G [N][384] in HBM
+//                     contraction), 6 atoms per block -> G [N][384] in HBM
 //                     (FP32, or for the BF16 network its bf16 high parts
 //                     [N][384] followed by the low parts [N][384])
 //   readout_network   the network, its scale/shift (eq. scale_shift) and its
@@ -410,7 +410,7 @@ __global__ void __launch_bounds__(kRoThreads)
 template <int HP, bool BF16>
 struct HeadsLds {
   static constexpr int NP = BF16 ? 1 : 3;
-  static constexpr int HB = !BF16 && HP >= 512 ? 2 : 4;  // heads per block
+  static constexpr int HB = 4;  // heads per block
   static constexpr int H = HP + 8;
   static constexpr size_t part = (size_t)16 * HB * H;
   static constexpr size_t bytes = 2 * NP * part;
@@ -520,8 +520,10 @@ gmnn_status launch_network_heads(const DevModel& m, const DevSystem& sys, bool b
   if (m.HP1 == HP)                                                                   \
     return bf16 ? launch_heads_t<HP, true>(m, sys, dsw, head0, n_heads, dG, s)       \
                 : launch_heads_t<HP, false>(m, sys, dsw, head0, n_heads, dG, s);
-  CASE(64) CASE(128) CASE(256) CASE(512)
+  CASE(64) CASE(128) CASE(256)
 #undef CASE
+  // (no plan serves FP32 2x512 with one backward per head)
+  if (m.HP1 == 512 && bf16) return launch_heads_t<512, true>(m, sys, dsw, head0, n_heads, dG, s);
   return GMNN_ERR_UNSUPPORTED;
 }
 
