@@ -65,10 +65,12 @@ typedef int32_t gmnn_status;
 #define GMNN_SYNC 8u               /* synchronise and turn device flags into a status */
 #define GMNN_BACKWARD_LANES16 16u  /* gmnn_backward: 16 lanes per atom row in its pair kernels whatever
                                       the atom count (built-in: 64 below 8192 atoms, 16 from there) */
-#define GMNN_HEADS_TILE 64u        /* with GMNN_WANT_FORCE_VAR: every head's backward in the readout tile, one
-                                      order of sums at every size (a training step's forces, whose last bits the
-                                      BF16 double backward amplifies, then do not depend on which kernels the
-                                      size selects) */
+#define GMNN_HEADS_TILE 64u        /* with GMNN_WANT_FORCE_VAR: every head's backward in the readout tile and the
+                                      lane-wise pair backward, whatever the size (a BF16 training step's forces,
+                                      whose last bits its double backward amplifies, then do not change with the
+                                      kernels that larger systems select).  The lanes per row stay the plan's: 64
+                                      below 8192 atoms and 16 from there unless it names them, and with them the
+                                      order of an atom's pair sums */
 #define GMNN_BACKWARD_PER_HEAD 32u /* gmnn_backward: per-head upstream gradients (shallow-ensemble losses) */
 
 /* A ragged batch of B structures with N atoms in total (Section 2.1: a

@@ -86,8 +86,12 @@ __device__ inline float split_low(float v, __bf16 hi) {
   return v - (float)hi;
 }
 
-// the three bf16 parts of an FP32 value, h + m + l = v exactly (8 significant
-// bits each, nearest even, so each remainder is exact in FP32)
+// the three bf16 parts of an FP32 value, 8 significant bits each, nearest even,
+// so each remainder is exact in FP32: h + m + l = v exactly for 2^-103 <= |v| <
+// 3.396e38 (below, the last parts leave the range of normal bf16 values; above,
+// where h rounds to infinity, and for infinities the parts are NaN, so what is
+// not finite stays so.  Clamps that keep those values cost 1-2% of an FP32
+// evaluation: 2195 -> 2234 us for ten MD steps of 10,626 atoms)
 __device__ inline void split3(float v, __bf16& h, __bf16& m, __bf16& l) {
   h = (__bf16)v;
   const float r = split_low(v, h);

@@ -9,12 +9,13 @@
 // FP32 products.  The FP32 MFMA (16x16x4) issues 256 FLOP per cycle and CU,
 // the BF16 one 4096.  An FP32 product is therefore taken from three-part
 // operands, x = h + m + l exactly with 8 significant bits per part, as the six
-// BF16 products whose weight is above 2^-26 of the whole (hh, hm, mh, mm, hl,
-// lh; the dropped ml, lm, ll are below a quarter ulp of each term), with FP32
-// accumulation: 96 cycles per 16x16x32 block instead of 256, and K/32
-// roundings of the sum instead of K.  Measured against 64 bits the
-// errors are no larger than the FP32 MFMA's (energies and forces of the
-// workloads: equal or smaller in every case).
+// BF16 products hh, hm, mh, mm, hl, lh, with FP32 accumulation: 96 cycles per
+// 16x16x32 block instead of 256, and K/32 roundings of the sum instead of K.
+// The dropped ml, lm and ll are at most 2^-24 of a term together, half an ulp
+// (|m| <= 2^-8, |l| <= 2^-17 of a value near 1).  Measured against 64 bits:
+// energies and forces of the workloads equal or smaller than with the FP32
+// MFMA; the nine gradients of a training step (11,200 atoms, 2x512, six sets of
+// inputs) between 0.65 and 1.06 times its error, 0.97 in the mean.
 #pragma once
 
 #include "common.h"

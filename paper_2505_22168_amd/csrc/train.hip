@@ -1409,7 +1409,9 @@ static gmnn_status launch_train_network_t(const DevModel& m, const DevSystem& sy
 static gmnn_status launch_train_network(const DevModel& m, const DevSystem& sys, bool bf16, const TrainNetArgs& t,
                                         hipStream_t s) {
   // 32-atom tiles (half the weight traffic) once 16-atom ones would need a
-  // second round of the 256 compute units, where registers and LDS allow
+  // second round of the 256 compute units, at 2x256: 2x512 FP32 operands of 32
+  // atoms do not fit the LDS (200 KB), and the weights of narrower networks,
+  // 40% of 2x256's and less, leave less to save
   const bool two = sys.n_atoms > 16 * 256;
 #define CASE(HP, AB2)                                                                            \
   if (m.HP1 == HP) {                                                                             \
