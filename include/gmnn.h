@@ -70,7 +70,8 @@ typedef int32_t gmnn_status;
                                       whose last bits its double backward amplifies, then do not change with the
                                       kernels that larger systems select).  The lanes per row stay the plan's: 64
                                       below 8192 atoms and 16 from there unless it names them, and with them the
-                                      order of an atom's pair sums */
+                                      order of an atom's pair sums.  The Python EnsembleTrainer sets it in BF16; a
+                                      step composed of single calls sets it itself */
 #define GMNN_BACKWARD_PER_HEAD 32u /* gmnn_backward: per-head upstream gradients (shallow-ensemble losses) */
 
 /* A ragged batch of B structures with N atoms in total (Section 2.1: a
