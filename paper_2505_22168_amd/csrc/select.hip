@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(1024) ll_features(DevModel m, DevSystem sys, i
 
 constexpr int kSelBlock = 256;   // threads
 constexpr int kSelRows = 16;     // pool rows staged at a time
-constexpr int kSelDims = 288;    // features staged at a time (257 of a 2x256 network in one go)
+constexpr int kSelDims = 288;    // features staged at a time (257 of a 2x256 network in one go, 513 of 2x512 in two)
 constexpr int kSelLd = kSelDims + 1;
 constexpr int kSelPer = kSelRows * kSelDims / kSelBlock;  // values a thread stages
 constexpr int kSelMaxBlocks = 512;
