@@ -1409,9 +1409,11 @@ static gmnn_status launch_train_network_t(const DevModel& m, const DevSystem& sy
 static gmnn_status launch_train_network(const DevModel& m, const DevSystem& sys, bool bf16, const TrainNetArgs& t,
                                         hipStream_t s) {
   // 32-atom tiles (half the weight traffic) once 16-atom ones would need a
-  // second round of the 256 compute units, at 2x256: 2x512 FP32 operands of 32
-  // atoms do not fit the LDS (200 KB), and the weights of narrower networks,
-  // 40% of 2x256's and less, leave less to save
+  // second round of the 256 compute units, at 2x256.  At 2x512 the FP32 operands
+  // of 32 atoms do not fit the LDS (200 KB); narrower networks gain little or
+  // lose (a step of 4900 and of 11,200 atoms, 16- against 32-atom tiles: 2x64 FP32
+  // 341 and 427 us against 346 and 439, BF16 306 and 396 against 311 and 393;
+  // 2x128 303 and 428 against 307 and 413, 304 and 396 against 306 and 396)
   const bool two = sys.n_atoms > 16 * 256;
 #define CASE(HP, AB2)                                                                            \
   if (m.HP1 == HP) {                                                                             \
